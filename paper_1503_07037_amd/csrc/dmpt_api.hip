@@ -644,6 +644,7 @@ dmpt_status run_gemm(const Call& k, const G& g) {
   GemmArgs a{};
   a.eng = k.eng;
   a.Np = k.Np;
+  a.Ne = k.N;
   a.batch = g.batch;
   a.X = g.X;
   a.Y = g.Y;
@@ -719,7 +720,7 @@ dmpt_status run_gemm(const Call& k, const G& g) {
   if (ok_q8_bounds(k, a, g.batch) == false)
     return fail(k.c, DMPT_ERR_ARG, "internal: an int8 operand would leave its workspace");
   // the share of the output tiles computed (below 1 for symmetric outputs)
-  const double tf = (double)gemm_launch_tiles(a) / (double)gemm_tiles(k.eng, k.Np, a.variant, a.acc64);
+  const double tf = gemm_tile_share(a);
   const double n3 = 2.0 * (double)k.Np * k.Np * k.Np * tf;
   if (k.graph) {
     // replays skip converged members on the device: count there
@@ -1314,11 +1315,11 @@ bool ns_pass(const Call& k, int order) {
 }
 
 // Whether a product marked symmetric computes only the lower triangle of
-// tiles (the tile count per side is even; DMPT_FULL_TILES unset; not recorded):
-// then its output is exactly symmetric.
+// tiles (gemm_sym_tiles; DMPT_FULL_TILES unset; not recorded): then its output
+// is exactly symmetric.
 bool sym_tiles(const Call& k) {
-  const int edge = gemm_tile_edge(k.eng, k.Np, variant_for(k.c, k.eng, k.Np), acc64_of(k.c, k.eng));
-  return !k.rec && !k.c->full_tiles && (k.Np / edge) % 2 == 0;
+  return !k.rec && !k.c->full_tiles &&
+         gemm_sym_tiles(k.eng, k.Np, variant_for(k.c, k.eng, k.Np), acc64_of(k.c, k.eng));
 }
 
 // Steps of the iteration from a stored inverse Z_old of T'_old (a pass at
@@ -3063,6 +3064,11 @@ void scratch_setup(ScratchDevice& sd, int device) {
     sd.st = DMPT_ERR_HIP;
     return;
   }
+  if (gemm_prepare() != hipSuccess) {
+    sd.err = "product kernel attributes";
+    sd.st = DMPT_ERR_HIP;
+    return;
+  }
   dmpt_ctx c = new dmpt_ctx_s();
   c->device = device;
   dmpt_default_options(&c->opt);
@@ -3091,7 +3097,7 @@ void scratch_setup(ScratchDevice& sd, int device) {
   c->ws.ref = (double*)take(sizeof(double));
   c->ws.active = (int*)take(sizeof(int));
   c->ws.iters = (int*)take(sizeof(int));
-  c->part_count = std::max<size_t>((size_t)(c->np_max / 128) * (c->np_max / 128),
+  c->part_count = std::max<size_t>((size_t)(c->np_max / 32) * (c->np_max / 32),
                                    (size_t)reduce_blocks((int64_t)c->np_max * c->np_max));
   c->d_part = (double*)take(sizeof(double) * c->part_count);
   c->d_res = (double*)take(sizeof(double) * RES_COUNT);
@@ -3283,8 +3289,10 @@ dmpt_status dmpt_init(dmpt_ctx* out, int device, int64_t n_max, int dirs_max, co
   c->d_res = (double*)alloc(sizeof(double) * RES_COUNT);
   c->d_tally = (double*)alloc(sizeof(double) * 2);
   c->d_cgstat = (int*)alloc(sizeof(int) * 4);
+  // per member: a product's tiles (at most 63 x 63 below the 128-wide tiles, 4096 keeps them all) or
+  // a reduction's blocks
   const size_t tiles = (size_t)(c->np_max / 128) * (c->np_max / 128);
-  c->part_count = std::max<size_t>(tiles, 1024) * dm;
+  c->part_count = std::max<size_t>(tiles, 4096) * dm;
   c->d_part = (double*)alloc(sizeof(double) * c->part_count);
   if (c->debug) {
     c->d_dbg = (double*)alloc(sizeof(double) * (size_t)reduce_blocks(c->np_max * c->np_max));
@@ -3435,6 +3443,7 @@ dmpt_status dmpt_bench_product(dmpt_ctx c, int64_t N, dmpt_prec prec, int varian
   GemmArgs a{};
   a.eng = k.eng;
   a.Np = k.Np;
+  a.Ne = k.Np;
   a.batch = 1;
   a.X = op(k, c->ws.D0, 0, false);
   a.Y = op(k, c->ws.S0, 0, false);
@@ -4286,7 +4295,8 @@ dmpt_status dmpt_mu_newton_batched(dmpt_ctx c, int nsys, const int64_t* Ns, cons
     const size_t per = nn * (c->esize + 2 * np);
     need += per * (size_t)b.m * (2 + 3 * (size_t)dmem + (size_t)(order >= 1 ? 2 * d : 0) +
                                  (size_t)(order >= 2 ? 2 * d : 0));
-    part_need = std::max(part_need, (size_t)(b.Np / 128) * (b.Np / 128) * b.m * dmem);
+    part_need = std::max(part_need, (size_t)gemm_tiles(eng, b.Np, variant_for(c, eng, b.Np), acc64_of(c, eng)) *
+                                        b.m * dmem);
     part_need = std::max(part_need, (size_t)reduce_blocks((int64_t)nn) * b.m * dmem);
   }
   if (c->opt.grouped) {

@@ -99,6 +99,8 @@ struct BOp {
 struct GemmArgs {
   Engine eng;
   int64_t Np;          // all operands are Np x Np, ld = Np
+  int64_t Ne;          // rows and columns that can be non-zero (N <= Ne <= Np): the inner dimension
+                       // stops there
   int batch;           // gridDim.z
   BOp X, Y;            // C = alpha * X * Y^T (+ beta1 C1 + beta2 C2)
   void* C;             // master output
@@ -115,8 +117,7 @@ struct GemmArgs {
   double* cmax;                // int8 kernels, optional: max |C| of every launched tile at
   int64_t cmax_stride;         //   cmax[z * cmax_stride + tile] (the int8 slicing of C then skips its scan)
   int sym;                     // C is symmetric: only the tiles on and below the diagonal are
-                               // computed (when the tile count per side is even and W is unset),
-                               // then the upper triangle is mirrored from the lower one
+                               // computed (gemm_sym_tiles, W unset), then the upper triangle is mirrored from the lower one
   // int8 kernels with sym, optional: each diagonal tile is computed as dsplit
   // blocks over consecutive ranges of the inner index that leave their FP64
   // partial tiles in dpart (room for dpart_members members), then summed in a
@@ -138,8 +139,12 @@ int gemm_variants(Engine eng, int acc64);
 const char* gemm_variant_name(Engine eng, int acc64, int variant);
 int gemm_tile_edge(Engine eng, int64_t Np, int variant, int acc64);
 int gemm_tiles(Engine eng, int64_t Np, int variant, int acc64);
-// Output tiles per member that gemm() computes (fewer than gemm_tiles with sym).
+// Whether gemm() computes only the lower triangle of tiles of a product marked symmetric.
+bool gemm_sym_tiles(Engine eng, int64_t Np, int variant, int acc64);
+// Output tiles per member that gemm() computes (the lower triangle with sym), and their share of
+// all tiles of the kernel's edge.
 int gemm_launch_tiles(const GemmArgs& a);
+double gemm_tile_share(const GemmArgs& a);
 // Tile maxima per member that an int8 product with cmax leaves.
 int gemm_cmax_entries(const GemmArgs& a);
 hipError_t gemm(const GemmArgs& a, hipStream_t s);

@@ -29,7 +29,8 @@
 // are FP64 for every engine.
 //
 // FP64 and FP32: 128 x 128 output tile per 512-thread workgroup (eight waves,
-// 64 x 32 each, two per SIMD), K staged through LDS in a two-stage ring.  Split BF16: 256 x
+// 64 x 32 each, two per SIMD), K staged through LDS in a two-stage ring; FP64
+// below Np = 4096: 32 x 32 or 64 x 64 tiles (f64_edge).  Split BF16: 256 x
 // 256 tiles (128 x 128 per wave) when Np allows, else 128 x 128; the BF16
 // planes are stored in a blocked layout in the MFMA operand order (see
 // plane_off), so operand tiles move as contiguous 1 KB blocks.  Operands are
@@ -42,6 +43,7 @@ namespace dmpt {
 namespace {
 
 typedef double d4v __attribute__((__vector_size__(4 * sizeof(double))));
+typedef double d2f __attribute__((ext_vector_type(2)));
 typedef float f16v __attribute__((__vector_size__(16 * sizeof(float))));
 typedef __bf16 bf8v __attribute__((__vector_size__(8 * sizeof(__bf16))));
 typedef unsigned int u4v __attribute__((__vector_size__(4 * sizeof(unsigned int))));
@@ -66,22 +68,26 @@ __device__ inline void raster(int b, int tiles_m, int tiles_n, int& tm, int& tn)
 }
 
 // With sym, only the tiles on and below the diagonal of the square T x T
-// tile grid (T even): rows p and T - 1 - p hold p + 1 and T - p of them,
-// T + 1 together, so the triangle is the (T / 2) x (T + 1) grid folded at
-// q = p (gemm_launch_tiles gives the launch size).
+// tile grid (gemm_launch_tiles gives the launch size).  T even: rows p and
+// T - 1 - p hold p + 1 and T - p of them, T + 1 together, so the triangle is
+// the (T / 2) x (T + 1) grid folded at q = p.  T odd: rows p and T - 2 - p
+// hold T together and the last row T by itself: the ((T + 1) / 2) x T grid.
 __device__ inline void tile_coords(int b, int tiles_m, int tiles_n, int& tm, int& tn, int sym = 0) {
   if (!sym) {
     raster(b, tiles_m, tiles_n, tm, tn);
     return;
   }
-  const int T = tiles_m;
+  const int T = tiles_m, odd = T & 1;
   int p, q;
-  raster(b, T / 2, T + 1, p, q);
-  if (q <= p) {
+  raster(b, (T + odd) / 2, T + 1 - odd, p, q);
+  if (odd && p == (T - 1) / 2) {
+    tm = T - 1;
+    tn = q;
+  } else if (q <= p) {
     tm = p;
     tn = q;
   } else {
-    tm = T - 1 - p;
+    tm = T - 1 - odd - p;
     tn = q - p - 1;
   }
 }
@@ -225,7 +231,7 @@ __device__ __forceinline__ void gemm_f64_tile(const GemmArgs& a, int z, int bx, 
   gload(0);
   swrite(0);
   __syncthreads();
-  const int nk = (int)(Np / BK);
+  const int nk = (int)((a.Ne + BK - 1) / BK);
   for (int kt = 0; kt < nk; ++kt) {
     const int buf = kt & 1;
     if (kt + 1 < nk) gload((kt + 1) * BK);
@@ -280,6 +286,305 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f64_grouped(const GemmArgs* __
   const int tiles = (int)((a.Np / BM) * (a.Np / BN));
   const int local = b - start[p];
   gemm_f64_tile<BK, NW>(a, local / tiles, local % tiles, tiles);
+}
+
+// Direct form for products that leave most of the chip idle with 128 x 128
+// tiles (see f64_edge): TM x TM output tile per workgroup (TM 32 or 64), KS
+// waves per 32 x 32 quadrant that take the 16-wide k chunks in turn, so even
+// an Np = 128 product runs on 16 CUs with a serial chain of one or two chunks
+// instead of 16 LDS stages on one CU.  Each lane loads four consecutive k of a
+// row (two 16-byte loads; the four lane groups together one 128-byte line)
+// straight into registers: both operands then hold k = 4 (lane / 16) + e in
+// element e, the same order on both sides, which is all the MFMA needs.  No
+// LDS in the k loop, the next chunk's loads run under the current chunk's 16
+// MFMAs.  The KS partial tiles are summed through LDS in a fixed order.  With
+// sym the block writes its tile and the mirrored one from LDS, so no
+// mirroring pass follows.
+template <int TM>
+constexpr int f64_direct_ld() { return TM + 1; }
+template <int TM, int KS>
+constexpr size_t f64_direct_lds() { return (size_t)KS * TM * f64_direct_ld<TM>() * sizeof(double); }
+
+// Epilogue of the FP64 kernels whose KS k groups each hold partial 32 x 32
+// quadrants (acc of wave (qm, qn, ks)) of a TM x TM tile: the partial tiles
+// meet in LDS (f64_direct_lds bytes) and are summed in the order of ks.  With
+// sym the block writes its tile and the mirrored one.
+template <int TM, int KS>
+__device__ __forceinline__ void f64_partial_epilogue(const GemmArgs& a, int z, int bx, int nbx, int tm, int tn, int qm,
+                                                     int qn, int ks, const d4v (&acc)[2][2], double* s, double* red) {
+  constexpr int THREADS = (TM / 32) * (TM / 32) * KS * 64;
+  constexpr int LD = f64_direct_ld<TM>(), PART = TM * LD;
+  constexpr int PER = TM * TM / THREADS;
+  static_assert(PER >= 1, "at least one output element per thread");
+  const int64_t Np = a.Np;
+  const int tid = threadIdx.x, lane = tid & 63;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        s[ks * PART + (qm * 32 + i * 16 + 4 * r + (lane >> 4)) * LD + qn * 32 + j * 16 + (lane & 15)] = acc[i][j][r];
+  __syncthreads();
+  const bool diag = a.sym && tm == tn;
+  double dsum = 0.0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = tid + u * THREADS, r = e / TM, c = e % TM;
+    if (diag && c > r) continue;
+    double v = s[r * LD + c];
+#pragma unroll
+    for (int p = 1; p < KS; ++p) v += s[p * PART + r * LD + c];
+    v = epi<double>(a, z, (int64_t)tm * TM + r, (int64_t)tn * TM + c, v, dsum);
+    if (a.sym) s[r * LD + c] = v;
+  }
+  if (a.sym) {
+    __syncthreads();
+    double* C = (double*)a.C + z * a.sC;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int e = tid + u * THREADS, r = e / TM, c = e % TM;
+      if (!diag || c > r) C[((int64_t)tn * TM + r) * Np + (int64_t)tm * TM + c] = s[c * LD + r];
+    }
+  }
+  if (a.W) {
+    const double t = block_sum(dsum, red);
+    if (tid == 0) a.partials[(int64_t)z * nbx + bx] = t;
+  }
+}
+
+template <int TM, int KS>
+__device__ __forceinline__ void gemm_f64_direct_tile(const GemmArgs& a, int z, int bx, int nbx) {
+  constexpr int QS = TM / 32, NQ = QS * QS, NW = NQ * KS;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ double red[NW];
+  if (a.active && !a.active[z]) return;
+  count_member(a, bx);
+  const int64_t Np = a.Np;
+  int tm, tn;
+  tile_coords(bx, (int)(Np / TM), (int)(Np / TM), tm, tn, a.sym);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int quad = wave % NQ, ks = wave / NQ;
+  const int qm = quad / QS, qn = quad % QS;
+  const int64_t lrow = (int64_t)(lane & 15) * Np + 2 * (lane >> 4);
+  const double* X = (const double*)a.X.m + (z / a.X.div) * a.X.stride + ((int64_t)tm * TM + qm * 32) * Np + lrow;
+  const double* Y = (const double*)a.Y.m + (z / a.Y.div) * a.Y.stride + ((int64_t)tn * TM + qn * 32) * Np + lrow;
+  d4v acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (d4v){0.0, 0.0, 0.0, 0.0};
+  struct Frag {
+    d2f v[2][2];  // [16-row group][half of the four k]
+  };
+  auto load = [&](Frag& x, Frag& y, int ch) {
+    const int64_t k0 = (int64_t)ch * 16;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        x.v[i][h] = *(const d2f*)(X + (int64_t)i * 16 * Np + k0 + 8 * h);
+        y.v[i][h] = *(const d2f*)(Y + (int64_t)i * 16 * Np + k0 + 8 * h);
+      }
+  };
+  auto mma = [&](const Frag& x, const Frag& y) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.v[i][e >> 1][e & 1], y.v[j][e >> 1][e & 1],
+                                                           acc[i][j], 0, 0, 0);
+  };
+  // a tile that lies in the padding has a zero product
+  const int nch = (tm * TM < a.Ne && tn * TM < a.Ne) ? (int)((a.Ne + 15) >> 4) : 0;
+  Frag x0, y0, x1, y1;
+  int ch = ks;
+  if (ch < nch) load(x0, y0, ch);
+  while (ch < nch) {
+    if (ch + KS < nch) load(x1, y1, ch + KS);
+    mma(x0, y0);
+    ch += KS;
+    if (ch >= nch) break;
+    if (ch + KS < nch) load(x0, y0, ch + KS);
+    mma(x1, y1);
+    ch += KS;
+  }
+  f64_partial_epilogue<TM, KS>(a, z, bx, nbx, tm, tn, qm, qn, ks, acc, (double*)smem, red);
+}
+
+template <int TM, int KS>
+__global__ __launch_bounds__((TM / 32) * (TM / 32) * KS * 64) void k_gemm_f64_direct(GemmArgs a) {
+  gemm_f64_direct_tile<TM, KS>(a, blockIdx.z, blockIdx.x, gridDim.x);
+}
+
+template <int TM, int KS>
+__global__ __launch_bounds__((TM / 32) * (TM / 32) * KS * 64) void k_gemm_f64_direct_grouped(
+    const GemmArgs* __restrict__ list, const int* __restrict__ start, int nprob) {
+  int p = 0;
+  const int b = blockIdx.x;
+  while (p + 1 < nprob && b >= start[p + 1]) ++p;
+  const GemmArgs& a = list[p];
+  const int tiles = (int)((a.Np / TM) * (a.Np / TM));
+  const int local = b - start[p];
+  gemm_f64_direct_tile<TM, KS>(a, local / tiles, local % tiles, tiles);
+}
+
+// 64 x 64 output tile, KS groups of four waves (32 x 32 each) that take the
+// 16-wide k chunks in turn, operands staged through LDS (rows of 128 bytes
+// padded to 144: the 16-byte fragment reads of 16 rows fall on different
+// banks), two LDS stages and one register stage.
+constexpr int kF64LdRow = 18;  // doubles per staged row
+template <int KS>
+constexpr size_t f64_lds64_lds() {
+  const size_t stage = (size_t)KS * 2 * 2 * 64 * kF64LdRow * sizeof(double);
+  return stage > f64_direct_lds<64, KS>() ? stage : f64_direct_lds<64, KS>();
+}
+
+template <int KS>
+__device__ __forceinline__ void gemm_f64_lds64_tile(const GemmArgs& a, int z, int bx, int nbx) {
+  constexpr int NW = 4 * KS;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ double red[NW];
+  if (a.active && !a.active[z]) return;
+  count_member(a, bx);
+  const int64_t Np = a.Np;
+  int tm, tn;
+  tile_coords(bx, (int)(Np / 64), (int)(Np / 64), tm, tn, a.sym);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int quad = wave & 3, ks = wave >> 2;
+  const int qm = quad >> 1, qn = quad & 1;
+  const int gt = tid & 255;  // thread within its k group
+  // this thread's 16-byte pieces of a chunk: rows gt / 8 and gt / 8 + 32 of either operand, piece gt % 8
+  const int64_t goff = (int64_t)(gt >> 3) * Np + 2 * (gt & 7);
+  const double* X = (const double*)a.X.m + (z / a.X.div) * a.X.stride + (int64_t)tm * 64 * Np + goff;
+  const double* Y = (const double*)a.Y.m + (z / a.Y.div) * a.Y.stride + (int64_t)tn * 64 * Np + goff;
+  double* base = (double*)smem + (size_t)ks * 2 * 2 * 64 * kF64LdRow;  // [stage][operand][row][18]
+  const int woff = (gt >> 3) * kF64LdRow + 2 * (gt & 7);
+  d2f gx[2], gy[2];
+  auto gload = [&](int ch) {
+    const int64_t k0 = (int64_t)ch * 16;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      gx[i] = *(const d2f*)(X + (int64_t)i * 32 * Np + k0);
+      gy[i] = *(const d2f*)(Y + (int64_t)i * 32 * Np + k0);
+    }
+  };
+  auto swrite = [&](int st) {
+    double* d = base + st * 2 * 64 * kF64LdRow + woff;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      *(d2f*)(d + i * 32 * kF64LdRow) = gx[i];
+      *(d2f*)(d + (64 + i * 32) * kF64LdRow) = gy[i];
+    }
+  };
+  d4v acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (d4v){0.0, 0.0, 0.0, 0.0};
+  const int nch = (tm * 64 < a.Ne && tn * 64 < a.Ne) ? (int)((a.Ne + 15) >> 4) : 0;
+  const int rounds = (nch + KS - 1) / KS;  // the same for every group (the barriers)
+  if (ks < nch) {
+    gload(ks);
+    swrite(0);
+    if (ks + KS < nch) gload(ks + KS);
+  }
+  __syncthreads();
+  const int foff = (lane & 15) * kF64LdRow + 2 * (lane >> 4);
+  for (int rd = 0; rd < rounds; ++rd) {
+    const int ch = ks + rd * KS;
+    if (ch < nch) {
+      const double* sx = base + (rd & 1) * 2 * 64 * kF64LdRow + qm * 32 * kF64LdRow + foff;
+      const double* sy = base + ((rd & 1) * 2 + 1) * 64 * kF64LdRow + qn * 32 * kF64LdRow + foff;
+      d2f xv[2][2], yv[2][2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          xv[i][h] = *(const d2f*)(sx + i * 16 * kF64LdRow + 8 * h);
+          yv[i][h] = *(const d2f*)(sy + i * 16 * kF64LdRow + 8 * h);
+        }
+      if (ch + KS < nch) {
+        swrite((rd + 1) & 1);
+        if (ch + 2 * KS < nch) gload(ch + 2 * KS);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[i][e >> 1][e & 1], yv[j][e >> 1][e & 1], acc[i][j], 0,
+                                                             0, 0);
+    }
+    __syncthreads();
+  }
+  f64_partial_epilogue<64, KS>(a, z, bx, nbx, tm, tn, qm, qn, ks, acc, (double*)smem, red);
+}
+
+template <int KS>
+__global__ __launch_bounds__(KS * 256) void k_gemm_f64_lds64(GemmArgs a) {
+  gemm_f64_lds64_tile<KS>(a, blockIdx.z, blockIdx.x, gridDim.x);
+}
+
+template <int KS>
+__global__ __launch_bounds__(KS * 256) void k_gemm_f64_lds64_grouped(const GemmArgs* __restrict__ list,
+                                                                     const int* __restrict__ start, int nprob) {
+  int p = 0;
+  const int b = blockIdx.x;
+  while (p + 1 < nprob && b >= start[p + 1]) ++p;
+  const GemmArgs& a = list[p];
+  const int tiles = (int)((a.Np / 64) * (a.Np / 64));
+  const int local = b - start[p];
+  gemm_f64_lds64_tile<KS>(a, local / tiles, local % tiles, tiles);
+}
+
+// Default FP64 tile edge by padded size.  A 128 x 128 tile occupies a CU for
+// Np / 128 * 18 us whatever the grid, so it pays only when the tiles fill the
+// 256 CUs several times.  Measured per product, full / symmetric (us; 128-wide
+// tiles, 64-wide ones, 32-wide ones):  Np 128: 23 / 23, 9 / 10, 5.2 / 5.5;  512:
+// 78 / 81, 23 / 24, 12 / 12;  768: 115 / 118, 34 / 34, 38 / 27;  1024: 151 / 156,
+// 45 / 44, 67 / 51;  2048: 321 / 314, 321 / 241;  2432: 648 / 647, 568 / 297;
+// 3072: 1565 / 807, 1076 / 596;  4096: 2187 / 1675, 2396 / 1368 (full products
+// of three members at 4096: 6.1 and 6.7 ms, the 128-wide tiles' 68 TFLOP/s
+// against 62).
+int f64_edge(int64_t Np) { return Np <= 512 ? 32 : (Np < 4096 ? 64 : 128); }
+// Symmetric products keep the 64-wide tiles: twice the granularity, and the
+// mirrored tile is written from LDS instead of by a mirroring pass.
+int f64_sym_edge(int64_t Np) { return Np <= 512 ? 32 : 64; }
+// k groups per block: with no more blocks than CUs every block has its CU to
+// itself, and more waves hide the latency of its serial k loop (Np = 1024, one
+// full product: 45 us with 4 groups, 49 with 2; three members: 132 and 129).
+bool f64_few_blocks(int blocks) { return blocks <= 256; }
+
+template <class K>
+hipError_t f64_attr(K* kernel, size_t lds) {
+  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+hipError_t prepare_f64_small() {
+  hipError_t e;
+  if ((e = f64_attr(k_gemm_f64_direct<32, 8>, f64_direct_lds<32, 8>()))) return e;
+  if ((e = f64_attr(k_gemm_f64_direct<32, 4>, f64_direct_lds<32, 4>()))) return e;
+  if ((e = f64_attr(k_gemm_f64_direct_grouped<32, 4>, f64_direct_lds<32, 4>()))) return e;
+  if ((e = f64_attr(k_gemm_f64_lds64<4>, f64_lds64_lds<4>()))) return e;
+  if ((e = f64_attr(k_gemm_f64_lds64<2>, f64_lds64_lds<2>()))) return e;
+  return f64_attr(k_gemm_f64_lds64_grouped<2>, f64_lds64_lds<2>());
+}
+
+hipError_t launch_f64_small(const GemmArgs& a, int edge, int tiles, hipStream_t s) {
+  const dim3 grid((unsigned)tiles, 1, (unsigned)a.batch);
+  const bool few = f64_few_blocks(tiles * a.batch);
+  if (edge == 32) {
+    if (few) hipLaunchKernelGGL((k_gemm_f64_direct<32, 8>), grid, dim3(512), (f64_direct_lds<32, 8>()), s, a);
+    else hipLaunchKernelGGL((k_gemm_f64_direct<32, 4>), grid, dim3(256), (f64_direct_lds<32, 4>()), s, a);
+  } else {
+    if (few) hipLaunchKernelGGL((k_gemm_f64_lds64<4>), grid, dim3(1024), (f64_lds64_lds<4>()), s, a);
+    else hipLaunchKernelGGL((k_gemm_f64_lds64<2>), grid, dim3(512), (f64_lds64_lds<2>()), s, a);
+  }
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ FP32
@@ -1128,7 +1433,8 @@ hipError_t launch_i8_variant_grouped(int variant, const GemmArgs* list, const in
 
 // Kernel variants of each engine, chosen per padded size by the autotuner
 // (0 is the default):
-//   FP64  0: BK 8, 8 waves   1: BK 16, 8 waves   2: BK 8, 4 waves
+//   FP64  0: 32 x 32 or 64 x 64 tiles by size, 128 x 128 (BK 8, 8 waves) from Np = 4096 on (f64_edge)
+//         1: 128 x 128, BK 16, 8 waves   2: 128 x 128, BK 8, 4 waves
 //   FP32  0: BK 32, 8 waves  1: BK 16, 8 waves   2: BK 32, 4 waves
 //   split BF16  0: 256 x 256 tiles where Np allows (else 128)   1: 128 x 128 tiles
 //   (the 6-product kernel with FP64 slice sums has 128 x 128 tiles only)
@@ -1147,7 +1453,7 @@ int gemm_variants(Engine eng, int acc64) {
 }
 
 const char* gemm_variant_name(Engine eng, int acc64, int v) {
-  static const char* f64[3] = {"FP64 BK 8, 8 waves", "FP64 BK 16, 8 waves", "FP64 BK 8, 4 waves"};
+  static const char* f64[3] = {"FP64 tile edge by size", "FP64 BK 16, 8 waves", "FP64 BK 8, 4 waves"};
   static const char* f32[3] = {"FP32 BK 32, 8 waves", "FP32 BK 16, 8 waves", "FP32 BK 32, 4 waves"};
   static const char* bf[2] = {"BF16 256 x 256 tiles", "BF16 128 x 128 tiles"};
   static const char* i8[4] = {"int8 BK 32, 8 waves of 32 x 64", "int8 BK 32, 8 waves of 64 x 32",
@@ -1160,9 +1466,11 @@ const char* gemm_variant_name(Engine eng, int acc64, int v) {
   return bf[v];
 }
 
-// Output tile edge of the kernel `gemm` uses for an engine, size and variant:
-// the 256-wide split-BF16 kernel when Np and the variant allow it.
+// Output tile edge of the kernel `gemm` uses for an engine, size and variant
+// (symmetric FP64 products: f64_sym_edge): the 256-wide split-BF16 kernel when
+// Np and the variant allow it.
 int gemm_tile_edge(Engine eng, int64_t Np, int variant, int acc64) {
+  if (eng == Engine::F64 && variant == 0) return f64_edge(Np);
   const bool bf = eng == Engine::BF16S2 || (eng == Engine::BF16S3 && !acc64);
   if (bf && variant == 0 && Np % 256 == 0) return 256;
   return BM;
@@ -1172,6 +1480,7 @@ int gemm_tile_edge(Engine eng, int64_t Np, int variant, int acc64) {
 // default, once, before any launch (and so never inside a graph capture).
 hipError_t gemm_prepare() {
   hipError_t e;
+  if ((e = prepare_f64_small())) return e;
   if ((e = prepare_bf16<2, 128, 32, 4>())) return e;
   if ((e = prepare_bf16<3, 128, 32, 4>())) return e;
   if ((e = prepare_bf16<3, 128, 32, 8, 1>())) return e;
@@ -1192,10 +1501,32 @@ int gemm_tiles(Engine eng, int64_t Np, int variant, int acc64) {
   return (int)((Np / e) * (Np / e));
 }
 
+// Even counts of the engine's tiles per side; FP64 products also with an odd
+// count of 128-wide tiles once the full grid of 32- or 64-wide ones exceeds
+// the 256 CUs (up to there half the blocks take the same time: Np = 640, 100
+// blocks or 55).
+bool gemm_sym_tiles(Engine eng, int64_t Np, int variant, int acc64) {
+  if (eng == Engine::F64) return Np / BM % 2 == 0 || gemm_tiles(eng, Np, variant, acc64) > 256;
+  return (Np / gemm_tile_edge(eng, Np, variant, acc64)) % 2 == 0;
+}
+
+static bool sym_applies(const GemmArgs& a) {
+  return a.sym && !a.W && gemm_sym_tiles(a.eng, a.Np, a.variant, a.acc64);
+}
+
+static int launch_edge(const GemmArgs& a) {
+  if (a.eng == Engine::F64 && a.variant == 0 && sym_applies(a)) return f64_sym_edge(a.Np);
+  return gemm_tile_edge(a.eng, a.Np, a.variant, a.acc64);
+}
+
 int gemm_launch_tiles(const GemmArgs& a) {
-  const int T = (int)(a.Np / gemm_tile_edge(a.eng, a.Np, a.variant, a.acc64));
-  if (a.sym && !a.W && T % 2 == 0) return T / 2 * (T + 1);
-  return T * T;
+  const int T = (int)(a.Np / launch_edge(a));
+  return sym_applies(a) ? T * (T + 1) / 2 : T * T;
+}
+
+double gemm_tile_share(const GemmArgs& a) {
+  const int T = (int)(a.Np / launch_edge(a));
+  return (double)gemm_launch_tiles(a) / ((double)T * T);
 }
 
 // Whether gemm() computes the diagonal tiles of a symmetric product in parts:
@@ -1204,8 +1535,7 @@ int gemm_launch_tiles(const GemmArgs& a) {
 static bool diag_split(const GemmArgs& a) {
   const int T = (int)(a.Np / 128);
   return (a.eng == Engine::I8S4 || a.eng == Engine::I8S3) && a.variant <= 1 && a.dpart && a.dsplit >= 2 &&
-         a.dsplit <= 8 && a.batch <= a.dpart_members && T >= 8 && a.Np / 32 >= a.dsplit &&
-         gemm_launch_tiles(a) < T * T;
+         a.dsplit <= 8 && a.batch <= a.dpart_members && T >= 8 && a.Np / 32 >= a.dsplit && sym_applies(a);
 }
 
 int gemm_cmax_entries(const GemmArgs& a) {
@@ -1298,13 +1628,14 @@ __global__ __launch_bounds__(256) void k_diag_sum(GemmArgs a) {
 hipError_t gemm_launch(const GemmArgs& a, int tiles, hipStream_t s);
 
 hipError_t gemm(const GemmArgs& a0, hipStream_t s) {
-  if (a0.Np <= 0 || a0.Np % BM != 0 || a0.batch <= 0 || a0.X.div < 1 || a0.Y.div < 1 || a0.variant < 0 ||
+  if (a0.Np <= 0 || a0.Np % BM != 0 || a0.Ne < 1 || a0.Ne > a0.Np || a0.batch <= 0 || a0.X.div < 1 || a0.Y.div < 1 || a0.variant < 0 ||
       a0.variant >= gemm_variants(a0.eng, a0.acc64))
     return hipErrorInvalidValue;
   GemmArgs a = a0;
-  const int full = gemm_tiles(a.eng, a.Np, a.variant, a.acc64);
   int tiles = gemm_launch_tiles(a);
-  a.sym = tiles < full ? 1 : 0;
+  const int edge = launch_edge(a);
+  a.sym = sym_applies(a) ? 1 : 0;
+  if (a.eng == Engine::F64 && edge < BM) return launch_f64_small(a, edge, tiles, s);
   const int T = (int)(a.Np / 128);
   if (a.sym && diag_split(a)) {
     a.sym = 2;
@@ -1364,7 +1695,11 @@ hipError_t gemm_grouped(Engine eng, int variant, int acc64, int edge, const Gemm
     case Engine::I8S4: return launch_i8_variant_grouped<4>(variant, list, start, nprob, blocks, s);
     case Engine::I8S3: return launch_i8_variant_grouped<3>(variant, list, start, nprob, blocks, s);
     case Engine::F64:
-      if (variant == 1) hipLaunchKernelGGL((k_gemm_f64_grouped<16, 8>), dim3(blocks), dim3(8 * 64), 0, s, list, start, nprob);
+      if (edge == 32)
+        hipLaunchKernelGGL((k_gemm_f64_direct_grouped<32, 4>), dim3(blocks), dim3(256), (f64_direct_lds<32, 4>()), s, list, start, nprob);
+      else if (edge == 64)
+        hipLaunchKernelGGL((k_gemm_f64_lds64_grouped<2>), dim3(blocks), dim3(512), (f64_lds64_lds<2>()), s, list, start, nprob);
+      else if (variant == 1) hipLaunchKernelGGL((k_gemm_f64_grouped<16, 8>), dim3(blocks), dim3(8 * 64), 0, s, list, start, nprob);
       else if (variant == 2) hipLaunchKernelGGL((k_gemm_f64_grouped<8, 4>), dim3(blocks), dim3(4 * 64), 0, s, list, start, nprob);
       else hipLaunchKernelGGL((k_gemm_f64_grouped<kF64BK, kF64NW>), dim3(blocks), dim3(kF64NW * 64), 0, s, list, start, nprob);
       return hipGetLastError();

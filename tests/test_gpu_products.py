@@ -1,0 +1,67 @@
+"""GPU tests of the product kernels at the sizes where their tiling can go wrong.
+
+FP64 products go through dmpt_congruence (two full products) against numpy, and
+through the fixed-mu recursion with the shared inverse (symmetric products) against
+the oracle: sizes on both sides of the 16-wide k chunks, the 32- and 64-wide tiles
+(odd and even tile counts), the padding granule and the changes of tile edge.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+@pytest.fixture(scope="module")
+def dm():
+    import paper_1503_07037_amd as m
+    m.load()
+    return m
+
+
+def T(a):
+    return torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device=_dev())
+
+
+@pytest.mark.parametrize("n_max,sizes", [(700, (1, 15, 16, 17, 32, 33, 127, 128, 129, 500, 512, 513, 640, 700)),
+                                         (1400, (1025, 1400, 65)), (4100, (4100, 3969, 130))])
+def test_fp64_products_match_numpy(dm, n_max, sizes):
+    """Z^T A Z by two full products; one context for falling and rising sizes, so stale padding
+    would show.  Each entry is within the bound of two length-N FP64 sums, 4 N eps times the same
+    sums of magnitudes."""
+    rng = np.random.default_rng(5)
+    with dm.Context(n_max, dirs_max=1, prec="fp64") as ctx:
+        for N in sizes:
+            print(f"case fp64 products N={N}", flush=True)
+            Z = rng.standard_normal((N, N))
+            A = rng.standard_normal((N, N))
+            A = 0.5 * (A + A.T)
+            for mode, L, R in ((0, Z.T, Z), (1, Z, Z.T)):
+                B = ctx.congruence(T(Z), T(A), mode).cpu().numpy()
+                ref = L @ A @ R
+                bound = 4 * N * np.finfo(float).eps * (np.abs(L) @ np.abs(A) @ np.abs(R))
+                assert (np.abs(B - ref) <= bound + 1e-300).all()
+
+
+@pytest.mark.parametrize("n_max,sizes", [(700, (2, 31, 64, 97, 129, 384, 449, 513, 577, 640, 700)),
+                                         (1400, (1400, 1153, 96))])
+def test_fp64_symmetric_products_match_the_oracle(dm, n_max, sizes):
+    """P0 at fixed mu with the shared inverse (every product symmetric; odd and even tile counts)."""
+    beta, n, mu = 10.0, 20, 0.05
+    with dm.Context(n_max, dirs_max=0, prec="fp64", solver="hybrid") as ctx:
+        for N in sizes:
+            print(f"case fp64 symmetric products N={N}", flush=True)
+            h0 = workloads.chain_1d(N, 21)
+            P0, _ = ctx.fermi_recursion(T(h0), beta, mu, n)
+            p = P0.cpu().numpy()
+            assert np.array_equal(p, p.T)
+            assert np.abs(p - oracle.density(h0, beta, n, mu)).max() < 1e-12
