@@ -397,7 +397,8 @@ dmpt_status dmpt_congruence(dmpt_ctx ctx, int64_t N, const double* Z, const doub
 /* Product-kernel variants (per engine; 0 is the default):
  *   DMPT_FP64    0: output tile edge by size (32 up to N = 512, 64 below 4096, else 128)
  *                1: 128 x 128 tiles, 16-deep k stages, 8 waves   2: 128 x 128, 8-deep, 4 waves
- *   DMPT_FP32    0: 32-deep k stages, 8 waves  1: 16-deep, 8 waves   2: 32-deep, 4 waves
+ *   DMPT_FP32    0: output tile edge by size (32 up to N = 384, 64 below 4096, else 128)
+ *                1: 128 x 128 tiles, 16-deep k stages, 8 waves   2: 128 x 128, 32-deep, 4 waves
  *   DMPT_BF16X3, DMPT_BF16X6 (options.acc64 = 0)
  *                0: 256 x 256 output tiles where the padded size allows   1: 128 x 128 tiles
  *   DMPT_BF16X6 with options.acc64 = 1: 0 only (128 x 128 tiles, FP64 slice sums)

@@ -375,6 +375,7 @@ struct Call {
   Engine eng;
   int np;                        // planes used by the engine
   int64_t N, Np, nn;             // nn = Np*Np
+  int64_t Ne = 0;                // largest N of the pass's systems where N stands for Np (0: N)
   int64_t stride;                // member stride of every group (elements)
   double tol_cg;                 // relative residual of every solve of this pass
   int m = 1;                     // systems in the pass (members of D0, S0)
@@ -644,7 +645,7 @@ dmpt_status run_gemm(const Call& k, const G& g) {
   GemmArgs a{};
   a.eng = k.eng;
   a.Np = k.Np;
-  a.Ne = k.N;
+  a.Ne = k.Ne > 0 ? k.Ne : k.N;
   a.batch = g.batch;
   a.X = g.X;
   a.Y = g.Y;
@@ -659,8 +660,9 @@ dmpt_status run_gemm(const Call& k, const G& g) {
   a.active = g.active;
   a.variant = variant_for(k.c, k.eng, k.Np);
   a.acc64 = acc64_of(k.c, k.eng);
-  // recorded launches (graph replays, grouped launches) keep every tile
-  a.sym = g.sym && !k.rec && !g.W && !k.c->full_tiles ? 1 : 0;
+  a.sym = g.sym && !g.W && !k.c->full_tiles ? 1 : 0;
+  // recorded launches (grouped): squares only
+  if (k.rec && !gemm_grouped_sym(a)) a.sym = 0;
   if (a.sym && engine_int8(k.eng) && k.c->d_dpart) {
     a.dpart = k.c->d_dpart;
     a.dsplit = k.c->diag_split;
@@ -713,7 +715,7 @@ dmpt_status run_gemm(const Call& k, const G& g) {
     if (ok && a.C1) ok = reg_ok(c, a.C1, span(a.sC1, 1) * es);
     if (ok && a.C2) ok = reg_ok(c, a.C2, span(a.sC2, 1) * es);
     if (ok && a.W) ok = reg_ok(c, a.W, span(a.sW, 1) * es) &&
-                        (size_t)b * gemm_tiles(k.eng, k.Np, a.variant, a.acc64) <= k.part_count;
+                        (size_t)b * gemm_partials(k.eng, k.Np, a.variant, a.acc64) <= k.part_count;
     if (ok && b > 1) ok = a.sC != 0;
     if (!ok) return fail(c, DMPT_ERR_ARG, "internal: a product would leave its workspace");
   }
@@ -726,7 +728,7 @@ dmpt_status run_gemm(const Call& k, const G& g) {
     // replays skip converged members on the device: count there
     a.tally = k.c->d_tally;
     a.tally_m = n3 * engine_terms(k.eng);
-    a.tally_u = 2.0 * (double)k.N * k.N * k.N;
+    a.tally_u = 2.0 * (double)k.N * k.N * k.N * tf;
   }
   const int members = g.counted >= 0 ? g.counted : g.batch;
   const double mf = n3 * engine_terms(k.eng) * members;
@@ -786,10 +788,11 @@ dmpt_status run_gemm(const Call& k, const G& g) {
 
 // Sum the GEMM per-tile partials into out[z*ostride + oidx].
 dmpt_status sum_gemm_partials(const Call& k, int batch, double* out, int ostride, int oidx) {
-  const int tiles = gemm_tiles(k.eng, k.Np, variant_for(k.c, k.eng, k.Np), acc64_of(k.c, k.eng));
+  const int v = variant_for(k.c, k.eng, k.Np);
+  const int count = gemm_partials(k.eng, k.Np, v, acc64_of(k.c, k.eng)), group = gemm_partial_group(k.eng, k.Np, v);
   hipStream_t s = k.c->stream;
   double* part = k.part;
-  EMIT(k, sum_partials(part, tiles, batch, out, ostride, oidx, s));
+  EMIT(k, sum_partials(part, count, batch, out, ostride, oidx, s, group));
   return DMPT_OK;
 }
 
@@ -2179,6 +2182,7 @@ dmpt_status forward_step0(const Call& k) {
   g.Y = op(k, k.c->ws.D0, 0, false);
   g.C = mptr(k, k.c->ws.S0, 0);
   planes_of(k, k.c->ws.S0, 0, g.Cpl);
+  g.sym = k.np == 0;  // bit for bit with FP64 and FP32 products
   STCHK(run_gemm(k, g));
   return solve_order0<T>(k, -1);
 }
@@ -2236,6 +2240,7 @@ dmpt_status adjoint_impl(const Call& k, const double* H0, double beta, double mu
         g.Y = op(k, c->ws.D0, 0, false);
         g.C = mptr(k, c->ws.S0, 0);
         planes_of(k, c->ws.S0, 0, g.Cpl);
+        g.sym = k.np == 0;
         STCHK(run_gemm(k, g));
       }
       // U T' = Ybar (Ybar symmetric), initial guess U = Ybar
@@ -2366,7 +2371,7 @@ struct BatchedPlan {
 size_t bucket_part_need(const Bucket& b, int members, Engine eng, int variant, int acc64) {
   const size_t mem = (size_t)std::max(members, b.m);
   const size_t nn = (size_t)b.Np * b.Np;
-  return std::max((size_t)gemm_tiles(eng, b.Np, variant, acc64), (size_t)reduce_blocks((int64_t)nn)) * mem;
+  return std::max((size_t)gemm_partials(eng, b.Np, variant, acc64), (size_t)reduce_blocks((int64_t)nn)) * mem;
 }
 
 // lin = 1: order 1 with the linear schedule; the response P_J to H1 = I runs
@@ -2395,6 +2400,7 @@ dmpt_status batched_pass(dmpt_ctx c, std::vector<Bucket>& bk, int wsi, int ord, 
     k.eng = eng;
     k.np = engine_planes(eng);
     k.N = bk[b].Np;  // inside the workspace every member is treated as Np x Np
+    for (int i = 0; i < bk[b].m; ++i) k.Ne = std::max(k.Ne, Ns[slot_sys[bk[b].first + i]]);
     k.Np = bk[b].Np;
     k.nn = k.Np * k.Np;
     k.stride = k.nn;
@@ -2563,7 +2569,7 @@ dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned)
     for (size_t b0 = 0; b0 < nb; ++b0) {
       if (used[b0]) continue;
       const GemmArgs& a0 = plan.ops[b0][i].ga;
-      const int edge = gemm_tile_edge(a0.eng, a0.Np, a0.variant, a0.acc64);
+      const int edge = gemm_launch_edge(a0);
       BatchedPlan::Group G;
       G.op = (int)i;
       G.eng = a0.eng;
@@ -2577,12 +2583,12 @@ dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned)
       for (size_t b = b0; b < nb; ++b) {
         const GemmArgs& a = plan.ops[b][i].ga;
         if (used[b] || a.eng != a0.eng || a.variant != a0.variant || a.acc64 != a0.acc64 ||
-            gemm_tile_edge(a.eng, a.Np, a.variant, a.acc64) != edge)
+            gemm_launch_edge(a) != edge)
           continue;
         used[b] = true;
         list.push_back(a);
         starts.push_back(blocks);
-        blocks += a.batch * gemm_tiles(a.eng, a.Np, a.variant, a.acc64);
+        blocks += a.batch * gemm_launch_tiles(a);
         ++G.nprob;
       }
       starts.push_back(blocks);
@@ -3289,10 +3295,9 @@ dmpt_status dmpt_init(dmpt_ctx* out, int device, int64_t n_max, int dirs_max, co
   c->d_res = (double*)alloc(sizeof(double) * RES_COUNT);
   c->d_tally = (double*)alloc(sizeof(double) * 2);
   c->d_cgstat = (int*)alloc(sizeof(int) * 4);
-  // per member: a product's tiles (at most 63 x 63 below the 128-wide tiles, 4096 keeps them all) or
-  // a reduction's blocks
+  // per member: a product's partials (at most 62 x 62 x 2 below the 128-wide tiles) or a reduction's blocks
   const size_t tiles = (size_t)(c->np_max / 128) * (c->np_max / 128);
-  c->part_count = std::max<size_t>(tiles, 4096) * dm;
+  c->part_count = std::max<size_t>(tiles, 8192) * dm;
   c->d_part = (double*)alloc(sizeof(double) * c->part_count);
   if (c->debug) {
     c->d_dbg = (double*)alloc(sizeof(double) * (size_t)reduce_blocks(c->np_max * c->np_max));
@@ -4295,7 +4300,7 @@ dmpt_status dmpt_mu_newton_batched(dmpt_ctx c, int nsys, const int64_t* Ns, cons
     const size_t per = nn * (c->esize + 2 * np);
     need += per * (size_t)b.m * (2 + 3 * (size_t)dmem + (size_t)(order >= 1 ? 2 * d : 0) +
                                  (size_t)(order >= 2 ? 2 * d : 0));
-    part_need = std::max(part_need, (size_t)gemm_tiles(eng, b.Np, variant_for(c, eng, b.Np), acc64_of(c, eng)) *
+    part_need = std::max(part_need, (size_t)gemm_partials(eng, b.Np, variant_for(c, eng, b.Np), acc64_of(c, eng)) *
                                         b.m * dmem);
     part_need = std::max(part_need, (size_t)reduce_blocks((int64_t)nn) * b.m * dmem);
   }

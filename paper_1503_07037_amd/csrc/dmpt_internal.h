@@ -139,12 +139,19 @@ int gemm_variants(Engine eng, int acc64);
 const char* gemm_variant_name(Engine eng, int acc64, int variant);
 int gemm_tile_edge(Engine eng, int64_t Np, int variant, int acc64);
 int gemm_tiles(Engine eng, int64_t Np, int variant, int acc64);
+// Partials of <W, C> per member, and how many consecutive ones are added first (sum_partials' group).
+int gemm_partials(Engine eng, int64_t Np, int variant, int acc64);
+int gemm_partial_group(Engine eng, int64_t Np, int variant);
 // Whether gemm() computes only the lower triangle of tiles of a product marked symmetric.
 bool gemm_sym_tiles(Engine eng, int64_t Np, int variant, int acc64);
 // Output tiles per member that gemm() computes (the lower triangle with sym), and their share of
 // all tiles of the kernel's edge.
 int gemm_launch_tiles(const GemmArgs& a);
 double gemm_tile_share(const GemmArgs& a);
+// Tile edge of the kernel gemm() launches for a, and whether a grouped launch may compute only the
+// lower triangle of its product (squares with the small tiles; a.sym must be 0 otherwise).
+int gemm_launch_edge(const GemmArgs& a);
+bool gemm_grouped_sym(const GemmArgs& a);
 // Tile maxima per member that an int8 product with cmax leaves.
 int gemm_cmax_entries(const GemmArgs& a);
 hipError_t gemm(const GemmArgs& a, hipStream_t s);
@@ -203,9 +210,10 @@ int reduce_blocks(int64_t n_elems);
 template <class T>
 hipError_t dot_partials(const T* x, int64_t sx, const T* y, int64_t sy, int64_t n, int batch,
                         double* partials, hipStream_t s);
-// out[z * ostride + oidx] = sum of partials[z*count .. z*count+count)
+// out[z * ostride + oidx] = sum of partials[z*count .. z*count+count), each run of `group`
+// consecutive ones added in order first
 hipError_t sum_partials(const double* partials, int count, int batch, double* out,
-                        int ostride, int oidx, hipStream_t s);
+                        int ostride, int oidx, hipStream_t s, int group = 1);
 // out[z*ostride] = sum_i x[z][i*ld + i], i < N (trace, FP64 input);
 // aout[z*ostride] = sum_i |x_ii| when aout is not null
 template <class T>

@@ -284,10 +284,19 @@ __global__ __launch_bounds__(kT) void k_dot(const T* __restrict__ x, int64_t sx,
 }
 
 __global__ __launch_bounds__(kT) void k_sum_partials(const double* __restrict__ p, int count,
-                                                     double* out, int ostride, int oidx) {
+                                                     double* out, int ostride, int oidx, int group) {
   const int z = blockIdx.x;
   double s = 0.0;
-  for (int i = threadIdx.x; i < count; i += kT) s += p[(int64_t)z * count + i];
+  p += (int64_t)z * count;
+  if (group == 1) {
+    for (int i = threadIdx.x; i < count; i += kT) s += p[i];
+  } else {
+    for (int i = threadIdx.x; i < count / group; i += kT) {
+      double t = 0.0;
+      for (int g = 0; g < group; ++g) t += p[(int64_t)i * group + g];
+      s += t;
+    }
+  }
   s = block_sum(s);
   if (threadIdx.x == 0) out[z * ostride + oidx] = s;
 }
@@ -1141,9 +1150,10 @@ template hipError_t dot_partials<float>(const float*, int64_t, const float*, int
                                         double*, hipStream_t);
 
 hipError_t sum_partials(const double* partials, int count, int batch, double* out, int ostride,
-                        int oidx, hipStream_t s) {
+                        int oidx, hipStream_t s, int group) {
+  if (group < 1 || count % group) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_sum_partials, dim3(batch), dim3(kT), 0, s, partials, count, out, ostride,
-                     oidx);
+                     oidx, group);
   return hipGetLastError();
 }
 

@@ -29,8 +29,8 @@
 // are FP64 for every engine.
 //
 // FP64 and FP32: 128 x 128 output tile per 512-thread workgroup (eight waves,
-// 64 x 32 each, two per SIMD), K staged through LDS in a two-stage ring; FP64
-// below Np = 4096: 32 x 32 or 64 x 64 tiles (f64_edge).  Split BF16: 256 x
+// 64 x 32 each, two per SIMD), K staged through LDS in a two-stage ring; below
+// Np = 4096: 32 x 32 or 64 x 64 tiles (small_edge).  Split BF16: 256 x
 // 256 tiles (128 x 128 per wave) when Np allows, else 128 x 128; the BF16
 // planes are stored in a blocked layout in the MFMA operand order (see
 // plane_off), so operand tiles move as contiguous 1 KB blocks.  Operands are
@@ -38,6 +38,8 @@
 // index is remapped so that the tiles of one XCD form a contiguous,
 // row-grouped range (better reuse of that XCD's L2).
 #include "dmpt_internal.h"
+
+#include <algorithm>
 
 namespace dmpt {
 namespace {
@@ -148,6 +150,45 @@ __device__ inline double epi(const GemmArgs& a, int z, int64_t row, int64_t col,
   }
   if (a.W) dsum += (double)((const T*)a.W)[z * a.sW + off] * (double)out;
   return (double)out;
+}
+
+// The same for NV elements of one thread at the offsets off(0 .. NV - 1): the
+// addends are all loaded before the first store.  epi() element by element
+// makes every load wait for the store before it (C may be C1, C2 or W), one
+// memory latency per element: 7-10 us per block.  The elements are distinct, so
+// only W == C needs care (<C, C>: the new value).  out: the values written,
+// w: those of W (zero without).  No split planes.
+template <int NV, class Off>
+__device__ __forceinline__ void epi_values(const GemmArgs& a, int z, Off off, const double (&acc)[NV],
+                                           double (&out)[NV], double (&w)[NV]) {
+  double c1[NV], c2[NV];
+  if (a.C1) {
+    const double* p = (const double*)a.C1 + z * a.sC1;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) c1[i] = p[off(i)];
+  }
+  if (a.C2) {
+    const double* p = (const double*)a.C2 + z * a.sC2;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) c2[i] = p[off(i)];
+  }
+  const bool wself = a.W == a.C && a.sW == a.sC;
+  if (a.W && !wself) {
+    const double* p = (const double*)a.W + z * a.sW;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) w[i] = p[off(i)];
+  }
+  double* c = (double*)a.C + z * a.sC;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    double v = a.alpha * acc[i];
+    if (a.C1) v += a.beta1 * c1[i];
+    if (a.C2) v += a.beta2 * c2[i];
+    out[i] = v;
+    if (!a.W) w[i] = 0.0;
+    else if (wself) w[i] = v;
+    c[off(i)] = v;
+  }
 }
 
 __device__ inline double block_max(double v, double* red) {
@@ -288,55 +329,58 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f64_grouped(const GemmArgs* __
   gemm_f64_tile<BK, NW>(a, local / tiles, local % tiles, tiles);
 }
 
-// Direct form for products that leave most of the chip idle with 128 x 128
-// tiles (see f64_edge): TM x TM output tile per workgroup (TM 32 or 64), KS
-// waves per 32 x 32 quadrant that take the 16-wide k chunks in turn, so even
-// an Np = 128 product runs on 16 CUs with a serial chain of one or two chunks
-// instead of 16 LDS stages on one CU.  Each lane loads four consecutive k of a
-// row (two 16-byte loads; the four lane groups together one 128-byte line)
-// straight into registers: both operands then hold k = 4 (lane / 16) + e in
-// element e, the same order on both sides, which is all the MFMA needs.  No
-// LDS in the k loop, the next chunk's loads run under the current chunk's 16
-// MFMAs.  The KS partial tiles are summed through LDS in a fixed order.  With
-// sym the block writes its tile and the mirrored one from LDS, so no
-// mirroring pass follows.
-template <int TM>
-constexpr int f64_direct_ld() { return TM + 1; }
-template <int TM, int KS>
-constexpr size_t f64_direct_lds() { return (size_t)KS * TM * f64_direct_ld<TM>() * sizeof(double); }
+// Tiles per member of problem a in a grouped launch with TM-wide tiles.
+__device__ inline int grouped_tiles(const GemmArgs& a, int TM) {
+  const int T = (int)(a.Np / TM);
+  return a.sym ? T * (T + 1) / 2 : T * T;
+}
 
-// Epilogue of the FP64 kernels whose KS k groups each hold partial 32 x 32
-// quadrants (acc of wave (qm, qn, ks)) of a TM x TM tile: the partial tiles
-// meet in LDS (f64_direct_lds bytes) and are summed in the order of ks.  With
-// sym the block writes its tile and the mirrored one.
+// LDS of the small-tile kernels: KS partial tiles of TM x TM doubles, rows padded by one.
+template <int TM>
+constexpr int small_ld() { return TM + 1; }
 template <int TM, int KS>
-__device__ __forceinline__ void f64_partial_epilogue(const GemmArgs& a, int z, int bx, int nbx, int tm, int tn, int qm,
-                                                     int qn, int ks, const d4v (&acc)[2][2], double* s, double* red) {
+constexpr size_t small_lds() { return (size_t)KS * TM * small_ld<TM>() * sizeof(double); }
+
+// Epilogue of the small-tile FP64 and FP32 kernels, whose KS k groups left
+// their partial TM x TM tiles in LDS (rows of TM + 1 doubles, small_lds bytes;
+// the caller has synchronised): they are summed in the order of ks.  With sym
+// the block writes its tile and the mirrored one.
+template <int TM, int KS>
+__device__ __forceinline__ void partial_epilogue(const GemmArgs& a, int z, int bx, int nbx, int tm, int tn, double* s,
+                                                 double* red) {
   constexpr int THREADS = (TM / 32) * (TM / 32) * KS * 64;
-  constexpr int LD = f64_direct_ld<TM>(), PART = TM * LD;
+  constexpr int LD = small_ld<TM>(), PART = TM * LD;
   constexpr int PER = TM * TM / THREADS;
   static_assert(PER >= 1, "at least one output element per thread");
   const int64_t Np = a.Np;
-  const int tid = threadIdx.x, lane = tid & 63;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        s[ks * PART + (qm * 32 + i * 16 + 4 * r + (lane >> 4)) * LD + qn * 32 + j * 16 + (lane & 15)] = acc[i][j][r];
-  __syncthreads();
+  const int tid = threadIdx.x;
+  // a diagonal tile's elements above the diagonal are computed too (so the loads need no branch) and
+  // then replaced by the mirrored ones
   const bool diag = a.sym && tm == tn;
+  const int64_t base = (int64_t)tm * TM * Np + (int64_t)tn * TM;
+  auto off = [&](int u) {
+    const int e = tid + u * THREADS;
+    return base + (int64_t)(e / TM) * Np + e % TM;
+  };
+  constexpr int NV = PER < 4 ? PER : 4;
   double dsum = 0.0;
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = tid + u * THREADS, r = e / TM, c = e % TM;
-    if (diag && c > r) continue;
-    double v = s[r * LD + c];
+  for (int u0 = 0; u0 < PER; u0 += NV) {
+    double v[NV], out[NV], w[NV];
 #pragma unroll
-    for (int p = 1; p < KS; ++p) v += s[p * PART + r * LD + c];
-    v = epi<double>(a, z, (int64_t)tm * TM + r, (int64_t)tn * TM + c, v, dsum);
-    if (a.sym) s[r * LD + c] = v;
+    for (int u = 0; u < NV; ++u) {
+      const int e = tid + (u0 + u) * THREADS, r = e / TM, c = e % TM;
+      v[u] = s[r * LD + c];
+#pragma unroll
+      for (int p = 1; p < KS; ++p) v[u] += s[p * PART + r * LD + c];
+    }
+    epi_values<NV>(a, z, [&](int u) { return off(u0 + u); }, v, out, w);
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+      const int e = tid + (u0 + u) * THREADS, r = e / TM, c = e % TM;
+      dsum += w[u] * out[u];
+      if (a.sym) s[r * LD + c] = out[u];
+    }
   }
   if (a.sym) {
     __syncthreads();
@@ -353,6 +397,33 @@ __device__ __forceinline__ void f64_partial_epilogue(const GemmArgs& a, int z, i
   }
 }
 
+// The FP64 accumulators of wave (qm, qn, ks): register r of MFMA tile (i, j), lane l holds row
+// 4 r + l / 16, column l % 16.
+template <int TM>
+__device__ __forceinline__ void f64_store_partial(double* s, int ks, int qm, int qn, const d4v (&acc)[2][2]) {
+  constexpr int LD = small_ld<TM>(), PART = TM * LD;
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        s[ks * PART + (qm * 32 + i * 16 + 4 * r + (lane >> 4)) * LD + qn * 32 + j * 16 + (lane & 15)] = acc[i][j][r];
+}
+
+// Direct form for products that leave most of the chip idle with 128 x 128
+// tiles (see small_edge): TM x TM output tile per workgroup (TM 32 or 64), KS
+// waves per 32 x 32 quadrant that take the 16-wide k chunks in turn, so even
+// an Np = 128 product runs on 16 CUs with a serial chain of one or two chunks
+// instead of 16 LDS stages on one CU.  Each lane loads four consecutive k of a
+// row (two 16-byte loads; the four lane groups together one 128-byte line)
+// straight into registers: both operands then hold k = 4 (lane / 16) + e in
+// element e, the same order on both sides, which is all the MFMA needs.  No
+// LDS in the k loop, the next chunk's loads run under the current chunk's 16
+// MFMAs.  The KS partial tiles are summed through LDS in a fixed order.  With
+// sym the block writes its tile and the mirrored one from LDS, so no
+// mirroring pass follows.
 template <int TM, int KS>
 __device__ __forceinline__ void gemm_f64_direct_tile(const GemmArgs& a, int z, int bx, int nbx) {
   constexpr int QS = TM / 32, NQ = QS * QS, NW = NQ * KS;
@@ -411,7 +482,9 @@ __device__ __forceinline__ void gemm_f64_direct_tile(const GemmArgs& a, int z, i
     mma(x1, y1);
     ch += KS;
   }
-  f64_partial_epilogue<TM, KS>(a, z, bx, nbx, tm, tn, qm, qn, ks, acc, (double*)smem, red);
+  f64_store_partial<TM>((double*)smem, ks, qm, qn, acc);
+  __syncthreads();
+  partial_epilogue<TM, KS>(a, z, bx, nbx, tm, tn, (double*)smem, red);
 }
 
 template <int TM, int KS>
@@ -426,7 +499,7 @@ __global__ __launch_bounds__((TM / 32) * (TM / 32) * KS * 64) void k_gemm_f64_di
   const int b = blockIdx.x;
   while (p + 1 < nprob && b >= start[p + 1]) ++p;
   const GemmArgs& a = list[p];
-  const int tiles = (int)((a.Np / TM) * (a.Np / TM));
+  const int tiles = grouped_tiles(a, TM);
   const int local = b - start[p];
   gemm_f64_direct_tile<TM, KS>(a, local / tiles, local % tiles, tiles);
 }
@@ -439,7 +512,7 @@ constexpr int kF64LdRow = 18;  // doubles per staged row
 template <int KS>
 constexpr size_t f64_lds64_lds() {
   const size_t stage = (size_t)KS * 2 * 2 * 64 * kF64LdRow * sizeof(double);
-  return stage > f64_direct_lds<64, KS>() ? stage : f64_direct_lds<64, KS>();
+  return stage > small_lds<64, KS>() ? stage : small_lds<64, KS>();
 }
 
 template <int KS>
@@ -521,7 +594,9 @@ __device__ __forceinline__ void gemm_f64_lds64_tile(const GemmArgs& a, int z, in
     }
     __syncthreads();
   }
-  f64_partial_epilogue<64, KS>(a, z, bx, nbx, tm, tn, qm, qn, ks, acc, (double*)smem, red);
+  f64_store_partial<64>((double*)smem, ks, qm, qn, acc);  // the last round ended with a barrier
+  __syncthreads();
+  partial_epilogue<64, KS>(a, z, bx, nbx, tm, tn, (double*)smem, red);
 }
 
 template <int KS>
@@ -536,55 +611,9 @@ __global__ __launch_bounds__(KS * 256) void k_gemm_f64_lds64_grouped(const GemmA
   const int b = blockIdx.x;
   while (p + 1 < nprob && b >= start[p + 1]) ++p;
   const GemmArgs& a = list[p];
-  const int tiles = (int)((a.Np / 64) * (a.Np / 64));
+  const int tiles = grouped_tiles(a, 64);
   const int local = b - start[p];
   gemm_f64_lds64_tile<KS>(a, local / tiles, local % tiles, tiles);
-}
-
-// Default FP64 tile edge by padded size.  A 128 x 128 tile occupies a CU for
-// Np / 128 * 18 us whatever the grid, so it pays only when the tiles fill the
-// 256 CUs several times.  Measured per product, full / symmetric (us; 128-wide
-// tiles, 64-wide ones, 32-wide ones):  Np 128: 23 / 23, 9 / 10, 5.2 / 5.5;  512:
-// 78 / 81, 23 / 24, 12 / 12;  768: 115 / 118, 34 / 34, 38 / 27;  1024: 151 / 156,
-// 45 / 44, 67 / 51;  2048: 321 / 314, 321 / 241;  2432: 648 / 647, 568 / 297;
-// 3072: 1565 / 807, 1076 / 596;  4096: 2187 / 1675, 2396 / 1368 (full products
-// of three members at 4096: 6.1 and 6.7 ms, the 128-wide tiles' 68 TFLOP/s
-// against 62).
-int f64_edge(int64_t Np) { return Np <= 512 ? 32 : (Np < 4096 ? 64 : 128); }
-// Symmetric products keep the 64-wide tiles: twice the granularity, and the
-// mirrored tile is written from LDS instead of by a mirroring pass.
-int f64_sym_edge(int64_t Np) { return Np <= 512 ? 32 : 64; }
-// k groups per block: with no more blocks than CUs every block has its CU to
-// itself, and more waves hide the latency of its serial k loop (Np = 1024, one
-// full product: 45 us with 4 groups, 49 with 2; three members: 132 and 129).
-bool f64_few_blocks(int blocks) { return blocks <= 256; }
-
-template <class K>
-hipError_t f64_attr(K* kernel, size_t lds) {
-  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
-hipError_t prepare_f64_small() {
-  hipError_t e;
-  if ((e = f64_attr(k_gemm_f64_direct<32, 8>, f64_direct_lds<32, 8>()))) return e;
-  if ((e = f64_attr(k_gemm_f64_direct<32, 4>, f64_direct_lds<32, 4>()))) return e;
-  if ((e = f64_attr(k_gemm_f64_direct_grouped<32, 4>, f64_direct_lds<32, 4>()))) return e;
-  if ((e = f64_attr(k_gemm_f64_lds64<4>, f64_lds64_lds<4>()))) return e;
-  if ((e = f64_attr(k_gemm_f64_lds64<2>, f64_lds64_lds<2>()))) return e;
-  return f64_attr(k_gemm_f64_lds64_grouped<2>, f64_lds64_lds<2>());
-}
-
-hipError_t launch_f64_small(const GemmArgs& a, int edge, int tiles, hipStream_t s) {
-  const dim3 grid((unsigned)tiles, 1, (unsigned)a.batch);
-  const bool few = f64_few_blocks(tiles * a.batch);
-  if (edge == 32) {
-    if (few) hipLaunchKernelGGL((k_gemm_f64_direct<32, 8>), grid, dim3(512), (f64_direct_lds<32, 8>()), s, a);
-    else hipLaunchKernelGGL((k_gemm_f64_direct<32, 4>), grid, dim3(256), (f64_direct_lds<32, 4>()), s, a);
-  } else {
-    if (few) hipLaunchKernelGGL((k_gemm_f64_lds64<4>), grid, dim3(1024), (f64_lds64_lds<4>()), s, a);
-    else hipLaunchKernelGGL((k_gemm_f64_lds64<2>), grid, dim3(512), (f64_lds64_lds<2>()), s, a);
-  }
-  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ FP32
@@ -660,7 +689,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmArgs& a, int z, int bx, 
 #pragma unroll
       for (int r = 0; r < 16; ++r) accd[i][j][r] = 0.0;
     }
-  const int nk = (int)(Np / BK);
+  const int nk = (int)((a.Ne + BK - 1) / BK);
   gload(0);
   swrite(0);
   __syncthreads();
@@ -751,6 +780,265 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_f32_grouped(const GemmArgs* __
   const int tiles = (int)((a.Np / BM) * (a.Np / BN));
   const int local = b - start[p];
   gemm_f32_tile<BK, NW>(a, local / tiles, local % tiles, tiles);
+}
+
+// One 16-wide slice: eight MFMAs into a fresh acur, two values of the previous
+// slice's tile folded into FP64 after each (independent of the MFMAs in flight).
+__device__ __forceinline__ void f32_slice(const float (&xv)[8], const float (&yv)[8], f16v& acur, const f16v& aprev,
+                                          double (&accd)[16]) {
+  f16v zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    acur = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[m], yv[m], m == 0 ? zero : acur, 0, 0, 0);
+    accd[2 * m] += (double)aprev[2 * m];
+    accd[2 * m + 1] += (double)aprev[2 * m + 1];
+  }
+}
+
+// 64 x 64 output tile, four waves of 32 x 32, for the same reason as the small
+// FP64 tiles.  The rounding of the 128 x 128 kernel is kept bit for bit: the
+// same MFMA chain per slice, FP64 sums over the slices in order (so no split
+// of k), and <W, C> partials that the summing kernel can add in the order of
+// that kernel's lanes, waves and tiles (a change of 1e-16 there flips the FP32
+// rounding of an operand now and then, which moves a response by 1e-9).
+// BK of k per stage, two LDS stages and one register stage.  A slice is staged
+// in LDS as FP32, the even k of a row before the odd ones, so a lane reads its
+// eight operands of a slice as two 16-byte pieces (rows padded by 4 words: the
+// pieces of 16 rows fall on different banks).
+constexpr int kF32SmallBK = 32;
+template <int BK>
+constexpr int f32_ld_row() { return BK + 4; }  // floats per staged row
+template <int BK>
+constexpr size_t f32_lds64_lds() {
+  const size_t stage = (size_t)2 * 2 * 64 * f32_ld_row<BK>() * sizeof(float);
+  return stage > small_lds<64, 1>() ? stage : small_lds<64, 1>();
+}
+
+template <int BK>
+__device__ __forceinline__ void gemm_f32_lds64_tile(const GemmArgs& a, int z, int bx, int nbx) {
+  typedef float f4v __attribute__((ext_vector_type(4)));
+  typedef float f2v __attribute__((ext_vector_type(2)));
+  constexpr int LDR = f32_ld_row<BK>(), SL = BK / kF32Slice;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ double chain[2][64];
+  if (a.active && !a.active[z]) return;
+  count_member(a, bx);
+  const int64_t Np = a.Np;
+  int tm, tn;
+  if (a.sym) {
+    tile_coords(bx, (int)(Np / 64), (int)(Np / 64), tm, tn, 1);
+  } else {
+    // the four 64-wide tiles of a 128-wide one are consecutive blocks
+    raster(bx >> 2, (int)(Np / BM), (int)(Np / BN), tm, tn);
+    tm = 2 * tm + ((bx >> 1) & 1);
+    tn = 2 * tn + (bx & 1);
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qm = wave >> 1, qn = wave & 1;
+  // this thread stages row tid / 4 of either operand, four consecutive k of every slice
+  const int64_t goff = (int64_t)(tid >> 2) * Np + 4 * (tid & 3);
+  const double* X = (const double*)a.X.m + (z / a.X.div) * a.X.stride + (int64_t)tm * 64 * Np + goff;
+  const double* Y = (const double*)a.Y.m + (z / a.Y.div) * a.Y.stride + (int64_t)tn * 64 * Np + goff;
+  float* base = (float*)smem;  // [stage][operand][row][LDR]
+  const int woff = (tid >> 2) * LDR + 2 * (tid & 3);
+  d2f gx[SL][2], gy[SL][2];
+  auto gload = [&](int kt) {
+#pragma unroll
+    for (int q = 0; q < SL; ++q)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int64_t k0 = (int64_t)kt * BK + q * kF32Slice + 2 * i;
+        gx[q][i] = *(const d2f*)(X + k0);
+        gy[q][i] = *(const d2f*)(Y + k0);
+      }
+  };
+  auto swrite = [&](int st) {
+#pragma unroll
+    for (int q = 0; q < SL; ++q) {
+      float* d = base + st * 2 * 64 * LDR + woff + q * kF32Slice;
+      *(f2v*)d = f2v{(float)gx[q][0].x, (float)gx[q][1].x};
+      *(f2v*)(d + 8) = f2v{(float)gx[q][0].y, (float)gx[q][1].y};
+      d += 64 * LDR;
+      *(f2v*)d = f2v{(float)gy[q][0].x, (float)gy[q][1].x};
+      *(f2v*)(d + 8) = f2v{(float)gy[q][0].y, (float)gy[q][1].y};
+    }
+  };
+  f16v acc, acc2;
+  double accd[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    acc[r] = acc2[r] = 0.0f;
+    accd[r] = 0.0;
+  }
+  // a tile that lies in the padding has a zero product (Np is a multiple of BK)
+  const int nk = (tm * 64 < a.Ne && tn * 64 < a.Ne) ? (int)((a.Ne + BK - 1) / BK) : 0;
+  if (nk > 0) {
+    gload(0);
+    swrite(0);
+    if (nk > 1) gload(1);
+  }
+  __syncthreads();
+  const int foff = (lane & 31) * LDR + 8 * (lane >> 5);
+  auto slice = [&](int kt, int q, f16v& acur, const f16v& aprev) {
+    const float* sx = base + (kt & 1) * 2 * 64 * LDR + qm * 32 * LDR + foff + q * kF32Slice;
+    const float* sy = base + ((kt & 1) * 2 + 1) * 64 * LDR + qn * 32 * LDR + foff + q * kF32Slice;
+    float xv[8], yv[8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const f4v x4 = *(const f4v*)(sx + 4 * h), y4 = *(const f4v*)(sy + 4 * h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        xv[4 * h + e] = x4[e];
+        yv[4 * h + e] = y4[e];
+      }
+    }
+    if (q == 0 && kt + 1 < nk) {
+      swrite((kt + 1) & 1);
+      if (kt + 2 < nk) gload(kt + 2);
+    }
+    f32_slice(xv, yv, acur, aprev, accd);
+  };
+  static_assert(SL == 2, "the two FP32 tiles alternate within a stage");
+  for (int kt = 0; kt < nk; ++kt) {
+    slice(kt, 0, acc, acc2);  // acc2: the slice before (zero at the start)
+    slice(kt, 1, acc2, acc);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) accd[r] += (double)acc2[r];
+  if (a.sym) {
+    double* s = (double*)smem;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      s[(qm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * small_ld<64>() + qn * 32 + (lane & 31)] = accd[r];
+    __syncthreads();
+    partial_epilogue<64, 1>(a, z, bx, nbx, tm, tn, s, nullptr);
+    return;
+  }
+  const int64_t base_off = ((int64_t)tm * 64 + qm * 32 + 4 * (lane >> 5)) * Np + (int64_t)tn * 64 + qn * 32 + (lane & 31);
+  double out[16], w[16];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    double v8[8], o8[8], w8[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v8[r] = accd[8 * h + r];
+    epi_values<8>(a, z, [&](int r) { return base_off + (int64_t)(16 * h + 8 * (r >> 2) + (r & 3)) * Np; }, v8, o8, w8);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      out[8 * h + r] = o8[r];
+      w[8 * h + r] = w8[r];
+    }
+  }
+  if (!a.W) return;
+  // <W, C>: the 128 x 128 kernel's wave adds the rows of qm = 0 and then those
+  // of qm = 1 lane by lane, so the second wave continues the first one's sums
+  double dsum = 0.0;
+  if (qm == 0) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dsum += w[r] * out[r];
+    chain[qn][lane] = dsum;
+  }
+  __syncthreads();
+  if (qm == 1) {
+    dsum = chain[qn][lane];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dsum += w[r] * out[r];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o, 64);
+    // slot of the 128-wide tile's wave (row half, 32-wide column)
+    if (lane == 0)
+      a.partials[(int64_t)z * nbx * 2 + (bx >> 2) * 8 + ((bx >> 1) & 1) * 4 + (bx & 1) * 2 + qn] = dsum;
+  }
+}
+
+template <int BK>
+__global__ __launch_bounds__(256, 4) void k_gemm_f32_lds64(GemmArgs a) {
+  gemm_f32_lds64_tile<BK>(a, blockIdx.z, blockIdx.x, gridDim.x);
+}
+
+template <int BK>
+__global__ __launch_bounds__(256, 4) void k_gemm_f32_lds64_grouped(const GemmArgs* __restrict__ list,
+                                                                const int* __restrict__ start, int nprob) {
+  int p = 0;
+  const int b = blockIdx.x;
+  while (p + 1 < nprob && b >= start[p + 1]) ++p;
+  const GemmArgs& a = list[p];
+  const int tiles = grouped_tiles(a, 64);
+  const int local = b - start[p];
+  gemm_f32_lds64_tile<BK>(a, local / tiles, local % tiles, tiles);
+}
+
+// ---------------------------------------------------- small tiles: choice and launch
+// Default FP64 and FP32 tile edge by padded size.  A 128 x 128 tile occupies a
+// CU for Np / 128 * 18 us (FP32: 12) whatever the grid, so it pays only when the
+// tiles fill the 256 CUs several times.  Measured per product, full /
+// symmetric (us; 128-wide tiles, 64-wide ones, 32-wide ones):
+//   FP64  Np 128: 23 / 23, 9 / 10, 5.2 / 5.5;  512: 78 / 81, 23 / 24, 12 / 12;  768:
+//   115 / 118, 34 / 34, 38 / 27;  1024: 151 / 156, 45 / 44, 67 / 51;  2048: 321 / 314,
+//   321 / 241;  2432: 648 / 647, 568 / 297;  3072: 1565 / 807, 1076 / 596;  4096: 2187 /
+//   1675, 2396 / 1368 (full products of three members at 4096: 6.1 and 6.7 ms,
+//   the 128-wide tiles' 68 TFLOP/s against 62).
+//   FP32  (with C1, C2 and W) Np 128: 27 full, 16 symmetric, 8.7 / 8.4;  256: 39 / 28, 12.5 /
+//   12.2;  512: 62 / 51, 20 / 20;  1024: 125 / 100, 40 / 36;  2432: 549 / 492, 387 / 195
+//   (three members 1479 / 1272, 1108 / 578);  4096: 1910 / 1737, 1700 / 900 (three members
+//   4.9 ms with either).  VALU work (conversions, FP64 sums of slices) and FP32
+//   MFMAs do not overlap on this chip: 32 such instructions add 170 cycles to a
+//   slice's 530, so 75-85 TFLOP/s is near what this arithmetic allows.
+int small_edge(Engine eng, int64_t Np) {
+  if (eng == Engine::F64 && Np <= 512) return 32;
+  return Np < 4096 ? 64 : 128;
+}
+// Symmetric products keep the 64-wide tiles: twice the granularity, and the
+// mirrored tile is written from LDS instead of by a mirroring pass.
+int small_sym_edge(Engine eng, int64_t Np) { return std::min(64, small_edge(eng, Np)); }
+// k groups per FP64 block: with no more blocks than CUs every block has its CU
+// to itself, and more waves hide the latency of its serial k loop (Np = 1024,
+// one full product: 45 us with 4 groups, 49 with 2; three members: 132 and 129).
+bool few_blocks(int blocks) { return blocks <= 256; }
+
+template <class K>
+hipError_t lds_attr(K* kernel, size_t lds) {
+  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+hipError_t prepare_small() {
+  hipError_t e;
+  if ((e = lds_attr(k_gemm_f64_direct<32, 8>, small_lds<32, 8>()))) return e;
+  if ((e = lds_attr(k_gemm_f64_direct<32, 4>, small_lds<32, 4>()))) return e;
+  if ((e = lds_attr(k_gemm_f64_direct_grouped<32, 4>, small_lds<32, 4>()))) return e;
+  if ((e = lds_attr(k_gemm_f64_lds64<4>, f64_lds64_lds<4>()))) return e;
+  if ((e = lds_attr(k_gemm_f64_lds64<2>, f64_lds64_lds<2>()))) return e;
+  if ((e = lds_attr(k_gemm_f64_lds64_grouped<2>, f64_lds64_lds<2>()))) return e;
+  if ((e = lds_attr(k_gemm_f32_lds64<kF32SmallBK>, f32_lds64_lds<kF32SmallBK>()))) return e;
+  return lds_attr(k_gemm_f32_lds64_grouped<kF32SmallBK>, f32_lds64_lds<kF32SmallBK>());
+}
+
+hipError_t launch_small(const GemmArgs& a, int edge, int tiles, hipStream_t s) {
+  const dim3 grid((unsigned)tiles, 1, (unsigned)a.batch);
+  const bool few = few_blocks(tiles * a.batch);
+  if (a.eng == Engine::F32)
+    hipLaunchKernelGGL(k_gemm_f32_lds64<kF32SmallBK>, grid, dim3(256), f32_lds64_lds<kF32SmallBK>(), s, a);
+  else if (edge == 32 && few)
+    hipLaunchKernelGGL((k_gemm_f64_direct<32, 8>), grid, dim3(512), (small_lds<32, 8>()), s, a);
+  else if (edge == 32) hipLaunchKernelGGL((k_gemm_f64_direct<32, 4>), grid, dim3(256), (small_lds<32, 4>()), s, a);
+  else if (few) hipLaunchKernelGGL(k_gemm_f64_lds64<4>, grid, dim3(1024), f64_lds64_lds<4>(), s, a);
+  else hipLaunchKernelGGL(k_gemm_f64_lds64<2>, grid, dim3(512), f64_lds64_lds<2>(), s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_grouped(Engine eng, int edge, const GemmArgs* list, const int* start, int nprob, int blocks,
+                                hipStream_t s) {
+  const dim3 grid((unsigned)blocks);
+  if (eng == Engine::F32)
+    hipLaunchKernelGGL(k_gemm_f32_lds64_grouped<kF32SmallBK>, grid, dim3(256), f32_lds64_lds<kF32SmallBK>(), s, list,
+                       start, nprob);
+  else if (edge == 32)
+    hipLaunchKernelGGL((k_gemm_f64_direct_grouped<32, 4>), grid, dim3(256), (small_lds<32, 4>()), s, list, start, nprob);
+  else
+    hipLaunchKernelGGL(k_gemm_f64_lds64_grouped<2>, grid, dim3(512), f64_lds64_lds<2>(), s, list, start, nprob);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ split BF16
@@ -1433,9 +1721,10 @@ hipError_t launch_i8_variant_grouped(int variant, const GemmArgs* list, const in
 
 // Kernel variants of each engine, chosen per padded size by the autotuner
 // (0 is the default):
-//   FP64  0: 32 x 32 or 64 x 64 tiles by size, 128 x 128 (BK 8, 8 waves) from Np = 4096 on (f64_edge)
+//   FP64  0: 32 x 32 or 64 x 64 tiles by size, 128 x 128 (BK 8, 8 waves) from Np = 4096 on (small_edge)
 //         1: 128 x 128, BK 16, 8 waves   2: 128 x 128, BK 8, 4 waves
-//   FP32  0: BK 32, 8 waves  1: BK 16, 8 waves   2: BK 32, 4 waves
+//   FP32  0: the same by size, 128 x 128 (BK 32, 8 waves)   1: 128 x 128, BK 16, 8 waves
+//         2: 128 x 128, BK 32, 4 waves
 //   split BF16  0: 256 x 256 tiles where Np allows (else 128)   1: 128 x 128 tiles
 //   (the 6-product kernel with FP64 slice sums has 128 x 128 tiles only)
 //   int8 (both digit counts)  0: BK 32, 8 waves of 32 x 64   1: BK 32, 8 waves of 64 x 32
@@ -1454,7 +1743,7 @@ int gemm_variants(Engine eng, int acc64) {
 
 const char* gemm_variant_name(Engine eng, int acc64, int v) {
   static const char* f64[3] = {"FP64 tile edge by size", "FP64 BK 16, 8 waves", "FP64 BK 8, 4 waves"};
-  static const char* f32[3] = {"FP32 BK 32, 8 waves", "FP32 BK 16, 8 waves", "FP32 BK 32, 4 waves"};
+  static const char* f32[3] = {"FP32 tile edge by size", "FP32 BK 16, 8 waves", "FP32 BK 32, 4 waves"};
   static const char* bf[2] = {"BF16 256 x 256 tiles", "BF16 128 x 128 tiles"};
   static const char* i8[4] = {"int8 BK 32, 8 waves of 32 x 64", "int8 BK 32, 8 waves of 64 x 32",
                               "int8 LDS DMA, BK 64, 8 waves of 32 x 64", "int8 LDS DMA, BK 64, 8 waves of 64 x 32"};
@@ -1467,10 +1756,10 @@ const char* gemm_variant_name(Engine eng, int acc64, int v) {
 }
 
 // Output tile edge of the kernel `gemm` uses for an engine, size and variant
-// (symmetric FP64 products: f64_sym_edge): the 256-wide split-BF16 kernel when
+// (symmetric FP64 and FP32 products: small_sym_edge): the 256-wide split-BF16 kernel when
 // Np and the variant allow it.
 int gemm_tile_edge(Engine eng, int64_t Np, int variant, int acc64) {
-  if (eng == Engine::F64 && variant == 0) return f64_edge(Np);
+  if ((eng == Engine::F64 || eng == Engine::F32) && variant == 0) return small_edge(eng, Np);
   const bool bf = eng == Engine::BF16S2 || (eng == Engine::BF16S3 && !acc64);
   if (bf && variant == 0 && Np % 256 == 0) return 256;
   return BM;
@@ -1480,7 +1769,7 @@ int gemm_tile_edge(Engine eng, int64_t Np, int variant, int acc64) {
 // default, once, before any launch (and so never inside a graph capture).
 hipError_t gemm_prepare() {
   hipError_t e;
-  if ((e = prepare_f64_small())) return e;
+  if ((e = prepare_small())) return e;
   if ((e = prepare_bf16<2, 128, 32, 4>())) return e;
   if ((e = prepare_bf16<3, 128, 32, 4>())) return e;
   if ((e = prepare_bf16<3, 128, 32, 8, 1>())) return e;
@@ -1501,31 +1790,51 @@ int gemm_tiles(Engine eng, int64_t Np, int variant, int acc64) {
   return (int)((Np / e) * (Np / e));
 }
 
+// The small FP32 tiles leave a partial per wave of the 128-wide tile they are part of.
+int gemm_partial_group(Engine eng, int64_t Np, int variant) {
+  return eng == Engine::F32 && variant == 0 && small_edge(eng, Np) < BM ? 8 : 1;
+}
+
+int gemm_partials(Engine eng, int64_t Np, int variant, int acc64) {
+  const int t = gemm_tiles(eng, Np, variant, acc64);
+  return gemm_partial_group(eng, Np, variant) == 8 ? 2 * t : t;
+}
+
 // Even counts of the engine's tiles per side; FP64 products also with an odd
 // count of 128-wide tiles once the full grid of 32- or 64-wide ones exceeds
 // the 256 CUs (up to there half the blocks take the same time: Np = 640, 100
 // blocks or 55).
 bool gemm_sym_tiles(Engine eng, int64_t Np, int variant, int acc64) {
   if (eng == Engine::F64) return Np / BM % 2 == 0 || gemm_tiles(eng, Np, variant, acc64) > 256;
-  return (Np / gemm_tile_edge(eng, Np, variant, acc64)) % 2 == 0;
+  const int edge = eng == Engine::F32 ? BM : gemm_tile_edge(eng, Np, variant, acc64);
+  return (Np / edge) % 2 == 0;
 }
 
+// The FP32 square of a matrix is symmetric bit for bit (the same products in
+// the same order in both triangles), so it needs no even count.
 static bool sym_applies(const GemmArgs& a) {
-  return a.sym && !a.W && gemm_sym_tiles(a.eng, a.Np, a.variant, a.acc64);
+  const bool square = a.X.m == a.Y.m && a.X.stride == a.Y.stride && a.X.div == a.Y.div;
+  return a.sym && !a.W && ((a.eng == Engine::F32 && square) || gemm_sym_tiles(a.eng, a.Np, a.variant, a.acc64));
 }
 
-static int launch_edge(const GemmArgs& a) {
-  if (a.eng == Engine::F64 && a.variant == 0 && sym_applies(a)) return f64_sym_edge(a.Np);
+int gemm_launch_edge(const GemmArgs& a) {
+  if ((a.eng == Engine::F64 || a.eng == Engine::F32) && a.variant == 0 && sym_applies(a))
+    return small_sym_edge(a.eng, a.Np);
   return gemm_tile_edge(a.eng, a.Np, a.variant, a.acc64);
 }
 
+bool gemm_grouped_sym(const GemmArgs& a) {
+  const bool square = a.X.m == a.Y.m && a.X.stride == a.Y.stride && a.X.div == a.Y.div;
+  return (a.eng == Engine::F64 || a.eng == Engine::F32) && square && sym_applies(a) && gemm_launch_edge(a) < BM;
+}
+
 int gemm_launch_tiles(const GemmArgs& a) {
-  const int T = (int)(a.Np / launch_edge(a));
+  const int T = (int)(a.Np / gemm_launch_edge(a));
   return sym_applies(a) ? T * (T + 1) / 2 : T * T;
 }
 
 double gemm_tile_share(const GemmArgs& a) {
-  const int T = (int)(a.Np / launch_edge(a));
+  const int T = (int)(a.Np / gemm_launch_edge(a));
   return (double)gemm_launch_tiles(a) / ((double)T * T);
 }
 
@@ -1633,9 +1942,9 @@ hipError_t gemm(const GemmArgs& a0, hipStream_t s) {
     return hipErrorInvalidValue;
   GemmArgs a = a0;
   int tiles = gemm_launch_tiles(a);
-  const int edge = launch_edge(a);
+  const int edge = gemm_launch_edge(a);
   a.sym = sym_applies(a) ? 1 : 0;
-  if (a.eng == Engine::F64 && edge < BM) return launch_f64_small(a, edge, tiles, s);
+  if ((a.eng == Engine::F64 || a.eng == Engine::F32) && edge < BM) return launch_small(a, edge, tiles, s);
   const int T = (int)(a.Np / 128);
   if (a.sym && diag_split(a)) {
     a.sym = 2;
@@ -1691,15 +2000,13 @@ hipError_t gemm_launch(const GemmArgs& a, int tiles, hipStream_t s) {
 hipError_t gemm_grouped(Engine eng, int variant, int acc64, int edge, const GemmArgs* list, const int* start,
                         int nprob, int blocks, hipStream_t s) {
   if (nprob < 1 || blocks < 1 || variant < 0 || variant >= gemm_variants(eng, acc64)) return hipErrorInvalidValue;
+  if ((eng == Engine::F64 || eng == Engine::F32) && edge < BM)
+    return launch_small_grouped(eng, edge, list, start, nprob, blocks, s);
   switch (eng) {
     case Engine::I8S4: return launch_i8_variant_grouped<4>(variant, list, start, nprob, blocks, s);
     case Engine::I8S3: return launch_i8_variant_grouped<3>(variant, list, start, nprob, blocks, s);
     case Engine::F64:
-      if (edge == 32)
-        hipLaunchKernelGGL((k_gemm_f64_direct_grouped<32, 4>), dim3(blocks), dim3(256), (f64_direct_lds<32, 4>()), s, list, start, nprob);
-      else if (edge == 64)
-        hipLaunchKernelGGL((k_gemm_f64_lds64_grouped<2>), dim3(blocks), dim3(512), (f64_lds64_lds<2>()), s, list, start, nprob);
-      else if (variant == 1) hipLaunchKernelGGL((k_gemm_f64_grouped<16, 8>), dim3(blocks), dim3(8 * 64), 0, s, list, start, nprob);
+      if (variant == 1) hipLaunchKernelGGL((k_gemm_f64_grouped<16, 8>), dim3(blocks), dim3(8 * 64), 0, s, list, start, nprob);
       else if (variant == 2) hipLaunchKernelGGL((k_gemm_f64_grouped<8, 4>), dim3(blocks), dim3(4 * 64), 0, s, list, start, nprob);
       else hipLaunchKernelGGL((k_gemm_f64_grouped<kF64BK, kF64NW>), dim3(blocks), dim3(kF64NW * 64), 0, s, list, start, nprob);
       return hipGetLastError();

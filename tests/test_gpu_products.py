@@ -65,3 +65,16 @@ def test_fp64_symmetric_products_match_the_oracle(dm, n_max, sizes):
             p = P0.cpu().numpy()
             assert np.array_equal(p, p.T)
             assert np.abs(p - oracle.density(h0, beta, n, mu)).max() < 1e-12
+
+
+@pytest.mark.parametrize("n_max,sizes", [(700, (2, 31, 33, 128, 129, 384, 385, 449, 577, 640, 700)), (1400, (1400, 96))])
+def test_fp32_small_tiles_match_the_oracle(dm, n_max, sizes):
+    """P0 at fixed mu with the default FP32 tiles, at the FP32 engine's accuracy (as in the parity tests)."""
+    beta, n, mu = 10.0, 20, 0.05
+    with dm.Context(n_max, dirs_max=0, prec="fp32") as ctx:
+        for N in sizes:
+            print(f"case fp32 products N={N}", flush=True)
+            h0 = workloads.chain_1d(N, 22)
+            p = ctx.fermi_recursion(T(h0), beta, mu, n)[0].cpu().numpy()
+            assert np.array_equal(p, p.T)
+            assert np.abs(p - oracle.density(h0, beta, n, mu)).max() < 1e-6
