@@ -1292,6 +1292,7 @@ typedef int i16v __attribute__((ext_vector_type(16)));
 template <int BK, int NW, int WM, int SD>
 __device__ __forceinline__ void gemm_i8_tile(const GemmArgs& a, int z, int bx, int nbx) {
   constexpr int TM = 128;
+  constexpr int NV = 8;               // elements whose addends the epilogue loads together
   constexpr int S = SD;               // digits read (of the kQ8Slices stored)
   constexpr int W = SD == 4 ? 5 : 3;  // weights kept: 0 .. 4 or 0 .. 2
   constexpr int WN = NW / WM;         // waves along n
@@ -1454,15 +1455,22 @@ __device__ __forceinline__ void gemm_i8_tile(const GemmArgs& a, int z, int bx, i
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = (int64_t)tm * TM + wm * (TM / WM) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int64_t col = (int64_t)tn * TM + wn * (TM / WN) + j * 32 + (lane & 31);
-        double v = (double)acc[W - 1][i][j][r];
+      for (int h = 0; h < 16 / NV; ++h) {
+        const int64_t off = ((int64_t)tm * TM + wm * (TM / WM) + i * 32 + 2 * NV * h + 4 * (lane >> 5)) * Np +
+                            (int64_t)tn * TM + wn * (TM / WN) + j * 32 + (lane & 31);
+        double v[NV], out[NV], wv[NV];
 #pragma unroll
-        for (int w = W - 2; w >= 0; --w) v = v * rb + (double)acc[w][i][j][r];
-        {
-          const double o = epi<double>(e, z, row, col, v * scale, dsum);
-          fmx = o == o ? fmaxf(fmx, __double2float_ru(fabs(o))) : INFINITY;
+        for (int r = 0; r < NV; ++r) {
+          v[r] = (double)acc[W - 1][i][j][NV * h + r];
+#pragma unroll
+          for (int w = W - 2; w >= 0; --w) v[r] = v[r] * rb + (double)acc[w][i][j][NV * h + r];
+          v[r] = v[r] * scale;
+        }
+        epi_values<NV>(e, z, [&](int r) { return off + (int64_t)(8 * (r >> 2) + (r & 3)) * Np; }, v, out, wv);
+#pragma unroll
+        for (int r = 0; r < NV; ++r) {
+          dsum += wv[r] * out[r];
+          fmx = out[r] == out[r] ? fmaxf(fmx, __double2float_ru(fabs(out[r]))) : INFINITY;
         }
       }
   if (e.W) {
@@ -1486,6 +1494,7 @@ __device__ __forceinline__ void gemm_i8_tile(const GemmArgs& a, int z, int bx, i
 template <int NW, int WM, int SD>
 __device__ __forceinline__ void gemm_i8_dma_tile(const GemmArgs& a, int z, int bx, int nbx) {
   constexpr int TM = 128, BK = 64;
+  constexpr int NV = 8;
   constexpr int S = SD;
   constexpr int W = SD == 4 ? 5 : 3;
   constexpr int WN = NW / WM;
@@ -1589,15 +1598,22 @@ __device__ __forceinline__ void gemm_i8_dma_tile(const GemmArgs& a, int z, int b
 #pragma unroll
     for (int j = 0; j < FN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = (int64_t)tm * TM + wm * (TM / WM) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int64_t col = (int64_t)tn * TM + wn * (TM / WN) + j * 32 + (lane & 31);
-        double v = (double)acc[W - 1][i][j][r];
+      for (int h = 0; h < 16 / NV; ++h) {
+        const int64_t off = ((int64_t)tm * TM + wm * (TM / WM) + i * 32 + 2 * NV * h + 4 * (lane >> 5)) * Np +
+                            (int64_t)tn * TM + wn * (TM / WN) + j * 32 + (lane & 31);
+        double v[NV], out[NV], wv[NV];
 #pragma unroll
-        for (int w = W - 2; w >= 0; --w) v = v * rb + (double)acc[w][i][j][r];
-        {
-          const double o = epi<double>(a, z, row, col, v * scale, dsum);
-          fmx = o == o ? fmaxf(fmx, __double2float_ru(fabs(o))) : INFINITY;
+        for (int r = 0; r < NV; ++r) {
+          v[r] = (double)acc[W - 1][i][j][NV * h + r];
+#pragma unroll
+          for (int w = W - 2; w >= 0; --w) v[r] = v[r] * rb + (double)acc[w][i][j][NV * h + r];
+          v[r] = v[r] * scale;
+        }
+        epi_values<NV>(a, z, [&](int r) { return off + (int64_t)(8 * (r >> 2) + (r & 3)) * Np; }, v, out, wv);
+#pragma unroll
+        for (int r = 0; r < NV; ++r) {
+          dsum += wv[r] * out[r];
+          fmx = out[r] == out[r] ? fmaxf(fmx, __double2float_ru(fabs(out[r]))) : INFINITY;
         }
       }
   if (a.W) {
