@@ -80,7 +80,8 @@ struct WS {
   double* pq = nullptr;          // CG <p,Tp> history [member][hstride]
   double* pb = nullptr;          // CG bounds of max |P| for its int8 slices [member][hstride]
   double* ref = nullptr;         // ||rhs||^2 [member]
-  int* active = nullptr;         // CG masks [member]
+  double* rpart = nullptr;       // CG residual partials [member][reduce_blocks(Np^2)]
+  int* active = nullptr;         // CG masks [2][member]
   int* iters = nullptr;          // CG iteration counters [member]
   int* mask0 = nullptr;          // system mask (order-0 members), batched passes only
   int* mask1 = nullptr;          // system mask expanded to [system][direction] members
@@ -171,6 +172,10 @@ struct dmpt_ctx_s {
   double* d_gersh = nullptr;     // 2 + 2 n_max
   double* h_res = nullptr;       // pinned mirror of d_res
   int* h_int = nullptr;          // pinned ints: CG active flags, then iteration counts at kIterSlot
+  // pinned: the state of every member of a solve after each check, written by the device (CgArgs)
+  unsigned long long* h_flag = nullptr;
+  unsigned cg_solves = 0;        // solves begun (tags h_flag)
+  int cg_guess[2] = {1, 1};      // iterations of the last single-member / multi-member solve
   std::string err;
   // product-kernel timing (dmpt_profile)
   bool prof_on = false;
@@ -361,10 +366,14 @@ bool q8_needed(const dmpt_options& o) {
 size_t esize_needed(const dmpt_options&) { return 8; }
 
 // A launch of the recursion step code kept for a grouped replay: a product
-// (its arguments) or any other launch (a closure that issues it).
+// (its arguments), a fused CG launch (its arguments) or any other launch (a
+// closure that issues it).
 struct Op {
   bool gemm = false;
+  bool cg = false;               // a fused CG launch: cgop, ca
   GemmArgs ga{};
+  CgOp cgop = CgOp::Begin;
+  CgArgs ca{};
   std::function<hipError_t()> fn;
 };
 
@@ -796,6 +805,13 @@ dmpt_status sum_gemm_partials(const Call& k, int batch, double* out, int ostride
   return DMPT_OK;
 }
 
+// The squared norm of a solve's initial residual from the partials the product
+// that formed it left, into rr[z][0]; the fused solve sums them itself.
+bool cg_fused(const Call& k) { return k.np == 0 && !engine_int8(k.eng); }
+dmpt_status sum_residual(const Call& k, int batch) {
+  return cg_fused(k) ? DMPT_OK : sum_gemm_partials(k, batch, k.w->rr, k.c->hstride, 0);
+}
+
 // ------------------------------------------------------------------ typed helpers
 template <class T>
 dmpt_status sym_inplace(const Call& k, const Group& g, int z0, int batch, double a) {
@@ -832,6 +848,143 @@ dmpt_status sym_to(const Call& k, const Group& in, const Group& out, int batch, 
 // k_cg_check): warm starts must not freeze the iterate below the tolerance.
 constexpr double kEta = 0.05;
 
+// Issue a fused CG launch, or record it (k.rec).
+dmpt_status cg_emit(const Call& k, CgOp op, const CgArgs& a) {
+  if (k.rec) {
+    Op o;
+    o.cg = true;
+    o.cgop = op;
+    o.ca = a;
+    k.rec->push_back(o);
+    return DMPT_OK;
+  }
+  hipStream_t s = k.c->stream;
+  HIPCHK(k.c, op == CgOp::Begin ? cg_begin(a, s) : (op == CgOp::Xr ? cg_step_xr(a, s) : cg_step_p(a, s)));
+  return DMPT_OK;
+}
+
+// Wait until every member's state after `checks` checks of solve `solve` has
+// arrived in c->h_flag.  The launches that write it are queued, so it arrives,
+// or the stream fails or drains (both end the wait with an error).
+dmpt_status cg_wait(dmpt_ctx c, int batch, unsigned solve, unsigned checks) {
+  for (int z = 0; z < batch; ++z) {
+    auto arrived = [&]() {
+      const unsigned long long v = __atomic_load_n(c->h_flag + z, __ATOMIC_RELAXED);
+      return (unsigned)(v >> 32) == solve && (unsigned)((v >> 16) & 0xffff) >= checks;
+    };
+    for (unsigned spin = 1; !arrived(); ++spin) {
+      if (spin % 4096) continue;
+      const hipError_t e = hipStreamQuery(c->stream);
+      if (e == hipErrorNotReady) continue;
+      if (e != hipSuccess) HIPCHK(c, e);
+      if (!arrived()) return fail(c, DMPT_ERR_HIP, "internal: a solve ended without its check");
+    }
+  }
+  return DMPT_OK;
+}
+
+// cg_solve for FP64 and FP32 products: three launches per iteration and no
+// copy or stream synchronisation.  Without k.graph the launches run ahead of
+// the host's knowledge: as many iterations as the last such solve took, then
+// one more at a time while the state of the iteration before arrives in host
+// memory (converged members skip their work on the device, so iterations
+// queued past the end change nothing).
+dmpt_status cg_solve_fused(const Call& k, const Group& u, int batch, int ydiv, const int* mask) {
+  dmpt_ctx c = k.c;
+  const WS* w = k.w;
+  const int hs = c->hstride;
+  const int v = variant_for(c, k.eng, k.Np);
+  CgArgs a{};
+  a.U = (double*)mptr(k, u, 0);
+  a.R = (double*)mptr(k, w->R, 0);
+  a.P = (double*)mptr(k, w->P, 0);
+  a.Q = (const double*)mptr(k, w->Q, 0);
+  a.n = k.nn;
+  a.stride = k.stride;
+  a.batch = batch;
+  a.gpart = k.part;
+  a.gcount = gemm_partials(k.eng, k.Np, v, acc64_of(c, k.eng));
+  a.ggroup = gemm_partial_group(k.eng, k.Np, v);
+  a.rpart = w->rpart;
+  a.rr = w->rr;
+  a.ref = w->ref;
+  a.hstride = hs;
+  a.tol2 = k.tol_cg * k.tol_cg;
+  a.eta2 = kEta * kEta;
+  a.act = w->active;
+  a.iters = w->iters;
+  a.mask = mask;
+  if (!a.rpart) return fail(c, DMPT_ERR_ARG, "internal: no residual partials");
+  const bool live_known = k.graph || c->prof_on;  // without: the executed products are counted at the end
+  if (!k.graph) {
+    a.hflag = c->h_flag;
+    a.solve = ++c->cg_solves;
+  }
+  STCHK(cg_emit(k, CgOp::Begin, a));
+  auto iteration = [&](int it, int live) -> dmpt_status {
+    // Q = P + 4 P S0  (T' applied on the right), partials of <P, Q>
+    G g;
+    g.X = op(k, w->P, 0, true);
+    g.Y = op(k, w->S0, 0, true);
+    g.Y.div = ydiv;
+    g.C = mptr(k, w->Q, 0);
+    g.sC = k.stride;
+    g.alpha = 4.0;
+    g.C1 = mptr(k, w->P, 0); g.sC1 = k.stride; g.beta1 = 1.0;
+    g.W = mptr(k, w->P, 0); g.sW = k.stride;
+    g.batch = batch;
+    g.active = a.act + (it & 1) * batch;
+    g.counted = live;
+    STCHK(run_gemm(k, g));
+    a.it = it;
+    STCHK(cg_emit(k, CgOp::Xr, a));
+    return cg_emit(k, CgOp::P, a);
+  };
+  const int cap = std::min(k.graph ? std::min(k.cg_iters, c->opt.max_cg) : c->opt.max_cg, hs - 1);
+  if (k.graph) {
+    for (int it = 0; it < cap; ++it) STCHK(iteration(it, -1));
+    // fixed-count solve: its statistics accumulate on the device (read after the replays)
+    int* stat = c->d_cgstat;
+    const int* act = a.act + (cap & 1) * batch;
+    const int* its = a.iters;
+    hipStream_t s = c->stream;
+    EMIT(k, cg_account(act, its, batch, stat, s));
+    return DMPT_OK;
+  }
+  int& guess = c->cg_guess[batch > 1];
+  int queued = 0;
+  const int ahead = live_known ? 0 : 1;
+  for (; queued < cap; ++queued) {
+    int live = batch;
+    if (queued >= (live_known ? 0 : guess)) {
+      // the state after iteration queued - ahead (check queued - ahead + 1)
+      STCHK(cg_wait(c, batch, a.solve, (unsigned)std::max(1, queued - ahead + 1)));
+      live = 0;
+      for (int z = 0; z < batch; ++z) live += (int)(c->h_flag[z] & 1);
+      if (!live) break;
+    }
+    STCHK(iteration(queued, live_known ? live : 0));
+  }
+  // at the cap the last state is still to come; otherwise every member's final one has arrived
+  if (queued >= cap) STCHK(cg_wait(c, batch, a.solve, (unsigned)queued + 1));
+  long sum = 0;
+  guess = 1;
+  for (int z = 0; z < batch; ++z) {
+    // the count includes the initial check
+    const int its = std::max(0, (int)((c->h_flag[z] >> 1) & 0x7fff) - 1);
+    sum += its;
+    guess = std::max(guess, its);
+    c->cg_total += its;
+    c->cg_max = std::max(c->cg_max, its);
+    if (c->h_flag[z] & 1) c->cg_capped = true;
+  }
+  if (!live_known) {
+    c->mfma_flops += 2.0 * (double)k.Np * k.Np * k.Np * engine_terms(k.eng) * sum;
+    c->useful_flops += 2.0 * (double)k.N * k.N * k.N * sum;
+  }
+  return DMPT_OK;
+}
+
 // Conjugate gradients on the transposed unknowns U (U T' = R^T, see gemm.hip):
 //   U (group `u`, members z = 0..batch-1) holds the initial guess and
 //   receives the solution; R holds the initial residual, whose squared norm
@@ -866,6 +1019,7 @@ dmpt_status cg_solve(const Call& k, const Group& u, int batch, int ydiv, const i
   T* R = (T*)mptr(k, w->R, 0);
   T* P = (T*)mptr(k, w->P, 0);
   const T* Q = (const T*)mptr(k, w->Q, 0);
+  if (cg_fused(k)) return cg_solve_fused(k, u, batch, ydiv, mask);
   uint16_t* ppl[3];
   planes_of(k, w->P, 0, ppl);
   // P = R (with planes)
@@ -1136,16 +1290,13 @@ dmpt_status solve_order0(const Call& k, int step) {
   dmpt_ctx c = k.c;
   const WS* w = k.w;
   hipStream_t s = c->stream;
-  const int hs = c->hstride;
-  uint16_t* pl[3] = {nullptr, nullptr, nullptr};
   // ||rhs||^2 = 4 ||D0||^2
   {
     const T* d0 = (const T*)mptr(k, w->D0, 0);
     double* part = k.part;
     double* ref = w->ref;
     EMIT(k, dot_partials<T>(d0, k.stride, d0, k.stride, k.nn, k.m, part, s));
-    EMIT(k, sum_partials(part, reduce_blocks(k.nn), k.m, ref, 1, 0, s));
-    EMIT(k, axpby<double>(ref, 0, ref, 0, k.m, 1, 0.0, 4.0, pl, 0, 0, s));
+    EMIT(k, sum_partials(part, reduce_blocks(k.nn), k.m, ref, 1, 0, s, 1, 4.0));
   }
   const bool guess_tj = k.traj && c->tj_valid >= 0 && step >= 0;
   if (guess_tj && k.rec) return fail(c, DMPT_ERR_ARG, "internal: recorded passes keep no trajectory");
@@ -1161,7 +1312,7 @@ dmpt_status solve_order0(const Call& k, int step) {
     g.C2 = mptr(k, c->U0, 0); g.beta2 = -1.0;
     g.W = mptr(k, w->R, 0);
     STCHK(run_gemm(k, g));
-    STCHK(sum_gemm_partials(k, 1, w->rr, hs, 0));
+    STCHK(sum_residual(k, 1));
     STCHK(cg_solve<T>(k, c->U0, 1, 1, w->mask0));
     uint16_t* pd[3];
     planes_of(k, w->D0, 0, pd);
@@ -1197,7 +1348,7 @@ dmpt_status solve_order0(const Call& k, int step) {
     g.batch = k.m;
     g.active = w->mask0;
     STCHK(run_gemm(k, g));
-    STCHK(sum_gemm_partials(k, k.m, w->rr, hs, 0));
+    STCHK(sum_residual(k, k.m));
     STCHK(cg_solve<T>(k, w->D0, k.m, 1, w->mask0));
     STCHK(sym_inplace<T>(k, w->D0, 0, k.m, 0.5));
   } else {
@@ -1213,7 +1364,7 @@ dmpt_status solve_order0(const Call& k, int step) {
     g.batch = k.m;
     g.active = w->mask0;
     STCHK(run_gemm(k, g));
-    STCHK(sum_gemm_partials(k, k.m, w->rr, hs, 0));
+    STCHK(sum_residual(k, k.m));
     STCHK(cg_solve<T>(k, w->D0, k.m, 1, w->mask0));
     STCHK(sym_inplace<T>(k, w->D0, 0, k.m, 0.5));
   }
@@ -1486,7 +1637,7 @@ dmpt_status solve_jet(const Call& k, const Group& g, int md, int d) {
   h.batch = md;
   h.active = w->mask1;
   STCHK(run_gemm(k, h));
-  STCHK(sum_gemm_partials(k, md, w->rr, k.c->hstride, 0));
+  STCHK(sum_residual(k, md));
   STCHK(cg_solve<T>(k, g, md, d, w->mask1));
   STCHK(sym_inplace<T>(k, g, 0, md, 0.5));
   return DMPT_OK;
@@ -2198,7 +2349,6 @@ dmpt_status adjoint_impl(const Call& k, const double* H0, double beta, double mu
                          const double* Abar, double* Gout, int ck) {
   dmpt_ctx c = k.c;
   hipStream_t s = c->stream;
-  const int hs = c->hstride;
   const double cs = std::ldexp(beta, -(n + 2));
   const int nseg = (n + ck - 1) / ck;
   STCHK(ensure_adjoint(c, nseg, ck));
@@ -2262,7 +2412,7 @@ dmpt_status adjoint_impl(const Call& k, const double* H0, double beta, double mu
         g.sW = k.stride;
         g.batch = 2;
         STCHK(run_gemm(k, g));
-        STCHK(sum_gemm_partials(k, 2, c->ws.rr, hs, 0));
+        STCHK(sum_residual(k, 2));
         STCHK(cg_solve<T>(k, c->AU, 2, 2, nullptr));  // both seeds share S0
       }
       // W = U^T;  V = W Y;  V <- sym(V);  AG = V D
@@ -2362,6 +2512,13 @@ struct BatchedPlan {
   };
   std::vector<Group> groups;            // grouped products, in launch order
   std::vector<int> first_group;         // per launch index: first group, or -1 (issue per bucket)
+  struct CgGroup {
+    CgOp op;
+    int list_off, start_off, nprob, blocks;
+  };
+  std::vector<CgGroup> cgs;             // grouped CG launches
+  std::vector<int> cg_group;            // per launch index: its CG group, or -1
+  CgArgs* d_cglist = nullptr;
   GemmArgs* d_list = nullptr;           // device copies of the grouped products' arguments
   int* d_start = nullptr;
 };
@@ -2483,6 +2640,9 @@ dmpt_status batched_pass(dmpt_ctx c, std::vector<Bucket>& bk, int wsi, int ord, 
           HIPCHK(c, gemm_grouped(G.eng, G.variant, G.acc64, G.edge, plan->d_list + G.list_off,
                                  plan->d_start + G.start_off, G.nprob, G.blocks, s));
         }
+      } else if (plan->cg_group[i] >= 0) {
+        const BatchedPlan::CgGroup& G = plan->cgs[plan->cg_group[i]];
+        HIPCHK(c, cg_grouped(G.op, plan->d_cglist + G.list_off, plan->d_start + G.start_off, G.nprob, G.blocks, s));
       } else {
         for (size_t b = 0; b < bk.size(); ++b) {
           const Op& o = plan->ops[b][i];
@@ -2561,10 +2721,31 @@ dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned)
   std::vector<GemmArgs> list;
   std::vector<int> starts;
   plan.first_group.assign(nops, -1);
+  plan.cg_group.assign(nops, -1);
+  std::vector<CgArgs> cglist;
   for (size_t i = 0; i < nops; ++i) {
-    bool all = true;
-    for (size_t b = 0; b < nb && all; ++b) all = plan.ops[b][i].gemm;
-    if (!all) continue;
+    bool all = true, cg = true;
+    for (size_t b = 0; b < nb; ++b) {
+      all = all && plan.ops[b][i].gemm;
+      cg = cg && plan.ops[b][i].cg && plan.ops[b][i].cgop == plan.ops[0][i].cgop;
+    }
+    if (cg) {
+      BatchedPlan::CgGroup G{plan.ops[0][i].cgop, (int)cglist.size(), (int)starts.size(), (int)nb, 0};
+      for (size_t b = 0; b < nb; ++b) {
+        cglist.push_back(plan.ops[b][i].ca);
+        starts.push_back(G.blocks);
+        G.blocks += cg_blocks(G.op, plan.ops[b][i].ca);
+      }
+      starts.push_back(G.blocks);
+      plan.cg_group[i] = (int)plan.cgs.size();
+      plan.cgs.push_back(G);
+      continue;
+    }
+    if (!all) {
+      for (size_t b = 0; b < nb; ++b)
+        if (plan.ops[b][i].cg) return fail(c, DMPT_ERR_ARG, "internal: buckets recorded different launch sequences");
+      continue;
+    }
     std::vector<bool> used(nb, false);
     for (size_t b0 = 0; b0 < nb; ++b0) {
       if (used[b0]) continue;
@@ -2600,7 +2781,14 @@ dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned)
   if (list.empty()) return DMPT_OK;
   plan.d_list = (GemmArgs*)dev_alloc(c, list.size() * sizeof(GemmArgs));
   plan.d_start = (int*)dev_alloc(c, starts.size() * sizeof(int));
-  if (!plan.d_list || !plan.d_start) return fail(c, DMPT_ERR_NOMEM, "batched plan allocation failed");
+  if (!cglist.empty()) {
+    plan.d_cglist = (CgArgs*)dev_alloc(c, cglist.size() * sizeof(CgArgs));
+    if (plan.d_cglist) owned.push_back(plan.d_cglist);
+  }
+  if (!plan.d_list || !plan.d_start || (!cglist.empty() && !plan.d_cglist))
+    return fail(c, DMPT_ERR_NOMEM, "batched plan allocation failed");
+  if (!cglist.empty())
+    HIPCHK(c, hipMemcpy(plan.d_cglist, cglist.data(), cglist.size() * sizeof(CgArgs), hipMemcpyHostToDevice));
   owned.push_back(plan.d_list);
   owned.push_back(plan.d_start);
   HIPCHK(c, hipMemcpy(plan.d_list, list.data(), list.size() * sizeof(GemmArgs), hipMemcpyHostToDevice));
@@ -3101,7 +3289,8 @@ void scratch_setup(ScratchDevice& sd, int device) {
   c->ws.rr = (double*)take(sizeof(double) * c->hstride);
   c->ws.pq = (double*)take(sizeof(double) * c->hstride);
   c->ws.ref = (double*)take(sizeof(double));
-  c->ws.active = (int*)take(sizeof(int));
+  c->ws.rpart = (double*)take(sizeof(double) * (size_t)reduce_blocks((int64_t)c->np_max * c->np_max));
+  c->ws.active = (int*)take(sizeof(int) * 2);
   c->ws.iters = (int*)take(sizeof(int));
   c->part_count = std::max<size_t>((size_t)(c->np_max / 32) * (c->np_max / 32),
                                    (size_t)reduce_blocks((int64_t)c->np_max * c->np_max));
@@ -3289,7 +3478,8 @@ dmpt_status dmpt_init(dmpt_ctx* out, int device, int64_t n_max, int dirs_max, co
     if (!c->ws.pb) return bail(DMPT_ERR_NOMEM, "device scalar allocation failed");
   }
   c->ws.ref = (double*)alloc(sizeof(double) * dm);
-  c->ws.active = (int*)alloc(sizeof(int) * dm);
+  c->ws.rpart = (double*)alloc(sizeof(double) * dm * (size_t)reduce_blocks((int64_t)nn));
+  c->ws.active = (int*)alloc(sizeof(int) * 2 * dm);
   c->ws.iters = (int*)alloc(sizeof(int) * dm);
   c->d_flag = (int*)alloc(sizeof(int) * 4);
   c->d_res = (double*)alloc(sizeof(double) * RES_COUNT);
@@ -3318,7 +3508,7 @@ dmpt_status dmpt_init(dmpt_ctx* out, int device, int64_t n_max, int dirs_max, co
     c->jout = (double*)alloc(sizeof(double) * (size_t)n_max * n_max);
     if (!c->jout) return bail(DMPT_ERR_NOMEM, "device workspace allocation failed");
   }
-  if (!c->ws.rr || !c->ws.pq || !c->ws.ref || !c->ws.active || !c->ws.iters || !c->d_flag || !c->d_res ||
+  if (!c->ws.rr || !c->ws.pq || !c->ws.ref || !c->ws.rpart || !c->ws.active || !c->ws.iters || !c->d_flag || !c->d_res ||
       !c->d_tally || !c->d_cgstat || !c->d_part || !c->d_gersh)
     return bail(DMPT_ERR_NOMEM, "device scalar allocation failed");
   if (hipHostMalloc((void**)&c->h_res, sizeof(double) * RES_COUNT, hipHostMallocDefault) != hipSuccess)
@@ -3326,6 +3516,9 @@ dmpt_status dmpt_init(dmpt_ctx* out, int device, int64_t n_max, int dirs_max, co
   if (hipHostMalloc((void**)&c->h_int, sizeof(int) * 2 * kIterSlot, hipHostMallocDefault) !=
       hipSuccess)
     return bail(DMPT_ERR_NOMEM, "pinned allocation failed");
+  if (hipHostMalloc((void**)&c->h_flag, sizeof(unsigned long long) * kIterSlot, hipHostMallocDefault) != hipSuccess)
+    return bail(DMPT_ERR_NOMEM, "pinned allocation failed");
+  std::memset(c->h_flag, 0, sizeof(unsigned long long) * kIterSlot);
   // zero the workspace once so the padding of every member starts at zero
   {
     auto zero = [&](const Group& g) -> bool {
@@ -3646,6 +3839,7 @@ dmpt_status dmpt_finalize(dmpt_ctx c) {
   c->bt_allocs.clear();
   if (c->h_res) (void)hipHostFree(c->h_res);
   if (c->h_int) (void)hipHostFree(c->h_int);
+  if (c->h_flag) (void)hipHostFree(c->h_flag);
   if (c->tj) dev_free(c, c->tj);
   if (c->st) dev_free(c, c->st);
   if (c->ss) dev_free(c, c->ss);
@@ -4393,10 +4587,11 @@ dmpt_status dmpt_mu_newton_batched(dmpt_ctx c, int nsys, const int64_t* Ns, cons
     w.rr = ok ? (double*)dalloc(sizeof(double) * md * hs) : nullptr;
     w.pq = ok ? (double*)dalloc(sizeof(double) * md * hs) : nullptr;
     w.ref = ok ? (double*)dalloc(sizeof(double) * md) : nullptr;
-    w.active = ok ? (int*)dalloc(sizeof(int) * md) : nullptr;
+    w.rpart = ok ? (double*)dalloc(sizeof(double) * md * (size_t)reduce_blocks(b.Np * b.Np)) : nullptr;
+    w.active = ok ? (int*)dalloc(sizeof(int) * 2 * md) : nullptr;
     w.iters = ok ? (int*)dalloc(sizeof(int) * md) : nullptr;
     w.mask1 = ok ? (int*)dalloc(sizeof(int) * md) : nullptr;
-    if (!ok || !w.rr || !w.pq || !w.ref || !w.active || !w.iters || !w.mask1) {
+    if (!ok || !w.rr || !w.pq || !w.ref || !w.rpart || !w.active || !w.iters || !w.mask1) {
       cleanup();
       return fail(c, DMPT_ERR_NOMEM, "batched workspace allocation failed");
     }

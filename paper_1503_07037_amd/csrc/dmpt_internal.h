@@ -211,9 +211,9 @@ template <class T>
 hipError_t dot_partials(const T* x, int64_t sx, const T* y, int64_t sy, int64_t n, int batch,
                         double* partials, hipStream_t s);
 // out[z * ostride + oidx] = sum of partials[z*count .. z*count+count), each run of `group`
-// consecutive ones added in order first
+// consecutive ones added in order first, times scale
 hipError_t sum_partials(const double* partials, int count, int batch, double* out,
-                        int ostride, int oidx, hipStream_t s, int group = 1);
+                        int ostride, int oidx, hipStream_t s, int group = 1, double scale = 1.0);
 // out[z*ostride] = sum_i x[z][i*ld + i], i < N (trace, FP64 input);
 // aout[z*ostride] = sum_i |x_ii| when aout is not null
 template <class T>
@@ -242,6 +242,40 @@ template <class T>
 hipError_t cg_update_p(T* P, const T* R, int64_t n, int64_t stride, int batch,
                        const double* rr_new, const double* rr_old, int hstride, const int* active,
                        uint16_t* const* planes, int nplanes, hipStream_t s);
+// The same iteration as three launches (begin, then per iteration the product,
+// cg_step_xr and cg_step_p) for FP64 and FP32 products: the blocks reduce the
+// partials they need themselves (in sum_partials' order), and block 0 of a
+// member keeps its scalars.
+struct CgArgs {
+  double *U, *R, *P;
+  const double* Q;
+  int64_t n, stride;           // elements and stride of a member
+  int batch;
+  const double* gpart;         // partials of the product before this launch, gcount per member,
+  int gcount, ggroup;          //   runs of ggroup added first
+  double* rpart;               // [member][reduce_blocks(n)] residual partials
+  double* rr;                  // <r, r> history [member][hstride]
+  const double* ref;
+  int hstride;
+  int it;                      // iteration
+  double tol2, eta2;
+  int* act;                    // activity masks [2][batch]: iteration `it` reads it & 1, writes the other
+  int* iters;                  // checks made per member
+  const int* mask;             // begin: initial activity (null: all ones)
+  unsigned long long* hflag;   // host memory, or null: (solve << 32 | checks done << 16 |
+  unsigned solve;              //   iterations << 1 | active) of every member after each check
+};
+// P = R, rr[0] from the product's partials, masks and counts, the first check.
+hipError_t cg_begin(const CgArgs& a, hipStream_t s);
+// alpha = rr[it] / <p, q> (product partials); U += alpha P, R -= alpha Q, residual partials.
+hipError_t cg_step_xr(const CgArgs& a, hipStream_t s);
+// rr[it + 1] from the residual partials; P = R + (rr[it + 1] / rr[it]) P; the check.
+hipError_t cg_step_p(const CgArgs& a, hipStream_t s);
+// Blocks per launch of the three (all members), and the launches over several
+// problems at once: block b belongs to problem p with start[p] <= b < start[p + 1].
+enum class CgOp : int { Begin = 0, Xr = 1, P = 2 };
+int cg_blocks(CgOp op, const CgArgs& a);
+hipError_t cg_grouped(CgOp op, const CgArgs* list, const int* start, int nprob, int blocks, hipStream_t s);
 // convergence: active[z] stays 1 while rr > tol2 ref or rr > eta2 rr0 (rr0: the
 // initial residual); iters[z] counts the checks.  Any batch size.
 hipError_t cg_check(const double* rr, const double* rr0, const double* ref, int hstride, int batch,

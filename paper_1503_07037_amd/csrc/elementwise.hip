@@ -283,11 +283,9 @@ __global__ __launch_bounds__(kT) void k_dot(const T* __restrict__ x, int64_t sx,
   if (threadIdx.x == 0) partials[(int64_t)z * gridDim.x + blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(kT) void k_sum_partials(const double* __restrict__ p, int count,
-                                                     double* out, int ostride, int oidx, int group) {
-  const int z = blockIdx.x;
+// Sum of count partials, runs of group consecutive ones first; valid in thread 0.
+__device__ inline double partial_sum(const double* __restrict__ p, int count, int group) {
   double s = 0.0;
-  p += (int64_t)z * count;
   if (group == 1) {
     for (int i = threadIdx.x; i < count; i += kT) s += p[i];
   } else {
@@ -297,8 +295,14 @@ __global__ __launch_bounds__(kT) void k_sum_partials(const double* __restrict__ 
       s += t;
     }
   }
-  s = block_sum(s);
-  if (threadIdx.x == 0) out[z * ostride + oidx] = s;
+  return block_sum(s);
+}
+
+__global__ __launch_bounds__(kT) void k_sum_partials(const double* __restrict__ p, int count,
+                                                     double* out, int ostride, int oidx, int group, double scale) {
+  const int z = blockIdx.x;
+  const double s = partial_sum(p + (int64_t)z * count, count, group);
+  if (threadIdx.x == 0) out[z * ostride + oidx] = s * scale;
 }
 
 template <class T>
@@ -391,6 +395,161 @@ __global__ __launch_bounds__(kT) void k_cg_p(T* __restrict__ P, const T* __restr
     P[i] = p;
     if (np) split_store((double)p, p3, np, plane_off_lin(i, Np));
   }
+}
+
+// ---- conjugate gradients in three launches per iteration.  Small members are
+// bound by launches and latency (Np = 128: product 5 us, then 1.9 + 6.8 + 1.9 +
+// 3.2 + 1.3 us and a host round trip for sum, update, sum, direction and
+// check): every block reduces the partials it needs itself instead of waiting
+// for a one-block launch, and block 0 does the check.  The reductions and the
+// elements each thread sums are those of k_sum_partials, k_cg_xr and k_cg_p.
+
+// partial_sum for every thread of the block.
+__device__ inline double partial_sum_all(const double* __restrict__ p, int count, int group) {
+  __shared__ double total;
+  const double s = partial_sum(p, count, group);
+  __syncthreads();  // the previous use of total is over
+  if (threadIdx.x == 0) total = s;
+  __syncthreads();
+  return total;
+}
+
+// The check of member z after `it` iterations (one thread): see k_cg_check.
+__device__ inline void cg_checked(const CgArgs& a, int z, int active, double r, int it) {
+  if (active) {
+    a.iters[z] += 1;
+    if (!(r > a.tol2 * a.ref[z] || r > a.eta2 * a.rr[(int64_t)z * a.hstride])) active = 0;
+  }
+  a.act[(it & 1) * a.batch + z] = active;
+  if (a.hflag)
+    __hip_atomic_store(a.hflag + z, ((unsigned long long)a.solve << 32) | ((unsigned)(it + 1) << 16) |
+                                        ((unsigned)a.iters[z] << 1) | (unsigned)active,
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__device__ inline void cg_begin_block(const CgArgs& a, int z, int bx, int nbx) {
+  const double* R = a.R + z * a.stride;
+  double* P = a.P + z * a.stride;
+  for (int64_t c = (int64_t)bx * kT + threadIdx.x; c < (a.n >> 1); c += (int64_t)nbx * kT) {
+    const d2v v = *(const d2v*)(R + 2 * c);
+    *(d2v*)(P + 2 * c) = v;
+  }
+  if (bx == 0) {
+    const double r = partial_sum(a.gpart + (int64_t)z * a.gcount, a.gcount, a.ggroup);
+    if (threadIdx.x == 0) {
+      a.rr[(int64_t)z * a.hstride] = r;
+      a.iters[z] = 0;
+      cg_checked(a, z, a.mask ? a.mask[z] : 1, r, 0);
+    }
+  }
+}
+
+__device__ inline void cg_xr_block(const CgArgs& a, int z, int bx, int nbx) {
+  if (!a.act[(a.it & 1) * a.batch + z]) {
+    if (threadIdx.x == 0) a.rpart[(int64_t)z * nbx + bx] = 0.0;
+    return;
+  }
+  const double den = partial_sum_all(a.gpart + (int64_t)z * a.gcount, a.gcount, a.ggroup);
+  const double al = den != 0.0 ? a.rr[(int64_t)z * a.hstride + a.it] / den : 0.0;
+  double* __restrict__ U = a.U + z * a.stride;
+  double* __restrict__ R = a.R + z * a.stride;
+  const double* __restrict__ P = a.P + z * a.stride;
+  const double* __restrict__ Q = a.Q + z * a.stride;
+  const int64_t step = (int64_t)nbx * kT;
+  double s = 0.0;
+  int64_t i = (int64_t)bx * kT + threadIdx.x;
+  constexpr int V = 4;  // elements in flight per thread
+  for (; i + (V - 1) * step < a.n; i += V * step) {
+    double u[V], r[V], p[V], q[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      u[e] = U[i + e * step];
+      r[e] = R[i + e * step];
+      p[e] = P[i + e * step];
+      q[e] = Q[i + e * step];
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      U[i + e * step] = u[e] + al * p[e];
+      const double t = r[e] - al * q[e];
+      R[i + e * step] = t;
+      s += t * t;
+    }
+  }
+  for (; i < a.n; i += step) {
+    U[i] += al * P[i];
+    const double t = R[i] - al * Q[i];
+    R[i] = t;
+    s += t * t;
+  }
+  s = block_sum(s);
+  if (threadIdx.x == 0) a.rpart[(int64_t)z * nbx + bx] = s;
+}
+
+__device__ inline void cg_p_block(const CgArgs& a, int z, int bx, int nbx, int rblocks) {
+  const int active = a.act[(a.it & 1) * a.batch + z];
+  if (!active) {
+    if (bx == 0 && threadIdx.x == 0) cg_checked(a, z, 0, 0.0, a.it + 1);
+    return;
+  }
+  const double rn = partial_sum_all(a.rpart + (int64_t)z * rblocks, rblocks, 1);
+  double* rr = a.rr + (int64_t)z * a.hstride + a.it;
+  const double ro = rr[0];
+  const double be = ro != 0.0 ? rn / ro : 0.0;
+  if (bx == 0 && threadIdx.x == 0) {
+    rr[1] = rn;
+    cg_checked(a, z, 1, rn, a.it + 1);
+  }
+  const double* __restrict__ R = a.R + z * a.stride;
+  double* __restrict__ P = a.P + z * a.stride;
+  for (int64_t c = (int64_t)bx * kT + threadIdx.x; c < (a.n >> 1); c += (int64_t)nbx * kT) {
+    const d2v r = *(const d2v*)(R + 2 * c);
+    d2v p = *(const d2v*)(P + 2 * c);
+    p.x = r.x + be * p.x;
+    p.y = r.y + be * p.y;
+    *(d2v*)(P + 2 * c) = p;
+  }
+}
+
+template <CgOp OP>
+__device__ inline void cg_block(const CgArgs& a, int z, int bx, int nbx, int rblocks) {
+  if constexpr (OP == CgOp::Begin) cg_begin_block(a, z, bx, nbx);
+  else if constexpr (OP == CgOp::Xr) cg_xr_block(a, z, bx, nbx);
+  else cg_p_block(a, z, bx, nbx, rblocks);
+}
+
+template <CgOp OP>
+__global__ __launch_bounds__(kT) void k_cg(CgArgs a, int rblocks) {
+  cg_block<OP>(a, blockIdx.y, blockIdx.x, gridDim.x, rblocks);
+}
+
+__host__ __device__ inline int red_blocks(int64_t n) {
+  int64_t b = (n + kT * 8 - 1) / (kT * 8);
+  if (b < 1) b = 1;
+  if (b > kMaxRedBlocks) b = kMaxRedBlocks;
+  return (int)b;
+}
+
+// Blocks per member: the residual reduction's for xr (their partials), two
+// pairs per thread and at most 1024 for the copies and the direction update
+// (each block reduces up to 1024 partials first).
+__host__ __device__ inline int cg_member_blocks(CgOp op, int64_t n) {
+  if (op == CgOp::Xr) return red_blocks(n);
+  int64_t b = (n + kT * 4 - 1) / (kT * 4);
+  if (b < 1) b = 1;
+  if (b > 1024) b = 1024;
+  return (int)b;
+}
+
+template <CgOp OP>
+__global__ __launch_bounds__(kT) void k_cg_grouped(const CgArgs* __restrict__ list, const int* __restrict__ start,
+                                                   int nprob) {
+  int p = 0;
+  const int b = blockIdx.x;
+  while (p + 1 < nprob && b >= start[p + 1]) ++p;
+  const CgArgs& a = list[p];
+  const int nbx = cg_member_blocks(OP, a.n), local = b - start[p];
+  cg_block<OP>(a, local / nbx, local % nbx, nbx, red_blocks(a.n));
 }
 
 // A member stays active while ||r||^2 > tol2 ||rhs||^2 or ||r||^2 > eta2 ||r_0||^2:
@@ -1025,12 +1184,7 @@ __global__ void k_q8_bound_init(const double* qs, double* pb, int hstride, int b
   if (z < batch) pb[z * hstride] = 127.0 * qs[z];
 }
 
-inline unsigned red_grid(int64_t n) {
-  int64_t b = (n + kT * 8 - 1) / (kT * 8);
-  if (b < 1) b = 1;
-  if (b > kMaxRedBlocks) b = kMaxRedBlocks;
-  return (unsigned)b;
-}
+inline unsigned red_grid(int64_t n) { return (unsigned)red_blocks(n); }
 
 inline unsigned ew_grid(int64_t n) {
   int64_t b = (n + kT * 4 - 1) / (kT * 4);
@@ -1150,10 +1304,10 @@ template hipError_t dot_partials<float>(const float*, int64_t, const float*, int
                                         double*, hipStream_t);
 
 hipError_t sum_partials(const double* partials, int count, int batch, double* out, int ostride,
-                        int oidx, hipStream_t s, int group) {
+                        int oidx, hipStream_t s, int group, double scale) {
   if (group < 1 || count % group) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_sum_partials, dim3(batch), dim3(kT), 0, s, partials, count, out, ostride,
-                     oidx, group);
+                     oidx, group, scale);
   return hipGetLastError();
 }
 
@@ -1223,6 +1377,33 @@ template hipError_t cg_update_p<double>(double*, const double*, int64_t, int64_t
 template hipError_t cg_update_p<float>(float*, const float*, int64_t, int64_t, int, const double*,
                                        const double*, int, const int*, uint16_t* const*, int,
                                        hipStream_t);
+
+static bool cg_args_ok(const CgArgs& a) {
+  return a.n > 0 && a.n % 2 == 0 && a.stride % 2 == 0 && a.batch > 0 && a.gcount > 0 && a.ggroup > 0 &&
+         a.gcount % a.ggroup == 0 && ((uintptr_t)a.R | (uintptr_t)a.P) % 16 == 0;
+}
+
+int cg_blocks(CgOp op, const CgArgs& a) { return cg_member_blocks(op, a.n) * a.batch; }
+
+template <CgOp OP>
+static hipError_t cg_launch(const CgArgs& a, hipStream_t s) {
+  if (!cg_args_ok(a)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_cg<OP>, dim3(cg_member_blocks(OP, a.n), a.batch), dim3(kT), 0, s, a, red_blocks(a.n));
+  return hipGetLastError();
+}
+hipError_t cg_begin(const CgArgs& a, hipStream_t s) { return cg_launch<CgOp::Begin>(a, s); }
+hipError_t cg_step_xr(const CgArgs& a, hipStream_t s) { return cg_launch<CgOp::Xr>(a, s); }
+hipError_t cg_step_p(const CgArgs& a, hipStream_t s) { return cg_launch<CgOp::P>(a, s); }
+
+hipError_t cg_grouped(CgOp op, const CgArgs* list, const int* start, int nprob, int blocks, hipStream_t s) {
+  if (nprob < 1 || blocks < 1) return hipErrorInvalidValue;
+  switch (op) {
+    case CgOp::Begin: hipLaunchKernelGGL(k_cg_grouped<CgOp::Begin>, dim3(blocks), dim3(kT), 0, s, list, start, nprob); break;
+    case CgOp::Xr: hipLaunchKernelGGL(k_cg_grouped<CgOp::Xr>, dim3(blocks), dim3(kT), 0, s, list, start, nprob); break;
+    case CgOp::P: hipLaunchKernelGGL(k_cg_grouped<CgOp::P>, dim3(blocks), dim3(kT), 0, s, list, start, nprob); break;
+  }
+  return hipGetLastError();
+}
 
 hipError_t cg_check(const double* rr, const double* rr0, const double* ref, int hstride, int batch,
                     double tol2, double eta2, int* active, int* iters, hipStream_t s) {

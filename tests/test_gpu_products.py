@@ -78,3 +78,29 @@ def test_fp32_small_tiles_match_the_oracle(dm, n_max, sizes):
             p = ctx.fermi_recursion(T(h0), beta, mu, n)[0].cpu().numpy()
             assert np.array_equal(p, p.T)
             assert np.abs(p - oracle.density(h0, beta, n, mu)).max() < 1e-6
+
+
+@pytest.mark.parametrize("prec,N", [("fp64", 90), ("fp64", 513), ("fp32", 300)])
+def test_solves_that_run_ahead_of_the_host(dm, prec, N):
+    """The conjugate-gradient solves queue iterations before the host knows that they are needed;
+    with the product timing on they wait for every iteration instead.  Both give the same bits and
+    statistics, and a solve that ends at max_cg is reported either way."""
+    print(f"case solves {prec} N={N}", flush=True)
+    h0, h1 = workloads.chain_1d(N, 3), [np.diag(np.linspace(-1.0, 1.0, N))]
+    out = []
+    with dm.Context(N, dirs_max=1, prec=prec) as ctx:
+        for timed in (False, True):
+            ctx.profile(timed)
+            P0, P1, P2, mu, st = ctx.mu_newton(T(h0), [T(h) for h in h1], beta=10.0, Ne=N // 2, n=20, order=2)
+            ctx.profile(False)
+            out.append(([P0.cpu().numpy(), P1[0].cpu().numpy(), P2[0].cpu().numpy()], mu, st))
+    (a, mu_a, sa), (b, mu_b, sb) = out
+    assert all(np.array_equal(x, y) for x, y in zip(a, b)) and mu_a == mu_b
+    for key in ("cg_iters_total", "cg_iters_max", "newton_iters"):
+        assert sa[key] == sb[key]
+    assert abs(sa["mfma_flops"] - sb["mfma_flops"]) <= 1e-12 * sb["mfma_flops"]
+    for timed in (False, True):
+        with dm.Context(N, dirs_max=1, prec=prec, max_cg=2) as ctx:
+            ctx.profile(timed)
+            with pytest.raises(dm.DMPTError):
+                ctx.mu_newton(T(h0), [T(h) for h in h1], beta=10.0, Ne=N // 2, n=20, order=1)
