@@ -579,18 +579,24 @@ __device__ __forceinline__ void gemm_f64_lds64_tile(const GemmArgs& a, int z, in
           xv[i][h] = *(const d2f*)(sx + i * 16 * kF64LdRow + 8 * h);
           yv[i][h] = *(const d2f*)(sy + i * 16 * kF64LdRow + 8 * h);
         }
-      if (ch + KS < nch) {
-        swrite((rd + 1) & 1);
-        if (ch + 2 * KS < nch) gload(ch + 2 * KS);
-      }
+      // the staging of the next chunk goes between the halves of the MFMAs, so
+      // they start as soon as the fragments are there (2432 full 495 -> 490 us,
+      // three members of 1024 124 -> 116)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < 4; ++e) {
+        if (e == 2 && ch + KS < nch) {
+          __builtin_amdgcn_sched_barrier(0);
+          swrite((rd + 1) & 1);
+          if (ch + 2 * KS < nch) gload(ch + 2 * KS);
+          __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[i][e >> 1][e & 1], yv[j][e >> 1][e & 1], acc[i][j], 0,
                                                              0, 0);
+      }
     }
     __syncthreads();
   }
