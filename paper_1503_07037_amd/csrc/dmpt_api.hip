@@ -821,7 +821,7 @@ dmpt_status sym_inplace(const Call& k, const Group& g, int z0, int batch, double
   T* m = (T*)mptr(k, g, z0);
   hipStream_t s = k.c->stream;
   int64_t ms = 0;
-  double* mx = q8_sink(k, g, z0, batch, sym_pair_blocks(k.Np), &ms);
+  double* mx = q8_sink(k, g, z0, batch, sym_pair_blocks(k.Np, batch), &ms);
   EMIT(k, (sym_combine<T, T>(m, k.Np, k.stride, k.N, k.Np, a, nullptr, 0, m, k.Np, k.stride, pl, k.np, batch,
                              s, nullptr, 0.0, nullptr, mx, ms)));
   return DMPT_OK;
@@ -838,7 +838,7 @@ dmpt_status sym_to(const Call& k, const Group& in, const Group& out, int batch, 
   const int npl = planes ? k.np : 0;
   hipStream_t s = k.c->stream;
   int64_t ms = 0;
-  double* mx = q8_sink(k, out, 0, batch, sym_pair_blocks(k.Np), &ms);
+  double* mx = q8_sink(k, out, 0, batch, sym_pair_blocks(k.Np, batch), &ms);
   EMIT(k, (sym_combine<T, T>(src, k.Np, k.stride, k.N, k.Np, 1.0, nullptr, 0, dst, k.Np, k.stride, pl, npl,
                              batch, s, nullptr, 0.0, nullptr, mx, ms)));
   return DMPT_OK;

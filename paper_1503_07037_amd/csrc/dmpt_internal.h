@@ -170,7 +170,7 @@ hipError_t gemm_prepare();
 // in: Tin with leading dim ldi; out: Tout with leading dim ldo (+ split planes).
 // Batched over `batch` members with element strides.
 // The tile pair (i, j) / (j, i) is handled by one block, so in == out is allowed.
-// With mx (and no gate), member z also leaves sym_pair_blocks(span) partial
+// With mx (and no gate), member z also leaves sym_pair_blocks(span, batch) partial
 // maxima of |out| at mx + z mstride (their max is the member's max |out|).
 template <class Tin, class Tout>
 hipError_t sym_combine(const Tin* in, int64_t ldi, int64_t si, int64_t N, int64_t Np, double a,
@@ -178,9 +178,10 @@ hipError_t sym_combine(const Tin* in, int64_t ldi, int64_t si, int64_t N, int64_
                        uint16_t* const* planes, int nplanes, int batch, hipStream_t s,
                        const Tin* in2 = nullptr, double a2 = 0.0, const int* gate = nullptr,
                        double* mx = nullptr, int64_t mstride = 0);
-// Blocks per member of sym_combine over span rows: one per 128 x 128 tile
-// pair on and above the diagonal (with mx, the maxima each member leaves).
-int64_t sym_pair_blocks(int64_t span);
+// Blocks per member of sym_combine with mx over span rows: one per tile pair
+// on and above the diagonal, of an edge that fills the chip (the maxima each
+// member leaves).
+int64_t sym_pair_blocks(int64_t span, int batch);
 
 // out = in^T (Np x Np members, batched, with planes); in != out.
 template <class T>

@@ -127,7 +127,7 @@ inline bool pair_ok(const T* p, int64_t stride, int64_t n) {
 // ------------------------------------------------------------ symmetrise
 // Block t owns the 32 g x 32 g tile pair (BI, BJ) and (BJ, BI), BI <= BJ,
 // t = BJ (BJ + 1) / 2 + BI, and walks its 32 x 32 pairs (bi, bj), bi <= bj
-// (g = 4 when the block leaves a maximum, else 1: one pair per block):
+// (sym_group when the block leaves a maximum, else 1: one pair per block):
 // both input tiles of a pair are read before either output tile is written,
 // and the pairs are disjoint (reading the next pair while writing this one
 // touches other elements), so the kernel may run in place.  Reads and writes
@@ -1052,15 +1052,28 @@ __global__ __launch_bounds__(kT) void k_qscale(const double* __restrict__ part, 
 }
 
 __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int64_t sx, int64_t Np,
-                                              int8_t* __restrict__ q8, int64_t sq, const double* __restrict__ qs,
-                                              const int* active) {
+                                              int8_t* __restrict__ q8, int64_t sq, double* __restrict__ qs,
+                                              const int* active, const double* __restrict__ part, int64_t pstride,
+                                              int nb) {
   const int z = blockIdx.y;
   if (active && !active[z]) return;
+  __shared__ double sq_;
+  if (part) {
+    // few maxima: every block reduces them itself (as k_qscale does) and block 0 keeps the scale
+    double m = 0.0;
+    for (int i = threadIdx.x; i < nb; i += kT) m = fmax(m, part[(int64_t)z * pstride + i]);
+    m = block_max(m);
+    if (threadIdx.x == 0) {
+      sq_ = m / 127.0;
+      if (blockIdx.x == 0) qs[z] = sq_;
+    }
+    __syncthreads();
+  }
   // one 32 x 32 block per wave and round, staged through LDS: read with whole
   // 256-byte rows, then each lane takes 16 consecutive elements of one row
   __shared__ double tile[kT / 64][32][33];
   // digits of x / q, q = qs[z] = max |x| / 127 (the scale the products apply)
-  const double q = qs[z];
+  const double q = part ? sq_ : qs[z];
   const double inv = (q > 0.0 && q <= 1.0e306) ? 1.0 / q : 0.0;
   const double* xm = x + (int64_t)z * sx;
   int8_t* qm = q8 + (int64_t)z * sq;
@@ -1193,6 +1206,18 @@ inline unsigned ew_grid(int64_t n) {
   return (unsigned)b;
 }
 
+// Edge, in 32 x 32 tiles, of the tile pairs a symmetrising block with maxima
+// walks: 4 (few maxima, the next pair's loads under the current pair's
+// stores) once such blocks fill the chip, smaller ones before (Np = 2048, one
+// member: 136 blocks 67 us, against 20 with a block per 32 x 32 pair).
+inline int sym_group(int64_t span, int batch) {
+  for (int g = 4; g > 1; g /= 2) {
+    const int64_t nbg = ((span + 31) / 32 + g - 1) / g;
+    if (nbg * (nbg + 1) / 2 * batch >= 1024) return g;
+  }
+  return 1;
+}
+
 }  // namespace
 
 int reduce_blocks(int64_t n) { return (int)red_grid(n); }
@@ -1225,19 +1250,18 @@ hipError_t sym_combine(const Tin* in, int64_t ldi, int64_t si, int64_t N, int64_
   const int64_t rows = (ldo == N && ldo != Np) ? N : ldo;  // caller buffer: only N x N
   const int64_t span = rows > N ? rows : N;
   const int64_t nb = (span + 31) / 32;
-  // with maxima: one block per 128 x 128 pair (few maxima); else one per 32 x 32 pair
-  const int g = mx ? 4 : 1;
+  const int g = mx ? sym_group(span, batch) : 1;
   const int64_t nbg = (nb + g - 1) / g;
   const int64_t pairs = nbg * (nbg + 1) / 2;
-  if (mx && (mstride < pairs || gate || pairs != sym_pair_blocks(span))) return hipErrorInvalidValue;
+  if (mx && (mstride < pairs || gate || pairs != sym_pair_blocks(span, batch))) return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_sym<Tin, Tout>), dim3((unsigned)pairs, batch), dim3(kT), 0, s, in, ldi, si, N, Np, a,
                      dshift, dstride, out, ldo, so, pl, nplanes, rows, in2, a2, gate, nb, g, mx, mstride);
   return hipGetLastError();
 }
 
-int64_t sym_pair_blocks(int64_t span) {
-  const int64_t nb128 = (span + 127) / 128;
-  return nb128 * (nb128 + 1) / 2;
+int64_t sym_pair_blocks(int64_t span, int batch) {
+  const int64_t g = sym_group(span, batch), nbg = ((span + 31) / 32 + g - 1) / g;
+  return nbg * (nbg + 1) / 2;
 }
 
 #define DMPT_SYM_INST(TI, TO)                                                                   \
@@ -1263,8 +1287,8 @@ hipError_t quantize_q8(const double* x, int64_t sx, int64_t Np, int batch, doubl
   const int64_t nblk = (Np / 32) * (Np / 32);
   int64_t g = (nblk + 2 * (kT / 64) - 1) / (2 * (kT / 64));
   if (g > 65535) g = 65535;
-  hipLaunchKernelGGL(k_quant, dim3((unsigned)g, batch), dim3(kT), 0, s, x, sx, Np, q8, sq, (const double*)qs,
-                     active);
+  hipLaunchKernelGGL(k_quant, dim3((unsigned)g, batch), dim3(kT), 0, s, x, sx, Np, q8, sq, qs, active,
+                     (const double*)nullptr, (int64_t)0, 0);
   return hipGetLastError();
 }
 
@@ -1272,12 +1296,16 @@ hipError_t quantize_q8_known(const double* x, int64_t sx, int64_t Np, int batch,
                              int64_t pstride, int nb, int8_t* q8, int64_t sq, double* qs, hipStream_t s) {
   if (Np <= 0 || Np % 32 != 0 || batch < 1 || !x || !part || nb < 1 || pstride < nb || !q8 || !qs)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_qscale, dim3(batch), dim3(kT), 0, s, part, pstride, nb, qs, (const int*)nullptr);
+  // up to 2304 maxima (18 KB, nine loads per thread) are cheaper to reduce in
+  // every block than in a launch of their own (4.9 us at Np = 2048 and 9 at
+  // 4096, beside a slicing of 10 and 49)
+  const bool fused = nb <= 2304;
+  if (!fused) hipLaunchKernelGGL(k_qscale, dim3(batch), dim3(kT), 0, s, part, pstride, nb, qs, (const int*)nullptr);
   const int64_t nblk = (Np / 32) * (Np / 32);
   int64_t g = (nblk + 2 * (kT / 64) - 1) / (2 * (kT / 64));
   if (g > 65535) g = 65535;
-  hipLaunchKernelGGL(k_quant, dim3((unsigned)g, batch), dim3(kT), 0, s, x, sx, Np, q8, sq, (const double*)qs,
-                     (const int*)nullptr);
+  hipLaunchKernelGGL(k_quant, dim3((unsigned)g, batch), dim3(kT), 0, s, x, sx, Np, q8, sq, qs, (const int*)nullptr,
+                     fused ? part : (const double*)nullptr, pstride, nb);
   return hipGetLastError();
 }
 

@@ -54,7 +54,7 @@ constexpr int BM = 128, BN = 128;
 constexpr int kWaves256 = 8;  // waves of the 256 x 256 split-BF16 kernel (two per SIMD)
 constexpr int kGroupM = 8;   // tile rows per raster group
 constexpr int kXcd = 8;      // XCDs of an MI355X
-constexpr int kDiagParts = 4;  // row parts per diagonal tile in the summing kernel of split products
+constexpr int kDiagParts = 10;  // 32 x 32 pairs of a diagonal tile (on and below its diagonal)
 
 // Tile coordinates of a (possibly remapped) linear block index.
 __device__ inline void raster(int b, int tiles_m, int tiles_n, int& tm, int& tn) {
@@ -1456,14 +1456,20 @@ __device__ __forceinline__ void gemm_i8_tile(const GemmArgs& a, int z, int bx, i
   // the exact maximum's), and one register instead of two keeps the epilogue
   // within the register budget
   float fmx = 0.0f;
+  // off-diagonal tiles of a split symmetric product are mirrored here: each
+  // wave turns its 32 x 32 MFMA tiles round in its own 8 KB of the stage
+  // buffers (element (r, c) at 32 r + (c ^ r): no bank conflicts either way)
+  // and writes them as whole 256-byte rows of the upper triangle
+  const bool mirror = a.sym == 2 && split < 0;
+  double* turn = (double*)smem + wave * 1024;
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+    for (int j = 0; j < FN; ++j) {
+      const int64_t row0 = (int64_t)tm * TM + wm * (TM / WM) + i * 32, col0 = (int64_t)tn * TM + wn * (TM / WN) + j * 32;
 #pragma unroll
       for (int h = 0; h < 16 / NV; ++h) {
-        const int64_t off = ((int64_t)tm * TM + wm * (TM / WM) + i * 32 + 2 * NV * h + 4 * (lane >> 5)) * Np +
-                            (int64_t)tn * TM + wn * (TM / WN) + j * 32 + (lane & 31);
+        const int64_t off = (row0 + 2 * NV * h + 4 * (lane >> 5)) * Np + col0 + (lane & 31);
         double v[NV], out[NV], wv[NV];
 #pragma unroll
         for (int r = 0; r < NV; ++r) {
@@ -1478,7 +1484,27 @@ __device__ __forceinline__ void gemm_i8_tile(const GemmArgs& a, int z, int bx, i
           dsum += wv[r] * out[r];
           fmx = out[r] == out[r] ? fmaxf(fmx, __double2float_ru(fabs(out[r]))) : INFINITY;
         }
+        if (mirror) {
+#pragma unroll
+          for (int r = 0; r < NV; ++r) {
+            const int lr = 2 * NV * h + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            turn[lr * 32 + ((lane & 31) ^ lr)] = out[r];
+          }
+        }
       }
+      if (mirror) {
+        double* c = (double*)a.C + (int64_t)z * a.sC + (col0 + (lane >> 5)) * Np + row0 + (lane & 31);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+          const int mr = 2 * t + (lane >> 5), mc = lane & 31;
+          c[(int64_t)2 * t * Np] = turn[mc * 32 + (mr ^ mc)];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
   if (e.W) {
     const double s = block_sum(dsum, red);
     if (tid == 0) a.partials[(int64_t)z * nbx + bx] = s;
@@ -1666,8 +1692,12 @@ __global__ __launch_bounds__(NW * 64) void k_gemm_i8_grouped(const GemmArgs* __r
   gemm_i8_tile<BK, NW, WM, SD>(a, local / tiles, local % tiles, tiles);
 }
 
+// Two stages, and at least 8 KB per wave for the mirrored tiles.
 template <int BK, int SD>
-constexpr size_t i8_lds() { return (size_t)2 * 2 * SD * 4 * (BK / 32) * 1024; }
+constexpr size_t i8_lds() {
+  constexpr size_t stages = (size_t)2 * 2 * SD * 4 * (BK / 32) * 1024;
+  return stages > 8 * 8192 ? stages : 8 * 8192;
+}
 
 template <int BK, int NW, int WM, int SD>
 hipError_t prepare_i8() {
@@ -1909,48 +1939,68 @@ __global__ __launch_bounds__(256) void k_mirror(double* __restrict__ C, int64_t 
   }
 }
 
-// The diagonal tiles of a split symmetric int8 product: block (d, part, z)
-// sums the dsplit partial tiles of rows 32 part .. 32 part + 31 of diagonal
-// tile d in order, applies the epilogue of the product kernels and leaves
-// their max |C| in slot d kDiagParts + part.
+// The diagonal tiles of a split symmetric int8 product: block (d, p, z) sums
+// the dsplit partial tiles of the 32 x 32 pair p = (bi, bj), bi >= bj, of
+// diagonal tile d in order, both triangles, applies the epilogue of the
+// product kernels, writes the lower one and its mirror image, and leaves the
+// max |C| of both in slot d kDiagParts + p.
 __global__ __launch_bounds__(256) void k_diag_sum(GemmArgs a) {
-  constexpr int TM = 128, RP = TM / kDiagParts, PER = RP * TM / 256;
-  const int z = blockIdx.z, d = blockIdx.x, part = blockIdx.y;
+  constexpr int TM = 128;
+  const int z = blockIdx.z, d = blockIdx.x;
   if (a.active && !a.active[z]) return;
   __shared__ double red[4];
+  __shared__ double tile[32][33];
+  int bi = 0, p = blockIdx.y;
+  while (p > bi) p -= ++bi;
+  const int bj = p;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   // partial s of member z: rows 0 .. 127 of the strip (z, s) of 128 x Np
   // values, diagonal tile d at columns 128 d ..
   const int64_t strip = (int64_t)TM * a.Np;
   const double* dp = a.dpart + (int64_t)z * a.dsplit * strip + (int64_t)d * TM;
-  double dsum = 0.0, m = 0.0;
+  double m = 0.0;
   bool bad = false;
-  double v[PER];
+  double out[2][4];  // lower (bi, bj), upper (bj, bi)
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = threadIdx.x + 256 * u;
-    const int64_t lr = part * RP + e / TM, lc = e % TM;
-    v[u] = dp[lr * a.Np + lc];
-  }
-  for (int sp = 1; sp < a.dsplit; ++sp)
+  for (int t = 0; t < 2; ++t) {
+    const int br = t ? bj : bi, bc = t ? bi : bj;
+    double v[4], c1[4], c2[4];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      const int64_t lr = part * RP + e / TM, lc = e % TM;
-      v[u] += dp[sp * strip + lr * a.Np + lc];
+    for (int u = 0; u < 4; ++u) {
+      const int64_t lr = br * 32 + ty + 8 * u, lc = bc * 32 + tx;
+      const int64_t off = ((int64_t)d * TM + lr) * a.Np + (int64_t)d * TM + lc;
+      v[u] = dp[lr * a.Np + lc];
+      if (a.C1) c1[u] = ((const double*)a.C1)[z * a.sC1 + off];
+      if (a.C2) c2[u] = ((const double*)a.C2)[z * a.sC2 + off];
     }
+    for (int sp = 1; sp < a.dsplit; ++sp)
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = threadIdx.x + 256 * u;
-    const int64_t row = (int64_t)d * TM + part * RP + e / TM, col = (int64_t)d * TM + e % TM;
-    const double o = epi<double>(a, z, row, col, v[u], dsum);
-    const double ao = fabs(o);
-    bad |= !(ao <= 1.0e308);
-    m = fmax(m, ao);
+      for (int u = 0; u < 4; ++u) v[u] += dp[sp * strip + (br * 32 + ty + 8 * u) * a.Np + bc * 32 + tx];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      double x = a.alpha * v[u];
+      if (a.C1) x += a.beta1 * c1[u];
+      if (a.C2) x += a.beta2 * c2[u];
+      out[t][u] = x;
+      const double ao = fabs(x);
+      bad |= !(ao <= 1.0e308);
+      m = fmax(m, ao);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) tile[ty + 8 * u][tx] = out[0][u];
+  __syncthreads();  // also: every addend of the pair is read before C (which may be C1) is written
+  double* c = (double*)a.C + (int64_t)z * a.sC + (int64_t)d * TM * a.Np + (int64_t)d * TM;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = ty + 8 * u;
+    if (bi != bj || tx <= r) c[(int64_t)(bi * 32 + r) * a.Np + bj * 32 + tx] = out[0][u];
+    if (bi != bj || tx > r) c[(int64_t)(bj * 32 + r) * a.Np + bi * 32 + tx] = tile[tx][r];
   }
   if (a.cmax) {
     // an FP32 value rounded up, as the product kernels leave it
     const double bm = block_max(bad ? (double)INFINITY : (double)__double2float_ru(m), red);
-    if (threadIdx.x == 0) a.cmax[(int64_t)z * a.cmax_stride + d * kDiagParts + part] = bm;
+    if (threadIdx.x == 0) a.cmax[(int64_t)z * a.cmax_stride + d * kDiagParts + blockIdx.y] = bm;
   }
 }
 
@@ -1975,9 +2025,9 @@ hipError_t gemm(const GemmArgs& a0, hipStream_t s) {
   hipError_t e = gemm_launch(a, tiles, s);
   if (e != hipSuccess || !a.sym) return e;
   if (a.sym == 2) {
+    // the product kernel mirrored the off-diagonal tiles, this one the diagonal ones
     hipLaunchKernelGGL(k_diag_sum, dim3((unsigned)T, kDiagParts, (unsigned)a.batch), dim3(256), 0, s, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    return hipGetLastError();
   }
   Planes3 pl{{a.Cpl[0], a.Cpl[1], a.Cpl[2]}};
   const int np = a.Cpl[2] ? 3 : (a.Cpl[1] ? 2 : (a.Cpl[0] ? 1 : 0));
