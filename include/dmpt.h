@@ -189,7 +189,9 @@ typedef struct {
   double idempotency;                    /* Tr[P0 (I - P0)] (check = 1) */
   double commutator;                     /* ||H0 P0 - P0 H0||_F (check = 1) */
   double asymmetry;                      /* max |P - P^T| over the outputs (check = 1) */
-  double mfma_flops;                     /* matrix-core flops executed (every split product counted) */
+  double mfma_flops;                     /* matrix-core flops of the products (every split product counted,
+                                            also those of zero digit blocks, which the int8 kernels
+                                            skip) */
   double useful_flops;                   /* 2 N^3 per logical matrix product */
   double seconds;                        /* wall time of the call */
 } dmpt_stats;
@@ -361,7 +363,8 @@ dmpt_status dmpt_sparse_response(dmpt_ctx ctx, int64_t N, const double* H0, int 
 typedef struct {
   int64_t launches;      /* product kernel launches timed */
   double ms;             /* summed device time of those launches (ms) */
-  double mfma_flops;     /* matrix-core flops of those launches (every split product counted) */
+  double mfma_flops;     /* matrix-core flops of those launches (every split product counted; the int8
+                            kernels skip the products of zero digit blocks, which still count here) */
   double useful_flops;   /* 2 N^3 per logical product and batch member */
   /* the same, per product engine: [0] FP64, [1] FP32, [2] BF16 3-product, [3] BF16 6-product,
      [4] int8 13-product, [5] int8 6-product (their mfma_flops are int8 operations) */

@@ -46,6 +46,7 @@ struct Group {
   uint16_t* pl[3] = {nullptr, nullptr, nullptr};
   int8_t* q8 = nullptr;          // int8 slices (I8S4, I8S3), members 4 stride bytes apart
   double* qs = nullptr;          // their q, one per member
+  uint8_t* zm = nullptr;         // their digit masks, members stride / 1024 bytes apart
   int count = 0;
 };
 
@@ -58,6 +59,7 @@ struct Q8Reg {
   int count = 0;
   int8_t* q8 = nullptr;
   double* qs = nullptr;
+  uint8_t* zm = nullptr;
   std::vector<char> dirty;
   // max |x| of the tiles of each member as the int8 product that last wrote
   // it left them (mx + z * mx_cap; mx_n[z] of them, 0: unknown, scan again)
@@ -602,7 +604,9 @@ bool ok_q8_bounds(const Call& k, const GemmArgs& a, int batch) {
   };
   auto nq = [&](const BOp& o) -> size_t { return (o.stride ? (size_t)((batch - 1) / o.div) : 0) + 1; };
   return a.X.q8 && a.Y.q8 && reg_ok(k.c, a.X.q8, span(a.X)) && reg_ok(k.c, a.Y.q8, span(a.Y)) &&
-         reg_ok(k.c, a.X.qs, nq(a.X) * sizeof(double)) && reg_ok(k.c, a.Y.qs, nq(a.Y) * sizeof(double));
+         reg_ok(k.c, a.X.qs, nq(a.X) * sizeof(double)) && reg_ok(k.c, a.Y.qs, nq(a.Y) * sizeof(double)) &&
+         a.X.zm && a.Y.zm && reg_ok(k.c, a.X.zm, span(a.X) / (kQ8Slices * 1024)) &&
+         reg_ok(k.c, a.Y.zm, span(a.Y) / (kQ8Slices * 1024));
 }
 
 dmpt_status q8_operand(const Call& k, BOp& o, int batch) {
@@ -629,6 +633,7 @@ dmpt_status q8_operand(const Call& k, BOp& o, int batch) {
       const double* src = (const double*)(r.m + (size_t)z * mb);
       int8_t* dst = r.q8 + (size_t)z * r.stride * kQ8Slices;
       double* qd = r.qs + z;
+      uint8_t* zd = r.zm + (size_t)z * (r.stride / 1024);
       const int cnt = e - z;
       const int64_t st = r.stride, Np = k.Np;
       double* part = c->d_qpart;
@@ -636,15 +641,16 @@ dmpt_status q8_operand(const Call& k, BOp& o, int batch) {
       if (kn > 0) {
         const double* known = r.mx + (size_t)z * r.mx_cap;
         const int64_t cap = r.mx_cap;
-        EMIT(k, quantize_q8_known(src, st, Np, cnt, known, cap, kn, dst, st * kQ8Slices, qd, s));
+        EMIT(k, quantize_q8_known(src, st, Np, cnt, known, cap, kn, dst, st * kQ8Slices, qd, zd, st / 1024, s));
       } else {
-        EMIT(k, quantize_q8(src, st, Np, cnt, part, dst, st * kQ8Slices, qd, nullptr, s));
+        EMIT(k, quantize_q8(src, st, Np, cnt, part, dst, st * kQ8Slices, qd, zd, st / 1024, nullptr, s));
       }
       for (int i = z; i < e; ++i) r.dirty[i] = 0;
       z = e;
     }
     o.q8 = r.q8 + (size_t)z0 * r.stride * kQ8Slices;
     o.qs = r.qs + z0;
+    o.zm = r.zm + (size_t)z0 * (r.stride / 1024);
     return DMPT_OK;
   }
   return fail(c, DMPT_ERR_ARG, "internal: an int8 product operand lies outside the sliced workspace");
@@ -1070,7 +1076,7 @@ dmpt_status cg_solve(const Call& k, const Group& u, int batch, int ydiv, const i
     if (preg) {
       if constexpr (std::is_same<T, double>::value) {
         EMIT(k, cg_update_p_q8(P, R, k.Np, st, batch, rr + it + 1, rr + it, hs, act, c->d_qpart, w->pb + it,
-                               w->pb + it + 1, preg->q8, st * kQ8Slices, preg->qs, s));
+                               w->pb + it + 1, preg->q8, st * kQ8Slices, preg->qs, preg->zm, st / 1024, s));
       }
       for (int z = 0; z < batch; ++z) preg->dirty[z] = 0;
     } else {
@@ -3442,17 +3448,19 @@ dmpt_status dmpt_init(dmpt_ctx* out, int device, int64_t n_max, int dirs_max, co
     if (planes && c->q8 && count > 0) {
       g.q8 = (int8_t*)alloc(nn * kQ8Slices * count);
       g.qs = (double*)alloc(sizeof(double) * count);
+      g.zm = (uint8_t*)alloc(nn / 1024 * count);
       // room for one maximum per product tile, and for the blocks of the
       // element-wise writers (up to 16384 per member keeps them streaming)
       const int64_t cap = std::max<int64_t>((c->np_max / 128) * (c->np_max / 128), 16384);
       double* mx = (double*)alloc(sizeof(double) * (size_t)cap * count);
-      if (!g.q8 || !g.qs || !mx) return false;
+      if (!g.q8 || !g.qs || !g.zm || !mx) return false;
       Q8Reg r;
       r.m = (const char*)g.m;
       r.stride = (int64_t)nn;
       r.count = count;
       r.q8 = g.q8;
       r.qs = g.qs;
+      r.zm = g.zm;
       r.dirty.assign(count, 1);
       r.mx = mx;
       r.mx_cap = cap;

@@ -50,6 +50,8 @@ inline int engine_terms(Engine e) {
 // v_mfma_i32_32x32x32_i8 (lane l holds row l % 32 and 16 consecutive k of
 // half l / 32), so a wave moves a slice block as 64 consecutive 16-byte
 // pieces.  A member takes 4 Np^2 bytes; its q sits in a separate FP64 array.
+// Beside the slices: one byte per 32 x 32 block (row / 32) * (Np / 32) + col / 32
+// with bit s set when digit s of any element of the block is not zero.
 constexpr int kQ8Slices = 4;
 constexpr double kQ8Base = 254.0;
 __host__ __device__ inline int64_t q8_off(int64_t row, int64_t col, int64_t Np, int s) {
@@ -92,6 +94,7 @@ struct BOp {
   const uint16_t* pl[3] = {nullptr, nullptr, nullptr};
   const int8_t* q8 = nullptr;  // I8S4: int8 slices of the member (4 stride bytes apart)
   const double* qs = nullptr;  // I8S4: q of the member (one double apart)
+  const uint8_t* zm = nullptr; // I8S4: digit masks of the member's 32 x 32 blocks (stride / 1024 bytes apart)
   int64_t stride = 0;
   int div = 1;
 };
@@ -191,14 +194,15 @@ hipError_t transpose(const T* in, int64_t Np, int64_t stride, T* out, uint16_t* 
 // Int8 slices (I8S4) of `batch` FP64 members x + z sx (Np x Np): block maxima
 // of |x| into part[z * nb ..] (nb = q8_blocks(Np)), then every block of the
 // slicing kernel reduces them to the member's max, writes q to qs[z] and its
-// share of the slices to q8 + z sq (bytes).
+// share of the slices to q8 + z sq and of the digit masks to zm + z szm (bytes).
 int q8_blocks(int64_t Np);
 hipError_t quantize_q8(const double* x, int64_t sx, int64_t Np, int batch, double* part, int8_t* q8, int64_t sq,
-                       double* qs, const int* active, hipStream_t s);
+                       double* qs, uint8_t* zm, int64_t szm, const int* active, hipStream_t s);
 // The same with the maxima already known: nb partial maxima per member at
 // part[z * pstride ..] (e.g. the tile maxima a product kernel wrote).
 hipError_t quantize_q8_known(const double* x, int64_t sx, int64_t Np, int batch, const double* part,
-                             int64_t pstride, int nb, int8_t* q8, int64_t sq, double* qs, hipStream_t s);
+                             int64_t pstride, int nb, int8_t* q8, int64_t sq, double* qs, uint8_t* zm, int64_t szm,
+                             hipStream_t s);
 
 // Split a master matrix into BF16 planes (batched).
 hipError_t split_planes(const double* x, int64_t n_elems, int64_t sx, uint16_t* const* planes,
@@ -234,8 +238,8 @@ hipError_t cg_update_xr(T* U, T* R, const T* P, const T* Q, int64_t n, int64_t s
 //   pb_new[z hstride]
 hipError_t cg_update_p_q8(double* P, const double* R, int64_t Np, int64_t stride, int batch, const double* rr_new,
                           const double* rr_old, int hstride, const int* active, const double* rmax,
-                          const double* pb_old, double* pb_new, int8_t* q8, int64_t sq, double* qs,
-                          hipStream_t s);
+                          const double* pb_old, double* pb_new, int8_t* q8, int64_t sq, double* qs, uint8_t* zm,
+                          int64_t szm, hipStream_t s);
 //   pb[z hstride] = 127 qs[z] (the bound of the first sliced P)
 hipError_t q8_bound_init(const double* qs, double* pb, int hstride, int batch, hipStream_t s);
 //   update_p: beta = rr_new[z]/rr_old[z]; P = R + beta P (+ planes)

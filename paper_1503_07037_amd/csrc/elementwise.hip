@@ -1053,8 +1053,8 @@ __global__ __launch_bounds__(kT) void k_qscale(const double* __restrict__ part, 
 
 __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int64_t sx, int64_t Np,
                                               int8_t* __restrict__ q8, int64_t sq, double* __restrict__ qs,
-                                              const int* active, const double* __restrict__ part, int64_t pstride,
-                                              int nb) {
+                                              uint8_t* __restrict__ zm, int64_t szm, const int* active,
+                                              const double* __restrict__ part, int64_t pstride, int nb) {
   const int z = blockIdx.y;
   if (active && !active[z]) return;
   __shared__ double sq_;
@@ -1110,6 +1110,7 @@ __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int6
           r = (r - q) * kQ8Base;
         }
       }
+      uint32_t digits = 0;  // the digits any lane of the block has
 #pragma unroll
       for (int sl = 0; sl < kQ8Slices; ++sl) {
         uint32_t w[4];
@@ -1117,7 +1118,9 @@ __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int6
         for (int q = 0; q < 4; ++q) w[q] = pack4(&d[sl][4 * q]);
         uint32_t* dst = (uint32_t*)(qm + ((blk * kQ8Slices + sl) << 10) + l * 16);
         *(uint4*)dst = make_uint4(w[0], w[1], w[2], w[3]);
+        digits |= (__ballot((w[0] | w[1] | w[2] | w[3]) != 0) != 0 ? 1u : 0u) << sl;
       }
+      if (l == 0) zm[(int64_t)z * szm + blk] = (uint8_t)digits;
     }
     __syncthreads();
   }
@@ -1135,7 +1138,8 @@ __global__ __launch_bounds__(kT) void k_cg_p_q8(double* __restrict__ P, const do
                                                 int64_t stride, const double* rr_new, const double* rr_old,
                                                 int hstride, const int* active, const double* __restrict__ rmax,
                                                 int nb, const double* pb_old, double* pb_new, int8_t* __restrict__ q8,
-                                                int64_t sq, double* __restrict__ qs) {
+                                                int64_t sq, double* __restrict__ qs, uint8_t* __restrict__ zm,
+                                                int64_t szm) {
   const int z = blockIdx.y;
   if (active && !active[z]) return;
   __shared__ double sm;
@@ -1181,13 +1185,16 @@ __global__ __launch_bounds__(kT) void k_cg_p_q8(double* __restrict__ P, const do
         }
       }
     }
+    uint32_t digits = 0;  // a block is one wave's 64 pieces
 #pragma unroll
     for (int sl = 0; sl < kQ8Slices; ++sl) {
       uint32_t w[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) w[q] = pack4(&d[sl][4 * q]);
       *(uint4*)(qm + ((blk * kQ8Slices + sl) << 10) + l * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+      digits |= (__ballot((w[0] | w[1] | w[2] | w[3]) != 0) != 0 ? 1u : 0u) << sl;
     }
+    if (l == 0) zm[(int64_t)z * szm + blk] = (uint8_t)digits;
   }
 }
 
@@ -1278,8 +1285,8 @@ DMPT_SYM_INST(float, double)
 int q8_blocks(int64_t Np) { return (int)red_grid(Np * Np); }
 
 hipError_t quantize_q8(const double* x, int64_t sx, int64_t Np, int batch, double* part, int8_t* q8, int64_t sq,
-                       double* qs, const int* active, hipStream_t s) {
-  if (Np <= 0 || Np % 32 != 0 || batch < 1 || !x || !part || !q8 || !qs) return hipErrorInvalidValue;
+                       double* qs, uint8_t* zm, int64_t szm, const int* active, hipStream_t s) {
+  if (Np <= 0 || Np % 32 != 0 || batch < 1 || !x || !part || !q8 || !qs || !zm) return hipErrorInvalidValue;
   const int64_t n = Np * Np;
   const unsigned nb = red_grid(n);
   hipLaunchKernelGGL(k_amax, dim3(nb, batch), dim3(kT), 0, s, x, sx, n, part, (int)nb, active);
@@ -1287,14 +1294,15 @@ hipError_t quantize_q8(const double* x, int64_t sx, int64_t Np, int batch, doubl
   const int64_t nblk = (Np / 32) * (Np / 32);
   int64_t g = (nblk + 2 * (kT / 64) - 1) / (2 * (kT / 64));
   if (g > 65535) g = 65535;
-  hipLaunchKernelGGL(k_quant, dim3((unsigned)g, batch), dim3(kT), 0, s, x, sx, Np, q8, sq, qs, active,
-                     (const double*)nullptr, (int64_t)0, 0);
+  hipLaunchKernelGGL(k_quant, dim3((unsigned)g, batch), dim3(kT), 0, s, x, sx, Np, q8, sq, qs, zm, szm,
+                     active, (const double*)nullptr, (int64_t)0, 0);
   return hipGetLastError();
 }
 
 hipError_t quantize_q8_known(const double* x, int64_t sx, int64_t Np, int batch, const double* part,
-                             int64_t pstride, int nb, int8_t* q8, int64_t sq, double* qs, hipStream_t s) {
-  if (Np <= 0 || Np % 32 != 0 || batch < 1 || !x || !part || nb < 1 || pstride < nb || !q8 || !qs)
+                             int64_t pstride, int nb, int8_t* q8, int64_t sq, double* qs, uint8_t* zm, int64_t szm,
+                             hipStream_t s) {
+  if (Np <= 0 || Np % 32 != 0 || batch < 1 || !x || !part || nb < 1 || pstride < nb || !q8 || !qs || !zm)
     return hipErrorInvalidValue;
   // up to 2304 maxima (18 KB, nine loads per thread) are cheaper to reduce in
   // every block than in a launch of their own (4.9 us at Np = 2048 and 9 at
@@ -1304,8 +1312,8 @@ hipError_t quantize_q8_known(const double* x, int64_t sx, int64_t Np, int batch,
   const int64_t nblk = (Np / 32) * (Np / 32);
   int64_t g = (nblk + 2 * (kT / 64) - 1) / (2 * (kT / 64));
   if (g > 65535) g = 65535;
-  hipLaunchKernelGGL(k_quant, dim3((unsigned)g, batch), dim3(kT), 0, s, x, sx, Np, q8, sq, qs, (const int*)nullptr,
-                     fused ? part : (const double*)nullptr, pstride, nb);
+  hipLaunchKernelGGL(k_quant, dim3((unsigned)g, batch), dim3(kT), 0, s, x, sx, Np, q8, sq, qs, zm, szm,
+                     (const int*)nullptr, fused ? part : (const double*)nullptr, pstride, nb);
   return hipGetLastError();
 }
 
@@ -1368,7 +1376,7 @@ template hipError_t cg_update_xr<float>(float*, float*, const float*, const floa
 
 hipError_t cg_update_p_q8(double* P, const double* R, int64_t Np, int64_t stride, int batch, const double* rr_new,
                           const double* rr_old, int hstride, const int* active, const double* rmax,
-                          const double* pb_old, double* pb_new, int8_t* q8, int64_t sq, double* qs,
+                          const double* pb_old, double* pb_new, int8_t* q8, int64_t sq, double* qs, uint8_t* zm, int64_t szm,
                           hipStream_t s) {
   if (Np <= 0 || Np % 32 != 0 || batch < 1) return hipErrorInvalidValue;
   const int64_t n = Np * Np;
@@ -1376,7 +1384,7 @@ hipError_t cg_update_p_q8(double* P, const double* R, int64_t Np, int64_t stride
   int64_t g = (pieces + 2 * kT - 1) / (2 * kT);
   if (g > 65535) g = 65535;
   hipLaunchKernelGGL(k_cg_p_q8, dim3((unsigned)g, batch), dim3(kT), 0, s, P, R, Np, stride, rr_new, rr_old, hstride,
-                     active, rmax, (int)red_grid(n), pb_old, pb_new, q8, sq, qs);
+                     active, rmax, (int)red_grid(n), pb_old, pb_new, q8, sq, qs, zm, szm);
   return hipGetLastError();
 }
 

@@ -104,3 +104,29 @@ def test_solves_that_run_ahead_of_the_host(dm, prec, N):
             ctx.profile(timed)
             with pytest.raises(dm.DMPTError):
                 ctx.mu_newton(T(h0), [T(h) for h in h1], beta=10.0, Ne=N // 2, n=20, order=1)
+
+
+@pytest.mark.parametrize("prec", ["int8x13", "int8x6"])
+def test_int8_zero_digit_blocks(dm, monkeypatch, prec):
+    """The int8 kernels (variants 0, 1) leave out the products of digit blocks that are zero; the variants
+    with LDS DMA copies and the same wave tiles (2, 3) compute them all.  The digit sums are exact
+    integers, so with whole diagonal tiles the results agree bit for bit: a scalar H0 (every iterate a multiple of I), narrow bands (whole
+    stages without a product), entries spread over the digits' range, dense matrices, ragged sizes."""
+    rng = np.random.default_rng(9)
+    beta, n, mu = 8.0, 12, 0.07
+    monkeypatch.setenv("DMPT_DIAG_SPLIT", "0")
+    decay = np.exp(-0.05 * np.abs(np.subtract.outer(np.arange(1100), np.arange(1100))))
+    dense = rng.standard_normal((1100, 1100))
+    cases = [("scalar", 0.3 * np.eye(640)), ("chain", workloads.chain_1d(1000, 3)),
+             ("decaying", (0.5 * (dense + dense.T)) * decay),
+             ("dense", 0.02 * (dense + dense.T)[:300, :300]), ("tiny", 0.3 * np.ones((1, 1)))]
+    for solver in ("ns", "cg"):
+        for name, h0 in cases:
+            N = h0.shape[0]
+            print(f"case int8 zero blocks {prec} {solver} {name} N={N}", flush=True)
+            out = []
+            for v in (0, 1, 2, 3):
+                with dm.Context(N, dirs_max=0, prec=prec, solver=solver, tol_cg=1e-6) as ctx:
+                    ctx.set_variant(N, v)
+                    out.append(ctx.fermi_recursion(T(h0), beta, mu, n)[0].cpu().numpy())
+            assert np.array_equal(out[0], out[2]) and np.array_equal(out[1], out[3]), name
