@@ -3034,7 +3034,7 @@ dmpt_status linear_orders(Call& k, const PassIn& base, int64_t N, int order, dou
 }
 
 // ---------------------------------------------------------------- thresholded block-sparse path
-// A block-sparse matrix (see sparse.hip) with its block count.
+// A block-sparse matrix (see sparse.hip) with its block count (-1: known to the device only).
 struct BSMat {
   BSView v;
   int nslots = 0;
@@ -3054,7 +3054,8 @@ struct Sparse {
   double* bmax = nullptr;       // max(cap, nb^2)
   double* part = nullptr;       // 4 cap
   double* nprods = nullptr;     // cap
-  double* scal = nullptr;       // 8
+  double* scal = nullptr;       // 9: [8] block products of the evaluations on the device
+  int* need = nullptr;          // 2: largest candidate count, largest that did not fit
   BSMat tmp;                    // candidate blocks of the current result
   std::vector<void*> allocs;
   double products = 0.0;
@@ -3063,9 +3064,27 @@ struct Sparse {
     if (s) (void)hipStreamSynchronize(s);
     for (void* p : allocs) dev_free(c, p);
   }
+  // one allocation for the whole call (about a hundred arrays: hipMalloc and
+  // hipFree take 50-100 us each), handed out in 256-byte steps
+  char* arena = nullptr;
+  size_t arena_left = 0;
+  static size_t step(size_t bytes) { return (std::max<size_t>(bytes, 1) + 255) / 256 * 256; }
+  size_t mat_bytes() const {
+    return step(sizeof(int) * (nb + 1)) + 2 * step(sizeof(int) * (size_t)cap) +
+           step(sizeof(double) * (size_t)cap * kSparseBlock * kSparseBlock);
+  }
+  bool reserve(size_t bytes) {
+    arena = (char*)dev_alloc(c, bytes);
+    if (!arena) return false;
+    allocs.push_back(arena);
+    arena_left = bytes;
+    return true;
+  }
   void* alloc(size_t bytes) {
-    void* p = dev_alloc(c, bytes);
-    if (p) allocs.push_back(p);
+    if (!arena || step(bytes) > arena_left) return nullptr;
+    void* p = arena;
+    arena += step(bytes);
+    arena_left -= step(bytes);
     return p;
   }
   bool make(BSMat& m) {
@@ -3094,11 +3113,29 @@ dmpt_status sp_capacity(Sparse& w, int need) {
   return DMPT_OK;
 }
 
+// The block count of m; reports an earlier result that did not fit.
+dmpt_status sp_count(Sparse& w, BSMat& m) {
+  if (m.nslots >= 0) return DMPT_OK;
+  HIPCHK(w.c, hipMemcpyAsync(w.c->h_int, m.v.rows + w.nb, sizeof(int), hipMemcpyDeviceToHost, w.s));
+  HIPCHK(w.c, hipMemcpyAsync(w.c->h_int + 1, w.need, 2 * sizeof(int), hipMemcpyDeviceToHost, w.s));
+  HIPCHK(w.c, hipStreamSynchronize(w.s));
+  w.blocks_max = std::max(w.blocks_max, (double)w.c->h_int[1]);
+  STCHK(sp_capacity(w, w.c->h_int[2]));
+  m.nslots = w.c->h_int[0];
+  return DMPT_OK;
+}
+
 // out = e, truncated (out must not be an operand of e).
 dmpt_status sp_eval(Sparse& w, const BSExpr& e0, BSMat& out) {
   BSExpr e = e0;
   e.n = w.N;
   hipStream_t s = w.s;
+  if (w.nb <= kSparseFusedRows) {
+    HIPCHK(w.c, sparse_eval(e, w.nb, w.cap, w.tau, w.bits, w.counts, w.tmp.v, w.bmax, w.nprods, out.v, w.need,
+                            w.scal + 8, s));
+    out.nslots = -1;
+    return DMPT_OK;
+  }
   HIPCHK(w.c, sparse_symbolic(e, w.nb, w.bits, w.counts, w.tmp.v.rows, s));
   int cand = 0;
   STCHK(sp_read_int(w, w.tmp.v.rows + w.nb, &cand));
@@ -3130,7 +3167,8 @@ dmpt_status sp_from_dense(Sparse& w, const double* H, double a, double shift, BS
 }
 
 // Trace, sum of squares, count of |shift I - m| >= thr, sum of H .* m.
-dmpt_status sp_stats(Sparse& w, const BSMat& m, double shift, double thr, const double* H, double out[4]) {
+dmpt_status sp_stats(Sparse& w, BSMat& m, double shift, double thr, const double* H, double out[4]) {
+  STCHK(sp_count(w, m));
   HIPCHK(w.c, sparse_stats(m.v, m.nslots, w.N, shift, thr, H, w.part, w.scal + 4, w.s));
   HIPCHK(w.c, hipMemcpyAsync(w.c->h_res + RES_MISC, w.scal + 4, 4 * sizeof(double), hipMemcpyDeviceToHost,
                              w.s));
@@ -3944,25 +3982,33 @@ dmpt_status dmpt_sparse_response(dmpt_ctx c, int64_t N, const double* H0, int d,
                              : (int)std::min<int64_t>((int64_t)w.nb * w.nb, INT32_MAX / 2);
   w.tau = tau;
   const int words = sparse_words(w.nb);
+  const size_t nmat = 9 + 4 * (size_t)(dd + (order >= 1 ? 1 : 0)) + (order >= 2 ? 4 * (size_t)dd : 0);
+  const size_t nn = (size_t)w.nb * w.nb, cap = (size_t)w.cap;
+  (void)w.reserve(nmat * w.mat_bytes() + Sparse::step(sizeof(uint32_t) * (size_t)w.nb * words) +
+                  Sparse::step(sizeof(int) * (size_t)(w.nb + 1)) + Sparse::step(sizeof(int) * cap) +
+                  Sparse::step(sizeof(double) * std::max(cap, nn)) + Sparse::step(sizeof(double) * 4 * cap) +
+                  Sparse::step(sizeof(double) * cap) + 2 * Sparse::step(sizeof(double) * 9));
   w.bits = (uint32_t*)w.alloc(sizeof(uint32_t) * (size_t)w.nb * words);
   w.counts = (int*)w.alloc(sizeof(int) * (size_t)(w.nb + 1));
   w.keep = (int*)w.alloc(sizeof(int) * (size_t)w.cap);
   w.bmax = (double*)w.alloc(sizeof(double) * std::max<size_t>((size_t)w.cap, (size_t)w.nb * w.nb));
   w.part = (double*)w.alloc(sizeof(double) * 4 * (size_t)w.cap);
   w.nprods = (double*)w.alloc(sizeof(double) * (size_t)w.cap);
-  w.scal = (double*)w.alloc(sizeof(double) * 8);
+  w.scal = (double*)w.alloc(sizeof(double) * 9);
+  w.need = (int*)w.alloc(sizeof(int) * 2);
   const int d1max = dd + (order >= 1 ? 1 : 0);  // directions plus J
   SparseJets J;
   J.D1.resize(d1max); J.S1.resize(d1max); J.R.resize(d1max); J.Y1.resize(d1max);
   J.D2.resize(order >= 2 ? dd : 0); J.T2.resize(J.D2.size()); J.S2.resize(J.D2.size()); J.Y2.resize(J.D2.size());
   BSMat PJ, tmpJ;
-  bool ok = w.bits && w.counts && w.keep && w.bmax && w.part && w.nprods && w.scal && w.make(w.tmp) &&
+  bool ok = w.bits && w.counts && w.keep && w.bmax && w.part && w.nprods && w.scal && w.need && w.make(w.tmp) &&
             w.make(J.D0) && w.make(J.S0) && w.make(J.Z) && w.make(J.M) && w.make(J.Zn) && w.make(J.Y0) &&
             w.make(PJ) && w.make(tmpJ);
   for (int z = 0; ok && z < d1max; ++z) ok = w.make(J.D1[z]) && w.make(J.S1[z]) && w.make(J.R[z]) && w.make(J.Y1[z]);
   for (size_t z = 0; ok && z < J.D2.size(); ++z)
     ok = w.make(J.D2[z]) && w.make(J.T2[z]) && w.make(J.S2[z]) && w.make(J.Y2[z]);
   if (!ok) return fail(c, DMPT_ERR_NOMEM, "sparse path: storage allocation failed (lower blocks_per_row)");
+  HIPCHK(c, set_values(w.need, 0, 2, w.scal + 8, 0.0, 1, c->stream));
   const double tol = std::max(c->opt.tol_occ, tau);
   double st4[4];
   auto occupation = [&](double* trp0, double* frob) -> dmpt_status {
@@ -4052,6 +4098,12 @@ dmpt_status dmpt_sparse_response(dmpt_ctx c, int64_t N, const double* H0, int d,
       std::swap(J.D2[z], J.Y2[z]);
     }
   }
+  // every result of the last evaluations must have fitted before anything is written
+  STCHK(sp_count(w, J.D0));
+  for (int z = 0; z < dd; ++z) {
+    STCHK(sp_count(w, J.D1[z]));
+    if (order >= 2) STCHK(sp_count(w, J.D2[z]));
+  }
   // outputs and statistics
   if (P0) HIPCHK(c, sparse_to_dense(J.D0.v, w.nb, N, -1.0, 0.5, P0, c->stream));
   for (int z = 0; z < dd; ++z) {
@@ -4088,8 +4140,11 @@ dmpt_status dmpt_sparse_response(dmpt_ctx c, int64_t N, const double* H0, int d,
         st->blocks_p2[z] = J.D2[z].nslots;
       }
     }
+    // (the counts above have brought blocks_max up to date)
+    HIPCHK(c, hipMemcpyAsync(c->h_res + RES_MISC, w.scal + 8, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     st->blocks_max = w.blocks_max;
-    st->block_products = w.products;
+    st->block_products = w.products + c->h_res[RES_MISC];
   }
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (st) st->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();

@@ -396,7 +396,16 @@ struct BSExpr {
   int64_t n = 0;
 };
 
+// Largest number of block rows sparse_eval handles (each of its blocks adds up
+// all rows' counts and reads all candidates' maxima: N <= 8192).
+constexpr int kSparseFusedRows = 256;
+
 int sparse_words(int nb);
+// out = e truncated, without the host: candidates in tmp (at most cap blocks; a
+// result with more becomes empty and its size goes to need[1]), need[0] = max(need[0],
+// candidates), *prods += block products formed.
+hipError_t sparse_eval(const BSExpr& e, int nb, int cap, double tau, uint32_t* bits, int* counts, const BSView& tmp,
+                       double* bmax, double* nprods, const BSView& out, int* need, double* prods, hipStream_t s);
 // Candidate pattern of e: bit rows, block-row counts and their exclusive scan rows[0..nb].
 hipError_t sparse_symbolic(const BSExpr& e, int nb, uint32_t* bits, int* counts, int* rows, hipStream_t s);
 // cols / ridx of a pattern from its bit rows and scanned rows.

@@ -13,7 +13,7 @@
 //
 // Every product or combination
 //     C = a1 A1 B1 + a2 A2 B2 + b1 C1 + b2 C2 + s I
-// runs in three launches: a symbolic pass marks the candidate blocks of each
+// runs in three passes: a symbolic pass marks the candidate blocks of each
 // block row in a bit row (union of the products' and addends' patterns), a
 // fill pass turns the bit rows into the block list (after a scan of the row
 // counts), and a numeric pass forms each candidate block with FP64 MFMA
@@ -23,6 +23,8 @@
 // every candidate), and a compaction packs them.
 #include "dmpt_internal.h"
 
+#include <algorithm>
+
 namespace dmpt {
 namespace {
 
@@ -31,6 +33,8 @@ typedef double d4v __attribute__((__vector_size__(4 * sizeof(double))));
 constexpr int kB = kSparseBlock;     // block edge
 constexpr int kBB = kB * kB;         // elements per block
 constexpr int kT = 256;
+constexpr int kFusedRows = kSparseFusedRows;
+static_assert(kFusedRows <= kT, "a block row's candidates are one per thread");
 
 // Slot of block (i, j) of m, or -1 (binary search in block row i).
 __device__ inline int find_block(const BSView& m, int i, int j) {
@@ -164,12 +168,11 @@ __global__ __launch_bounds__(kT) void k_fill(const uint32_t* bits, int words, co
 // the common inner blocks (FP64 MFMA, 2 x 2 tiles of 16 x 16, k in steps of
 // 4), the addends and the diagonal; bmax[s] = max |C_s|, nprods[s] = block
 // products formed.  Block products read their operand blocks straight from
-// global memory (each is 8 KB contiguous).
-__global__ __launch_bounds__(kT) void k_numeric(BSExpr e, BSView Cv, int nslots, double* bmax,
-                                                double* nprods) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int s = blockIdx.x * (kT / 64) + wave;
-  if (s >= nslots) return;
+// global memory (each is 8 KB contiguous).  The searches for the blocks of B
+// run side by side, one inner block per lane (one after the other each is a
+// chain of five dependent loads).
+__device__ inline void numeric_block(const BSExpr& e, const BSView& Cv, int s, double* bmax, double* nprods) {
+  const int lane = threadIdx.x & 63;
   const int i = Cv.ridx[s], j = Cv.cols[s];
   d4v acc[2][2];
 #pragma unroll
@@ -181,27 +184,32 @@ __global__ __launch_bounds__(kT) void k_numeric(BSExpr e, BSView Cv, int nslots,
     const BSView& A = e.A[t];
     const BSView& B = e.B[t];
     const double alpha = e.alpha[t];
-    for (int as = A.rows[i]; as < A.rows[i + 1]; ++as) {
-      const int k = A.cols[as];
-      const int bs = find_block(B, k, j);
-      if (bs < 0) continue;
-      ++nprod;
-      const double* Ab = A.val + (int64_t)as * kBB;
-      const double* Bb = B.val + (int64_t)bs * kBB;
+    const int a1 = A.rows[i + 1];
+    for (int base = A.rows[i]; base < a1; base += 64) {
+      const int mine = base + lane < a1 ? find_block(B, A.cols[base + lane], j) : -1;
+      unsigned long long found = __ballot(mine >= 0);
+      nprod += __popcll(found);
+      while (found) {
+        const int l = __ffsll((long long)found) - 1;
+        found &= found - 1;
+        const int as = base + l, bs = __builtin_amdgcn_readlane(mine, l);
+        const double* Ab = A.val + (int64_t)as * kBB;
+        const double* Bb = B.val + (int64_t)bs * kBB;
 #pragma unroll
-      for (int kk = 0; kk < kB; kk += 4) {
-        double av[2], bv[2];
-        // A operand: lane l holds row (l % 16) and inner index kk + l / 16
+        for (int kk = 0; kk < kB; kk += 4) {
+          double av[2], bv[2];
+          // A operand: lane l holds row (l % 16) and inner index kk + l / 16
 #pragma unroll
-        for (int a = 0; a < 2; ++a) av[a] = alpha * Ab[(a * 16 + (lane & 15)) * kB + kk + (lane >> 4)];
-        // B operand: lane l holds inner index kk + l / 16 and column (l % 16)
+          for (int a = 0; a < 2; ++a) av[a] = alpha * Ab[(a * 16 + (lane & 15)) * kB + kk + (lane >> 4)];
+          // B operand: lane l holds inner index kk + l / 16 and column (l % 16)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) bv[b] = Bb[(kk + (lane >> 4)) * kB + b * 16 + (lane & 15)];
+          for (int b = 0; b < 2; ++b) bv[b] = Bb[(kk + (lane >> 4)) * kB + b * 16 + (lane & 15)];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+          for (int a = 0; a < 2; ++a)
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+            for (int b = 0; b < 2; ++b)
+              acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+        }
       }
     }
   }
@@ -231,6 +239,20 @@ __global__ __launch_bounds__(kT) void k_numeric(BSExpr e, BSView Cv, int nslots,
     bmax[s] = mx;
     nprods[s] = (double)nprod;
   }
+}
+
+__global__ __launch_bounds__(kT) void k_numeric(BSExpr e, BSView Cv, int nslots, double* bmax,
+                                                double* nprods) {
+  const int s = __builtin_amdgcn_readfirstlane(blockIdx.x * (kT / 64) + (threadIdx.x >> 6));
+  if (s < nslots) numeric_block(e, Cv, s, bmax, nprods);
+}
+
+// The same with the number of candidates on the device (Cv.rows[nb]).
+__global__ __launch_bounds__(kT) void k_numeric_dev(BSExpr e, BSView Cv, int nb, double* bmax, double* nprods) {
+  const int n = Cv.rows[nb];
+  for (int s = __builtin_amdgcn_readfirstlane(blockIdx.x * (kT / 64) + (threadIdx.x >> 6)); s < n;
+       s += gridDim.x * (kT / 64))
+    numeric_block(e, Cv, s, bmax, nprods);
 }
 
 // Largest of n values into out[0] (one workgroup, n = 0 gives 0).
@@ -281,6 +303,130 @@ __global__ __launch_bounds__(kT) void k_compact(BSView src, const int* keep, int
     double2* to = (double2*)(dst.val + (int64_t)pos * kBB);
     for (int q = lane; q < kBB / 2; q += 64) to[q] = from[q];
     ++pos;
+  }
+}
+
+// ---- evaluation without the host (nb <= kFusedRows): the sizes of the
+// intermediate results stay on the device, so the host neither waits for them
+// nor copies them, and the scans and reductions move into the kernels that
+// use them (4 launches instead of 10, 3 copies and 2 synchronisations).  The
+// evaluations are bound by that chain, not by their products: N = 2048, 64
+// block rows, one direction to second order 105 -> 33 ms, same bits.  The rows
+// end at one candidate per thread (kFusedRows); above, every block would read
+// the maxima of more than 65536 blocks.
+
+__device__ inline int block_sum_int(int v) {
+  __shared__ int red[kT / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  int t = 0;
+  for (int q = 0; q < kT / 64; ++q) t += red[q];
+  return t;
+}
+
+// k_scan of the candidate counts and k_fill in one: block row i adds up the
+// counts before it itself.  A result that exceeds cap blocks becomes empty
+// (nothing is written past the storage) and need[1] records its size; need[0]
+// keeps the largest size.
+__global__ __launch_bounds__(kT) void k_scan_fill(const uint32_t* bits, int words, const int* counts, int nb, int cap,
+                                                  int* rows, int* cols, int* ridx, int* need) {
+  __shared__ int pre[kT];
+  const int i = blockIdx.x;
+  int before = 0, all = 0;
+  for (int r = threadIdx.x; r < nb; r += kT) {
+    const int c = counts[r];
+    all += c;
+    if (r < i) before += c;
+  }
+  before = block_sum_int(before);
+  all = block_sum_int(all);
+  const bool over = all > cap;
+  if (threadIdx.x == 0) {
+    rows[i] = over ? 0 : before;
+    if (i == nb - 1) rows[nb] = over ? 0 : all;
+    if (i == 0) {
+      need[0] = max(need[0], all);
+      if (over) need[1] = max(need[1], all);
+    }
+  }
+  if (over) return;
+  const uint32_t* row = bits + (int64_t)i * words;
+  for (int base = 0; base < words; base += kT) {
+    const int w = base + (int)threadIdx.x;
+    const uint32_t v = w < words ? row[w] : 0u;
+    const int pc = __popc(v);
+    __syncthreads();
+    pre[threadIdx.x] = pc;
+    __syncthreads();
+    int pos = before;
+    for (int q = 0; q < (int)threadIdx.x && base + q < words; ++q) pos += pre[q];
+    uint32_t x = v;
+    while (x) {
+      const int b = __ffs(x) - 1;
+      x &= x - 1;
+      cols[pos] = w * 32 + b;
+      ridx[pos] = i;
+      ++pos;
+    }
+    before += block_sum_int(pc);
+  }
+}
+
+// Truncation and compaction of block row i: the largest element of the whole
+// result, the kept blocks before this row and the row's own kept blocks from
+// the block maxima (see k_keep), then the copies.  Block row 0 adds the block
+// products formed to *prods.
+__global__ __launch_bounds__(kT) void k_keep_compact(BSView src, const double* bmax, const double* nprods, int nb,
+                                                     double tau, BSView dst, double* prods) {
+  __shared__ double redd[kT / 64];
+  __shared__ int list[kFusedRows];
+  const int i = blockIdx.x;
+  const int n = src.rows[nb], r0 = src.rows[i], m = src.rows[i + 1] - r0;
+  double mx = 0.0;
+  for (int q = threadIdx.x; q < n; q += kT) mx = fmax(mx, bmax[q]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+  if ((threadIdx.x & 63) == 0) redd[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  for (int q = 0; q < kT / 64; ++q) mx = fmax(mx, redd[q]);
+  auto keep = [&](int s) { return tau > 0.0 ? bmax[s] >= tau * mx : true; };
+  int before = 0;
+  for (int q = threadIdx.x; q < r0; q += kT) before += keep(q) ? 1 : 0;
+  before = block_sum_int(before);
+  // the row has at most nb <= kT candidates: one per thread
+  const bool on = (int)threadIdx.x < m && keep(r0 + (int)threadIdx.x);
+  const unsigned long long bal = __ballot(on);
+  int pos = __popcll(bal & ((1ull << (threadIdx.x & 63)) - 1));
+  __shared__ int wc[kT / 64];
+  if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = __popcll(bal);
+  __syncthreads();
+  int kept = 0;
+  for (int q = 0; q < kT / 64; ++q) {
+    if (q < (int)(threadIdx.x >> 6)) pos += wc[q];
+    kept += wc[q];
+  }
+  if (on) {
+    list[pos] = r0 + (int)threadIdx.x;
+    dst.cols[before + pos] = src.cols[r0 + (int)threadIdx.x];
+    dst.ridx[before + pos] = i;
+  }
+  if (threadIdx.x == 0) {
+    dst.rows[i] = before;
+    if (i == nb - 1) dst.rows[nb] = before + kept;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < kept * (kBB / 2); q += kT) {
+    const int b = q / (kBB / 2), o = q % (kBB / 2);
+    ((double2*)(dst.val + (int64_t)(before + b) * kBB))[o] = ((const double2*)(src.val + (int64_t)list[b] * kBB))[o];
+  }
+  if (i == 0) {
+    int t = 0;
+    for (int q = threadIdx.x; q < n; q += kT) t += (int)nprods[q];
+    t = block_sum_int(t);
+    if (threadIdx.x == 0) *prods += (double)t;
   }
 }
 
@@ -474,6 +620,20 @@ hipError_t sparse_numeric(const BSExpr& e, const BSView& C, int nslots, double t
   hipLaunchKernelGGL(k_max, dim3(1), dim3(kT), 0, s, bmax, (int64_t)nslots, scal + 1);
   if (nslots > 0)
     hipLaunchKernelGGL(k_keep, dim3((nslots + 255) / 256), dim3(256), 0, s, bmax, nslots, tau, scal + 1, keep);
+  return hipGetLastError();
+}
+
+hipError_t sparse_eval(const BSExpr& e, int nb, int cap, double tau, uint32_t* bits, int* counts, const BSView& tmp,
+                       double* bmax, double* nprods, const BSView& out, int* need, double* prods, hipStream_t s) {
+  const int words = sparse_words(nb);
+  if (nb < 1 || nb > kFusedRows || cap < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_symbolic, dim3(nb), dim3(kT), (size_t)words * sizeof(uint32_t), s, e, nb, words, bits, counts);
+  hipLaunchKernelGGL(k_scan_fill, dim3(nb), dim3(kT), 0, s, bits, words, counts, nb, cap, tmp.rows, tmp.cols, tmp.ridx,
+                     need);
+  // a candidate per wave for up to 4096, the rest in turn
+  const int blocks = (int)std::min<int64_t>(((int64_t)cap + kT / 64 - 1) / (kT / 64), 1024);
+  hipLaunchKernelGGL(k_numeric_dev, dim3(blocks), dim3(kT), 0, s, e, tmp, nb, bmax, nprods);
+  hipLaunchKernelGGL(k_keep_compact, dim3(nb), dim3(kT), 0, s, tmp, bmax, nprods, nb, tau, out, prods);
   return hipGetLastError();
 }
 

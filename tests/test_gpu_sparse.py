@@ -121,3 +121,25 @@ def test_sparse_linear_scaling(dm):
     for q in range(5):
         vals = [r[q] for r in per]
         assert max(vals) <= 1.1 * min(vals), (q, vals)
+
+
+@pytest.mark.parametrize("N", [5, 32, 33, 1000, 8192, 8200])
+def test_sparse_sizes_on_both_sides_of_the_host_free_form(dm, N):
+    """One block row, ragged edges, and N on both sides of the largest size whose intermediate results
+    are sized on the device (8192): P0 against the oracle's closed form (absolute errors far below
+    the truncation's, as in the truncated chain above), and a capacity that is too small is refused."""
+    print(f"case sparse N={N}", flush=True)
+    beta, n = 10.0, 22
+    h0 = workloads.dimer_chain(N, 5)
+    H0 = T(h0)
+    with dm.Context(128, dirs_max=1, prec="fp64") as ctx:
+        P0, _, _, mu, st = ctx.sparse_response(H0, beta=beta, Ne=float(max(1, N // 2)), n=n, order=0, tau=1e-9,
+                                               count_thr=1e-5, blocks_per_row=48)
+        assert st["blocks_max"] <= 48 * ((N + 31) // 32) and st["block_products"] > 0
+        if N <= 1000:
+            assert np.abs(P0.cpu().numpy() - oracle.density(h0, beta, n, mu[0])).max() < 1e-6
+        assert abs(float(torch.diagonal(P0).sum()) - max(1, N // 2)) < 1e-6 * N
+        if N >= 1000:
+            with pytest.raises(dm.DMPTError) as e:
+                ctx.sparse_response(H0, beta=beta, Ne=N / 2.0, n=n, order=0, tau=1e-9, blocks_per_row=2)
+            assert "blocks_per_row" in str(e.value)
