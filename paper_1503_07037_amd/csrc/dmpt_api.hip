@@ -376,6 +376,9 @@ struct Op {
   GemmArgs ga{};
   CgOp cgop = CgOp::Begin;
   CgArgs ca{};
+  bool ew = false;               // ewop, ea describe the launch fn makes
+  EwOp ewop = EwOp::Sym;
+  EwArgs ea{};
   std::function<hipError_t()> fn;
 };
 
@@ -420,6 +423,16 @@ struct Call {
     } else {                                                                   \
       HIPCHK((k).c, (expr));                                                   \
     }                                                                          \
+  } while (0)
+
+// Describe the launch just recorded, so that build_plan can group it.
+#define EMITTED(k, op, args)       \
+  do {                             \
+    if ((k).rec) {                 \
+      (k).rec->back().ew = true;   \
+      (k).rec->back().ewop = op;   \
+      (k).rec->back().ea = (args); \
+    }                              \
   } while (0)
 
 // Chain flags of a pass (linear schedule): save or load the order-0/1
@@ -808,6 +821,7 @@ dmpt_status sum_gemm_partials(const Call& k, int batch, double* out, int ostride
   hipStream_t s = k.c->stream;
   double* part = k.part;
   EMIT(k, sum_partials(part, count, batch, out, ostride, oidx, s, group));
+  if (ostride == 1) EMITTED(k, EwOp::Sum, ew_sum(part, count, batch, out + oidx, 1.0, group));
   return DMPT_OK;
 }
 
@@ -830,6 +844,9 @@ dmpt_status sym_inplace(const Call& k, const Group& g, int z0, int batch, double
   double* mx = q8_sink(k, g, z0, batch, sym_pair_blocks(k.Np, batch), &ms);
   EMIT(k, (sym_combine<T, T>(m, k.Np, k.stride, k.N, k.Np, a, nullptr, 0, m, k.Np, k.stride, pl, k.np, batch,
                              s, nullptr, 0.0, nullptr, mx, ms)));
+  if constexpr (std::is_same<T, double>::value)
+    if (!mx) EMITTED(k, EwOp::Sym, ew_sym(m, k.Np, k.stride, k.N, k.Np, a, nullptr, m, k.Np, k.stride, pl, k.np, batch,
+                                          nullptr));
   return DMPT_OK;
 }
 
@@ -847,6 +864,9 @@ dmpt_status sym_to(const Call& k, const Group& in, const Group& out, int batch, 
   double* mx = q8_sink(k, out, 0, batch, sym_pair_blocks(k.Np, batch), &ms);
   EMIT(k, (sym_combine<T, T>(src, k.Np, k.stride, k.N, k.Np, 1.0, nullptr, 0, dst, k.Np, k.stride, pl, npl,
                              batch, s, nullptr, 0.0, nullptr, mx, ms)));
+  if constexpr (std::is_same<T, double>::value)
+    if (!mx) EMITTED(k, EwOp::Sym, ew_sym(src, k.Np, k.stride, k.N, k.Np, 1.0, nullptr, dst, k.Np, k.stride, pl, npl,
+                                          batch, nullptr));
   return DMPT_OK;
 }
 
@@ -955,6 +975,7 @@ dmpt_status cg_solve_fused(const Call& k, const Group& u, int batch, int ydiv, c
     const int* its = a.iters;
     hipStream_t s = c->stream;
     EMIT(k, cg_account(act, its, batch, stat, s));
+    EMITTED(k, EwOp::Account, ew_account(act, its, batch, stat));
     return DMPT_OK;
   }
   int& guess = c->cg_guess[batch > 1];
@@ -1089,6 +1110,7 @@ dmpt_status cg_solve(const Call& k, const Group& u, int batch, int ydiv, const i
     // fixed-count solve: its statistics accumulate on the device (read after the replays)
     int* stat = c->d_cgstat;
     EMIT(k, cg_account(act, its, batch, stat, s));
+    EMITTED(k, EwOp::Account, ew_account(act, its, batch, stat));
     return DMPT_OK;
   }
   HIPCHK(c, hipMemcpyAsync(c->h_int, w->active, batch * sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1302,7 +1324,10 @@ dmpt_status solve_order0(const Call& k, int step) {
     double* part = k.part;
     double* ref = w->ref;
     EMIT(k, dot_partials<T>(d0, k.stride, d0, k.stride, k.nn, k.m, part, s));
+    if constexpr (std::is_same<T, double>::value)
+      EMITTED(k, EwOp::Dot, ew_dot(d0, d0, k.stride, k.nn, k.m, part));
     EMIT(k, sum_partials(part, reduce_blocks(k.nn), k.m, ref, 1, 0, s, 1, 4.0));
+    EMITTED(k, EwOp::Sum, ew_sum(part, reduce_blocks(k.nn), k.m, ref, 4.0));
   }
   const bool guess_tj = k.traj && c->tj_valid >= 0 && step >= 0;
   if (guess_tj && k.rec) return fail(c, DMPT_ERR_ARG, "internal: recorded passes keep no trajectory");
@@ -2505,9 +2530,10 @@ double kappa_bound(double x, int step) {
 // The recursion steps of one batched pass, recorded before graph capture:
 // every bucket runs the same sequence of launches (the same code path with a
 // common CG count per step), so launch i of every bucket can be issued
-// together.  Where launch i is a product in every bucket, one grouped launch
-// covers all buckets' (member, tile) blocks; other launches are issued bucket
-// by bucket.  Each bucket has its own slice of the partial-sum buffer.
+// together.  Where launch i is a product, a fused CG launch or one of the
+// launches EwArgs describes in every bucket, one grouped launch covers all
+// buckets' blocks; other launches are issued bucket by bucket.  The inputs and
+// outputs are grouped over all systems.  Each bucket has its own slice of the partial-sum buffer.
 struct BatchedPlan {
   std::vector<std::vector<Op>> ops;     // per bucket
   struct Group {
@@ -2524,6 +2550,16 @@ struct BatchedPlan {
   };
   std::vector<CgGroup> cgs;             // grouped CG launches
   std::vector<int> cg_group;            // per launch index: its CG group, or -1
+  struct EwGroup {
+    EwOp op;
+    int list_off, start_off, nprob, blocks;
+  };
+  std::vector<EwGroup> ews;             // grouped small launches
+  std::vector<int> ew_group;            // per launch index: its small-launch group, or -1
+  // the launches before and after the steps, one problem per system
+  std::vector<std::pair<EwOp, std::vector<EwArgs>>> in, out;
+  std::vector<EwGroup> in_ews, out_ews;
+  EwArgs* d_ewlist = nullptr;
   CgArgs* d_cglist = nullptr;
   GemmArgs* d_list = nullptr;           // device copies of the grouped products' arguments
   int* d_start = nullptr;
@@ -2595,11 +2631,77 @@ dmpt_status batched_pass(dmpt_ctx c, std::vector<Bucket>& bk, int wsi, int ord, 
         ks[b].rec = nullptr;
       }
     }
+    if constexpr (std::is_same<T, double>::value) {
+      // the inputs and outputs of all systems, launch by launch
+      std::vector<EwArgs> ins;
+      std::vector<std::vector<EwArgs>> outs;
+      size_t off = 0;  // partial sums of a launch's systems
+      for (size_t b = 0; b < bk.size(); ++b) {
+        const Call& k = ks[b];
+        for (int i = 0; i < k.m; ++i) {
+          const int slot = bk[b].first + i, sys = slot_sys[slot];
+          const int64_t N = Ns[sys];
+          const int* gate = k.w->mask0 + i;
+          double* sh = d_mu_shift + (int64_t)slot * J;
+          double* t = d_tr + (int64_t)slot * rs;
+          auto load = [&](const double* H, double a, const double* shift, const Group& g, int mem) {
+            uint16_t* pl[3];
+            planes_of(k, g, mem, pl);
+            ins.push_back(ew_sym(H, N, 0, N, k.Np, a, shift, (double*)mptr(k, g, mem), k.Np, 0, pl, k.np, 1, gate));
+          };
+          load(H0s[sys], 0.5 * cs[sys], sh, k.w->D0, i);
+          if (lin == 1) load(H0s[sys], 0.0, d_par + 6 * (int64_t)slot + 2, k.w->D1, i * dd + d);
+          for (int z = 0; z < d && ord >= 1; ++z) {
+            load(H1s[sys * d + z], 0.5 * cs[sys], sh + 1 + z, k.w->D1, i * dd + z);
+            if (ord >= 2) load(H1s[sys * d + z], 0.0, sh + 1 + d + z, k.w->D2, i * dd + z);
+          }
+          const int nbd = reduce_blocks(N * N);
+          double* part = c->d_part + off;
+          off += nbd;
+          size_t at = 0;
+          auto put = [&](EwOp op, const EwArgs& e) {
+            if (plan->out.size() <= at) plan->out.push_back({op, {}});
+            plan->out[at++].second.push_back(e);
+          };
+          auto store = [&](const Group& g, int mem, const double* shift, double* P, double* tr, double* atr) {
+            put(EwOp::Sym, ew_sym((const double*)mptr(k, g, mem), k.Np, 0, N, k.Np, -0.5, shift, P, N, 0, nullptr, 0,
+                                  1, gate));
+            put(EwOp::Trace, ew_trace(P, N, N, tr, atr));
+          };
+          auto dot = [&](const double* x, const double* y, double* to) {
+            put(EwOp::Dot, ew_dot(x, y, 0, N * N, 1, part));
+            put(EwOp::Sum, ew_sum(part, nbd, 1, to, 1.0));
+          };
+          store(k.w->D0, i, d_half, P0s[sys], t, t + J);
+          dot(P0s[sys], P0s[sys], t + 2 * J);
+          for (int o = 1; o <= ord; ++o)
+            for (int z = 0; z < d; ++z) {
+              double* Pk = o == 1 ? P1s[sys * d + z] : P2s[sys * d + z];
+              const int jt = (o == 1 ? 1 : 1 + d) + z;
+              store(o == 1 ? k.w->D1 : k.w->D2, i * dd + z, nullptr, Pk, t + jt, t + J + jt);
+              dot(H1s[sys * d + z], Pk, t + 2 * J + 1 + (o == 1 ? 0 : d) + z);
+            }
+          if (lin == 1) {
+            store(k.w->D1, i * dd + d, nullptr, PJs[slot], t + rs0, t + rs0 + 1);
+            for (int z = 0; z < d; ++z) dot(H1s[sys * d + z], PJs[slot], t + rs0 + 2 + z);
+          }
+        }
+      }
+      if (off > c->part_count) return fail(c, DMPT_ERR_ARG, "internal: batched partials exceed their buffer");
+      plan->in = {{EwOp::Sym, ins}};
+    }
     return DMPT_OK;
   }
   // D_0 of every system and direction from the caller inputs; the shifts
   // -c mu live on the device so the graph picks up each Newton update.
-  for (size_t b = 0; b < bk.size(); ++b) {
+  auto play = [&](const BatchedPlan::EwGroup& G) -> dmpt_status {
+    HIPCHK(c, ew_grouped(G.op, plan->d_ewlist + G.list_off, plan->d_start + G.start_off, G.nprob, G.blocks, s));
+    return DMPT_OK;
+  };
+  const bool io = plan && !plan->in_ews.empty();  // inputs and outputs in launches over all systems
+  if (io)
+    for (auto& G : plan->in_ews) STCHK(play(G));
+  for (size_t b = 0; !io && b < bk.size(); ++b) {
     const Call& k = ks[b];
     for (int i = 0; i < k.m; ++i) {
       const int slot = bk[b].first + i, sys = slot_sys[slot];
@@ -2649,6 +2751,8 @@ dmpt_status batched_pass(dmpt_ctx c, std::vector<Bucket>& bk, int wsi, int ord, 
       } else if (plan->cg_group[i] >= 0) {
         const BatchedPlan::CgGroup& G = plan->cgs[plan->cg_group[i]];
         HIPCHK(c, cg_grouped(G.op, plan->d_cglist + G.list_off, plan->d_start + G.start_off, G.nprob, G.blocks, s));
+      } else if (plan->ew_group[i] >= 0) {
+        STCHK(play(plan->ews[plan->ew_group[i]]));
       } else {
         for (size_t b = 0; b < bk.size(); ++b) {
           const Op& o = plan->ops[b][i];
@@ -2665,6 +2769,8 @@ dmpt_status batched_pass(dmpt_ctx c, std::vector<Bucket>& bk, int wsi, int ord, 
       }
   }
   // outputs and traces, per system
+  if (io)
+    for (auto& G : plan->out_ews) STCHK(play(G));
   for (size_t b = 0; b < bk.size(); ++b) {
     const Call& k = ks[b];
     for (int i = 0; i < k.m; ++i) {
@@ -2672,32 +2778,36 @@ dmpt_status batched_pass(dmpt_ctx c, std::vector<Bucket>& bk, int wsi, int ord, 
       const int64_t N = Ns[sys];
       double* t = d_tr + (int64_t)slot * rs;
       const int* gate = k.w->mask0 + i;  // converged systems keep their outputs
-      HIPCHK(c, (sym_combine<T, double>((const T*)mptr(k, k.w->D0, i), k.Np, 0, N, k.Np, -0.5, d_half,
-                                        0, P0s[sys], N, 0, nullptr, 0, 1, s, nullptr, 0.0, gate)));
-      HIPCHK(c, trace<double>(P0s[sys], N, 0, N, 1, t, 1, t + J, s));
-      HIPCHK(c, dot_partials<double>(P0s[sys], 0, P0s[sys], 0, N * N, 1, c->d_part, s));
-      HIPCHK(c, sum_partials(c->d_part, reduce_blocks(N * N), 1, t + 2 * J, 1, 0, s));
-      for (int o = 1; o <= ord; ++o)
-        for (int z = 0; z < d; ++z) {
-          const int mem = i * dd + z;
-          double* Pk = o == 1 ? P1s[sys * d + z] : P2s[sys * d + z];
-          const Group& g = o == 1 ? k.w->D1 : k.w->D2;
-          const int jt = (o == 1 ? 1 : 1 + d) + z;
-          HIPCHK(c, (sym_combine<T, double>((const T*)mptr(k, g, mem), k.Np, 0, N, k.Np, -0.5, nullptr,
-                                            0, Pk, N, 0, nullptr, 0, 1, s, nullptr, 0.0, gate)));
-          HIPCHK(c, trace<double>(Pk, N, 0, N, 1, t + jt, 1, t + J + jt, s));
-          HIPCHK(c, dot_partials<double>(H1s[sys * d + z], 0, Pk, 0, N * N, 1, c->d_part, s));
-          HIPCHK(c, sum_partials(c->d_part, reduce_blocks(N * N), 1,
-                                 t + 2 * J + 1 + (o == 1 ? 0 : d) + z, 1, 0, s));
-        }
+      if (!io) {
+        HIPCHK(c, (sym_combine<T, double>((const T*)mptr(k, k.w->D0, i), k.Np, 0, N, k.Np, -0.5, d_half,
+                                          0, P0s[sys], N, 0, nullptr, 0, 1, s, nullptr, 0.0, gate)));
+        HIPCHK(c, trace<double>(P0s[sys], N, 0, N, 1, t, 1, t + J, s));
+        HIPCHK(c, dot_partials<double>(P0s[sys], 0, P0s[sys], 0, N * N, 1, c->d_part, s));
+        HIPCHK(c, sum_partials(c->d_part, reduce_blocks(N * N), 1, t + 2 * J, 1, 0, s));
+        for (int o = 1; o <= ord; ++o)
+          for (int z = 0; z < d; ++z) {
+            const int mem = i * dd + z;
+            double* Pk = o == 1 ? P1s[sys * d + z] : P2s[sys * d + z];
+            const Group& g = o == 1 ? k.w->D1 : k.w->D2;
+            const int jt = (o == 1 ? 1 : 1 + d) + z;
+            HIPCHK(c, (sym_combine<T, double>((const T*)mptr(k, g, mem), k.Np, 0, N, k.Np, -0.5, nullptr,
+                                              0, Pk, N, 0, nullptr, 0, 1, s, nullptr, 0.0, gate)));
+            HIPCHK(c, trace<double>(Pk, N, 0, N, 1, t + jt, 1, t + J + jt, s));
+            HIPCHK(c, dot_partials<double>(H1s[sys * d + z], 0, Pk, 0, N * N, 1, c->d_part, s));
+            HIPCHK(c, sum_partials(c->d_part, reduce_blocks(N * N), 1,
+                                   t + 2 * J + 1 + (o == 1 ? 0 : d) + z, 1, 0, s));
+          }
+      }
       if (lin == 1) {
         double* PJ = PJs[slot];
-        HIPCHK(c, (sym_combine<T, double>((const T*)mptr(k, k.w->D1, i * dd + d), k.Np, 0, N, k.Np, -0.5,
-                                          nullptr, 0, PJ, N, 0, nullptr, 0, 1, s, nullptr, 0.0, gate)));
-        HIPCHK(c, trace<double>(PJ, N, 0, N, 1, t + rs0, 1, t + rs0 + 1, s));
-        for (int z = 0; z < d; ++z) {
-          HIPCHK(c, dot_partials<double>(H1s[sys * d + z], 0, PJ, 0, N * N, 1, c->d_part, s));
-          HIPCHK(c, sum_partials(c->d_part, reduce_blocks(N * N), 1, t + rs0 + 2 + z, 1, 0, s));
+        if (!io) {
+          HIPCHK(c, (sym_combine<T, double>((const T*)mptr(k, k.w->D1, i * dd + d), k.Np, 0, N, k.Np, -0.5,
+                                            nullptr, 0, PJ, N, 0, nullptr, 0, 1, s, nullptr, 0.0, gate)));
+          HIPCHK(c, trace<double>(PJ, N, 0, N, 1, t + rs0, 1, t + rs0 + 1, s));
+          for (int z = 0; z < d; ++z) {
+            HIPCHK(c, dot_partials<double>(H1s[sys * d + z], 0, PJ, 0, N * N, 1, c->d_part, s));
+            HIPCHK(c, sum_partials(c->d_part, reduce_blocks(N * N), 1, t + rs0 + 2 + z, 1, 0, s));
+          }
         }
         HIPCHK(c, lin_correct(t, d, J, rs0, d_mu + (int64_t)slot * J, d_mu_shift + (int64_t)slot * J,
                               cs[sys], d_delta + (int64_t)slot * d, P1s + (size_t)sys * d, PJ, N, gate,
@@ -2714,9 +2824,9 @@ dmpt_status batched_pass(dmpt_ctx c, std::vector<Bucket>& bk, int wsi, int ord, 
   return DMPT_OK;
 }
 
-// Group the recorded launches: launch i is grouped when it is a product in
-// every bucket; products with the same variant and tile edge share one
-// grouped launch.  The arguments and block offsets are copied to the device
+// Group the recorded launches: launch i is grouped when it is a product, a
+// fused CG launch or a describable small launch in every bucket; products with
+// the same variant and tile edge share one grouped launch.  The arguments and block offsets are copied to the device
 // (before capture; they stay there for every replay).
 dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned) {
   const size_t nb = plan.ops.size();
@@ -2728,11 +2838,28 @@ dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned)
   std::vector<int> starts;
   plan.first_group.assign(nops, -1);
   plan.cg_group.assign(nops, -1);
+  plan.ew_group.assign(nops, -1);
   std::vector<CgArgs> cglist;
+  std::vector<EwArgs> ewlist;
+  // one group of small launches; a problem its own launch would refuse leaves none
+  auto add_ew = [&](EwOp op, const std::vector<EwArgs>& probs, std::vector<BatchedPlan::EwGroup>& to) {
+    for (auto& e : probs)
+      if (e.blocks < 1 || e.batch < 1) return false;
+    BatchedPlan::EwGroup G{op, (int)ewlist.size(), (int)starts.size(), (int)probs.size(), 0};
+    for (auto& e : probs) {
+      ewlist.push_back(e);
+      starts.push_back(G.blocks);
+      G.blocks += e.blocks * e.batch;
+    }
+    starts.push_back(G.blocks);
+    to.push_back(G);
+    return true;
+  };
   for (size_t i = 0; i < nops; ++i) {
-    bool all = true, cg = true;
+    bool all = true, cg = true, ew = true;
     for (size_t b = 0; b < nb; ++b) {
       all = all && plan.ops[b][i].gemm;
+      ew = ew && plan.ops[b][i].ew && plan.ops[b][i].ewop == plan.ops[0][i].ewop;
       cg = cg && plan.ops[b][i].cg && plan.ops[b][i].cgop == plan.ops[0][i].cgop;
     }
     if (cg) {
@@ -2746,6 +2873,14 @@ dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned)
       plan.cg_group[i] = (int)plan.cgs.size();
       plan.cgs.push_back(G);
       continue;
+    }
+    if (ew) {
+      std::vector<EwArgs> probs;
+      for (size_t b = 0; b < nb; ++b) probs.push_back(plan.ops[b][i].ea);
+      if (add_ew(plan.ops[0][i].ewop, probs, plan.ews)) {
+        plan.ew_group[i] = (int)plan.ews.size() - 1;
+        continue;
+      }
     }
     if (!all) {
       for (size_t b = 0; b < nb; ++b)
@@ -2784,7 +2919,25 @@ dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned)
       plan.groups.push_back(G);
     }
   }
-  if (list.empty()) return DMPT_OK;
+  bool io = !plan.in.empty();
+  for (auto& g : plan.in) io = io && add_ew(g.first, g.second, plan.in_ews);
+  for (auto& g : plan.out) io = io && add_ew(g.first, g.second, plan.out_ews);
+  if (!io) {
+    plan.in_ews.clear();
+    plan.out_ews.clear();
+  }
+  if (list.empty()) {
+    // nothing to multiply: every launch is issued by itself
+    plan.in_ews.clear();
+    plan.ew_group.assign(nops, -1);
+    return DMPT_OK;
+  }
+  if (!ewlist.empty()) {
+    plan.d_ewlist = (EwArgs*)dev_alloc(c, ewlist.size() * sizeof(EwArgs));
+    if (!plan.d_ewlist) return fail(c, DMPT_ERR_NOMEM, "batched plan allocation failed");
+    owned.push_back(plan.d_ewlist);
+    HIPCHK(c, hipMemcpy(plan.d_ewlist, ewlist.data(), ewlist.size() * sizeof(EwArgs), hipMemcpyHostToDevice));
+  }
   plan.d_list = (GemmArgs*)dev_alloc(c, list.size() * sizeof(GemmArgs));
   plan.d_start = (int*)dev_alloc(c, starts.size() * sizeof(int));
   if (!cglist.empty()) {

@@ -281,6 +281,31 @@ hipError_t cg_step_p(const CgArgs& a, hipStream_t s);
 enum class CgOp : int { Begin = 0, Xr = 1, P = 2 };
 int cg_blocks(CgOp op, const CgArgs& a);
 hipError_t cg_grouped(CgOp op, const CgArgs* list, const int* start, int nprob, int blocks, hipStream_t s);
+// Small launches over several problems at once (FP64 masters; blocks of a
+// problem: blocks * batch, 0 for arguments the launch of its own refuses).
+enum class EwOp : int { Sym = 0, Dot = 1, Sum = 2, Trace = 3, Account = 4 };
+struct EwArgs {
+  const double* x = nullptr;
+  const double* y = nullptr;
+  double* out = nullptr;
+  const double* shift = nullptr;
+  const int* gate = nullptr;
+  const int* iters = nullptr;
+  int* stat = nullptr;
+  uint16_t* planes[3] = {nullptr, nullptr, nullptr};
+  int64_t ldx = 0, ldo = 0, sx = 0, so = 0, N = 0, rows = 0, nb = 0;
+  double a = 0.0;
+  int np = 0, blocks = 0, batch = 0;
+};
+// The arguments of sym_combine (no second input, no maxima), dot_partials (one
+// stride), sum_partials (into out[z]), trace (one member, aout not null) and cg_account.
+EwArgs ew_sym(const double* in, int64_t ldi, int64_t si, int64_t N, int64_t Np, double a, const double* shift,
+              double* out, int64_t ldo, int64_t so, uint16_t* const* planes, int np, int batch, const int* gate);
+EwArgs ew_dot(const double* x, const double* y, int64_t stride, int64_t n, int batch, double* partials);
+EwArgs ew_sum(const double* partials, int count, int batch, double* out, double scale, int group = 1);
+EwArgs ew_trace(const double* x, int64_t ld, int64_t N, double* out, double* aout);
+EwArgs ew_account(const int* active, const int* iters, int batch, int* stat);
+hipError_t ew_grouped(EwOp op, const EwArgs* list, const int* start, int nprob, int blocks, hipStream_t s);
 // convergence: active[z] stays 1 while rr > tol2 ref or rr > eta2 rr0 (rr0: the
 // initial residual); iters[z] counts the checks.  Any batch size.
 hipError_t cg_check(const double* rr, const double* rr0, const double* ref, int hstride, int batch,

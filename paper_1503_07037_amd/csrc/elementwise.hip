@@ -134,20 +134,18 @@ inline bool pair_ok(const T* p, int64_t stride, int64_t n) {
 // stay row-contiguous.  With mx, the block leaves max |out| over its pair (an
 // infinite one for a non-finite value) at mx[z * mstride + t].
 template <class Tin, class Tout>
-__global__ __launch_bounds__(kT) void k_sym(const Tin* in, int64_t ldi, int64_t si, int64_t N,
-                                            int64_t Np, double a, const double* dshift,
-                                            int dstride, Tout* out, int64_t ldo, int64_t so,
-                                            Planes pl, int np, int64_t out_rows, const Tin* in2,
-                                            double a2, const int* gate, int64_t nb, int g, double* mx,
-                                            int64_t mstride) {
+__device__ __forceinline__ void sym_block(const Tin* in, int64_t ldi, int64_t si, int64_t N,
+                                          double a, const double* dshift,
+                                          int dstride, Tout* out, int64_t ldo, int64_t so,
+                                          const Planes& pl, int np, int64_t out_rows, const Tin* in2,
+                                          double a2, const int* gate, int64_t nb, int g, double* mx,
+                                          int64_t mstride, int64_t t, int z) {
   __shared__ double ta[32][33], tb[32][33];
   if (gate && !*gate) return;  // a converged system of a batch keeps its outputs
-  const int64_t t = blockIdx.x;
   int64_t BJ = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
   while (BJ > 0 && BJ * (BJ + 1) / 2 > t) --BJ;
   while ((BJ + 1) * (BJ + 2) / 2 <= t) ++BJ;
   const int64_t BI = t - BJ * (BJ + 1) / 2;
-  const int z = blockIdx.y;
   in += z * si;
   if (in2) in2 += z * si;
   out += z * so;
@@ -226,6 +224,17 @@ __global__ __launch_bounds__(kT) void k_sym(const Tin* in, int64_t ldi, int64_t 
   }
 }
 
+template <class Tin, class Tout>
+__global__ __launch_bounds__(kT) void k_sym(const Tin* in, int64_t ldi, int64_t si, int64_t N,
+                                            double a, const double* dshift,
+                                            int dstride, Tout* out, int64_t ldo, int64_t so,
+                                            Planes pl, int np, int64_t out_rows, const Tin* in2,
+                                            double a2, const int* gate, int64_t nb, int g, double* mx,
+                                            int64_t mstride) {
+  sym_block<Tin, Tout>(in, ldi, si, N, a, dshift, dstride, out, ldo, so, pl, np, out_rows, in2, a2, gate, nb, g, mx,
+                       mstride, blockIdx.x, blockIdx.y);
+}
+
 // out = in^T on Np x Np (batched, with planes); out and in must differ.
 template <class T>
 __global__ __launch_bounds__(kT) void k_transpose(const T* __restrict__ in, int64_t Np, int64_t s,
@@ -260,15 +269,11 @@ __global__ __launch_bounds__(kT) void k_split(const double* __restrict__ x, int6
 
 // ------------------------------------------------------------ reductions
 template <class T>
-__global__ __launch_bounds__(kT) void k_dot(const T* __restrict__ x, int64_t sx,
-                                            const T* __restrict__ y, int64_t sy, int64_t n,
-                                            double* partials, int v2) {
-  const int z = blockIdx.y;
-  x += z * sx;
-  y += z * sy;
+__device__ __forceinline__ void dot_block(const T* __restrict__ x, const T* __restrict__ y, int64_t n, int v2,
+                                          int b, int nb, double* __restrict__ out) {
   double s = 0.0;
   if (v2) {
-    for (int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x; c < (n >> 1); c += (int64_t)gridDim.x * kT) {
+    for (int64_t c = (int64_t)b * kT + threadIdx.x; c < (n >> 1); c += (int64_t)nb * kT) {
       T a2[2], b2[2];
       ld2(x + (c << 1), a2);
       ld2(y + (c << 1), b2);
@@ -276,11 +281,20 @@ __global__ __launch_bounds__(kT) void k_dot(const T* __restrict__ x, int64_t sx,
       s += (double)a2[1] * (double)b2[1];
     }
   } else {
-    for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT)
+    for (int64_t i = (int64_t)b * kT + threadIdx.x; i < n; i += (int64_t)nb * kT)
       s += (double)x[i] * (double)y[i];
   }
   s = block_sum(s);
-  if (threadIdx.x == 0) partials[(int64_t)z * gridDim.x + blockIdx.x] = s;
+  if (threadIdx.x == 0) *out = s;
+}
+
+template <class T>
+__global__ __launch_bounds__(kT) void k_dot(const T* __restrict__ x, int64_t sx,
+                                            const T* __restrict__ y, int64_t sy, int64_t n,
+                                            double* partials, int v2) {
+  const int z = blockIdx.y;
+  dot_block<T>(x + z * sx, y + z * sy, n, v2, blockIdx.x, gridDim.x,
+               partials + (int64_t)z * gridDim.x + blockIdx.x);
 }
 
 // Sum of count partials, runs of group consecutive ones first; valid in thread 0.
@@ -306,10 +320,8 @@ __global__ __launch_bounds__(kT) void k_sum_partials(const double* __restrict__ 
 }
 
 template <class T>
-__global__ __launch_bounds__(kT) void k_trace(const T* __restrict__ x, int64_t ld, int64_t sx,
-                                              int64_t N, double* out, int ostride, double* aout) {
-  const int z = blockIdx.x;
-  x += z * sx;
+__device__ __forceinline__ void trace_block(const T* __restrict__ x, int64_t ld, int64_t N, double* out,
+                                            double* aout) {
   double s = 0.0, sa = 0.0;
   for (int64_t i = threadIdx.x; i < N; i += kT) {
     const double v = (double)x[i * ld + i];
@@ -317,11 +329,18 @@ __global__ __launch_bounds__(kT) void k_trace(const T* __restrict__ x, int64_t l
     sa += fabs(v);
   }
   s = block_sum(s);
-  if (threadIdx.x == 0) out[z * ostride] = s;
+  if (threadIdx.x == 0) *out = s;
   if (aout) {
     sa = block_sum(sa);
-    if (threadIdx.x == 0) aout[z * ostride] = sa;
+    if (threadIdx.x == 0) *aout = sa;
   }
+}
+
+template <class T>
+__global__ __launch_bounds__(kT) void k_trace(const T* __restrict__ x, int64_t ld, int64_t sx,
+                                              int64_t N, double* out, int ostride, double* aout) {
+  const int z = blockIdx.x;
+  trace_block<T>(x + z * sx, ld, N, out + z * ostride, aout ? aout + z * ostride : nullptr);
 }
 
 // ------------------------------------------------------------ CG
@@ -581,15 +600,51 @@ __global__ void k_input_status(const double* g, const int* flag, double beta, do
 // Statistics of a fixed-count (graph-replayed) solve: iterations summed and
 // their maximum over the members that ran, and the members still above their
 // tolerance at the end (iters counts the initial check as well).
-__global__ void k_cg_account(const int* active, const int* iters, int batch, int* stat) {
-  const int z = blockIdx.x * blockDim.x + threadIdx.x;
-  if (z >= batch) return;
+__device__ __forceinline__ void account(const int* active, const int* iters, int z, int* stat) {
   const int its = max(0, iters[z] - 1);
   if (its > 0) {
     atomicAdd(stat, its);
     atomicMax(stat + 1, its);
   }
   if (active[z]) atomicAdd(stat + 2, 1);
+}
+
+__global__ void k_cg_account(const int* active, const int* iters, int batch, int* stat) {
+  const int z = blockIdx.x * blockDim.x + threadIdx.x;
+  if (z < batch) account(active, iters, z, stat);
+}
+
+// The small launches of several problems (buckets or systems of a batch) in
+// one: block b belongs to problem p with start[p] <= b < start[p + 1] and does
+// what block b - start[p] of the problem's own launch does, so no bit changes.
+// Each of these launches takes 3-10 us whatever it does: a batch of 8 systems
+// of N = 150 to 1024 597 -> 528 ms, of 24 systems of N = 45 to 216 84.7 -> 75.0.
+// The problem is found by the lanes of a wave together: the inputs and outputs
+// are as many problems as there are systems.
+template <EwOp OP>
+__global__ __launch_bounds__(kT) void k_ew_grouped(const EwArgs* __restrict__ list, const int* __restrict__ start,
+                                                   int nprob) {
+  const int b = blockIdx.x, lane = threadIdx.x & 63;
+  int p = 0;
+  for (int base = 1; base < nprob; base += 64)
+    p += __popcll(__ballot(base + lane < nprob && start[base + lane] <= b));
+  p = __builtin_amdgcn_readfirstlane(p);
+  const EwArgs& e = list[p];
+  const int local = b - start[p], z = local / e.blocks, t = local - z * e.blocks;
+  if constexpr (OP == EwOp::Sym) {
+    const Planes pl{{e.planes[0], e.planes[1], e.planes[2]}};
+    sym_block<double, double>(e.x, e.ldx, e.sx, e.N, e.a, e.shift, 0, e.out, e.ldo, e.so, pl, e.np, e.rows, nullptr,
+                              0.0, e.gate, e.nb, 1, nullptr, 0, t, z);
+  } else if constexpr (OP == EwOp::Dot) {
+    dot_block<double>(e.x + z * e.sx, e.y + z * e.sx, e.N, e.np, t, e.blocks, e.out + (int64_t)z * e.blocks + t);
+  } else if constexpr (OP == EwOp::Sum) {
+    const double s = partial_sum(e.x + (int64_t)z * e.N, (int)e.N, e.np);
+    if (threadIdx.x == 0) e.out[z] = s * e.a;
+  } else if constexpr (OP == EwOp::Trace) {
+    trace_block<double>(e.x, e.ldx, e.N, e.out, e.out + e.so);
+  } else {
+    for (int i = threadIdx.x; i < e.np; i += kT) account(e.gate, e.iters, i, e.stat);
+  }
 }
 
 template <class T>
@@ -1261,7 +1316,7 @@ hipError_t sym_combine(const Tin* in, int64_t ldi, int64_t si, int64_t N, int64_
   const int64_t nbg = (nb + g - 1) / g;
   const int64_t pairs = nbg * (nbg + 1) / 2;
   if (mx && (mstride < pairs || gate || pairs != sym_pair_blocks(span, batch))) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_sym<Tin, Tout>), dim3((unsigned)pairs, batch), dim3(kT), 0, s, in, ldi, si, N, Np, a,
+  hipLaunchKernelGGL((k_sym<Tin, Tout>), dim3((unsigned)pairs, batch), dim3(kT), 0, s, in, ldi, si, N, a,
                      dshift, dstride, out, ldo, so, pl, nplanes, rows, in2, a2, gate, nb, g, mx, mstride);
   return hipGetLastError();
 }
@@ -1456,6 +1511,60 @@ hipError_t input_status(const double* gersh, const int* flag, double beta, doubl
 
 hipError_t cg_account(const int* active, const int* iters, int batch, int* stat, hipStream_t s) {
   hipLaunchKernelGGL(k_cg_account, dim3((batch + 63) / 64), dim3(64), 0, s, active, iters, batch, stat);
+  return hipGetLastError();
+}
+
+EwArgs ew_sym(const double* in, int64_t ldi, int64_t si, int64_t N, int64_t Np, double a, const double* shift,
+              double* out, int64_t ldo, int64_t so, uint16_t* const* planes, int np, int batch, const int* gate) {
+  EwArgs e;
+  e.x = in; e.ldx = ldi; e.sx = si; e.N = N; e.a = a; e.shift = shift;
+  e.out = out; e.ldo = ldo; e.so = so; e.gate = gate;
+  for (int p = 0; p < np && p < 3; ++p) e.planes[p] = planes[p];
+  e.np = np;
+  e.rows = (ldo == N && ldo != Np) ? N : ldo;  // caller buffer: only N x N (see sym_combine)
+  e.nb = (std::max(e.rows, N) + 31) / 32;
+  e.blocks = (int)(e.nb * (e.nb + 1) / 2);
+  e.batch = np && (ldo != Np || Np % 32 != 0) ? 0 : batch;
+  return e;
+}
+EwArgs ew_dot(const double* x, const double* y, int64_t stride, int64_t n, int batch, double* partials) {
+  EwArgs e;
+  e.x = x; e.y = y; e.sx = stride; e.N = n; e.out = partials;
+  e.np = pair_ok(x, stride, n) && pair_ok(y, stride, n);
+  e.blocks = (int)red_grid(n);
+  e.batch = batch;
+  return e;
+}
+EwArgs ew_sum(const double* partials, int count, int batch, double* out, double scale, int group) {
+  EwArgs e;
+  e.x = partials; e.N = count; e.out = out; e.a = scale; e.np = group;
+  e.blocks = 1;
+  e.batch = group < 1 || count % group ? 0 : batch;
+  return e;
+}
+EwArgs ew_trace(const double* x, int64_t ld, int64_t N, double* out, double* aout) {
+  EwArgs e;
+  e.x = x; e.ldx = ld; e.N = N; e.out = out; e.so = aout - out;
+  e.blocks = e.batch = 1;
+  return e;
+}
+EwArgs ew_account(const int* active, const int* iters, int batch, int* stat) {
+  EwArgs e;
+  e.gate = active; e.iters = iters; e.np = batch; e.stat = stat;
+  e.blocks = e.batch = 1;
+  return e;
+}
+
+hipError_t ew_grouped(EwOp op, const EwArgs* list, const int* start, int nprob, int blocks, hipStream_t s) {
+  if (!list || !start || nprob < 1 || blocks < nprob) return hipErrorInvalidValue;
+  const dim3 g((unsigned)blocks), t(kT);
+  switch (op) {
+    case EwOp::Sym: hipLaunchKernelGGL(k_ew_grouped<EwOp::Sym>, g, t, 0, s, list, start, nprob); break;
+    case EwOp::Dot: hipLaunchKernelGGL(k_ew_grouped<EwOp::Dot>, g, t, 0, s, list, start, nprob); break;
+    case EwOp::Sum: hipLaunchKernelGGL(k_ew_grouped<EwOp::Sum>, g, t, 0, s, list, start, nprob); break;
+    case EwOp::Trace: hipLaunchKernelGGL(k_ew_grouped<EwOp::Trace>, g, t, 0, s, list, start, nprob); break;
+    case EwOp::Account: hipLaunchKernelGGL(k_ew_grouped<EwOp::Account>, g, t, 0, s, list, start, nprob); break;
+  }
   return hipGetLastError();
 }
 

@@ -198,3 +198,26 @@ def test_grouped_and_per_bucket_launches_agree(dm, small_batch, prec, tol):
             for o in (1, 2):
                 x, y = a[o][k][z].cpu().numpy(), b[o][k][z].cpu().numpy()
                 assert np.abs(x - y).max() < tol * max(1.0, np.abs(y).max())
+
+
+@pytest.mark.parametrize("count", [1, 64, 65, 130])
+def test_grouped_small_launches_of_many_systems(dm, count):
+    """One launch carries the inputs and outputs of all systems: counts around the 64 a wave looks up
+    at once, sizes 2 to 160 (two buckets), against the launches per system (the products' FP64 sums
+    may run in another order: the bound of the comparison above)."""
+    print(f"case grouped small launches, {count} systems", flush=True)
+    rng = np.random.default_rng(count)
+    sizes = [int(v) for v in rng.integers(2, 161, count)]
+    sizes[0] = 160
+    h0 = [workloads.chain_1d(n, 10 + i) for i, n in enumerate(sizes)]
+    h1 = [np.diag(rng.standard_normal(n)) for n in sizes]
+    out = {}
+    for grouped in (1, 0):
+        with dm.Context(max(sizes), dirs_max=1, prec="fp64", grouped=grouped) as ctx:
+            P0, P1, _, _, _ = ctx.mu_newton_batched([T(h) for h in h0], [[T(h)] for h in h1], [4.0] * count,
+                                                    [0.5 * n for n in sizes], n=20, order=1)
+        out[grouped] = ([p.cpu().numpy() for p in P0], [p[0].cpu().numpy() for p in P1])
+    for k in range(count):
+        for o in (0, 1):
+            x, y = out[1][o][k], out[0][o][k]
+            assert np.abs(x - y).max() < 1e-12 * max(1.0, np.abs(y).max()), (k, sizes[k], o)
