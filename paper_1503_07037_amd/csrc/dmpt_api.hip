@@ -3645,6 +3645,8 @@ dmpt_status dmpt_init(dmpt_ctx* out, int device, int64_t n_max, int dirs_max, co
       const int64_t cap = std::max<int64_t>((c->np_max / 128) * (c->np_max / 128), 16384);
       double* mx = (double*)alloc(sizeof(double) * (size_t)cap * count);
       if (!g.q8 || !g.qs || !g.zm || !mx) return false;
+      // nothing is known of the slices yet
+      if (hipMemsetAsync(g.zm, 0xff, nn / 1024 * count, c->stream) != hipSuccess) return false;
       Q8Reg r;
       r.m = (const char*)g.m;
       r.stride = (int64_t)nn;

@@ -51,7 +51,9 @@ inline int engine_terms(Engine e) {
 // half l / 32), so a wave moves a slice block as 64 consecutive 16-byte
 // pieces.  A member takes 4 Np^2 bytes; its q sits in a separate FP64 array.
 // Beside the slices: one byte per 32 x 32 block (row / 32) * (Np / 32) + col / 32
-// with bit s set when digit s of any element of the block is not zero.
+// with bit s set when digit s of any element of the block is not zero; a slice
+// block whose bit is clear holds zeros (a member's blocks and masks start at the
+// same index, whatever its Np or stride; all bits set: contents unknown).
 constexpr int kQ8Slices = 4;
 constexpr double kQ8Base = 254.0;
 __host__ __device__ inline int64_t q8_off(int64_t row, int64_t col, int64_t Np, int s) {

@@ -1141,8 +1141,10 @@ __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int6
     const int64_t blk = g * (kT / 64) + wave;
     const bool live = blk < nblk;
     const int64_t rb = live ? blk / kbr : 0, cb = live ? blk - rb * kbr : 0;
+    uint32_t was = 0;
     if (live) {
       const double* base = xm + rb * 32 * Np + cb * 32;
+      was = zm[(int64_t)z * szm + blk];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int r = i * 4 + (l >> 4), c = (l & 15) * 2;
@@ -1157,12 +1159,15 @@ __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int6
       int d[kQ8Slices][16];
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        double r = t[row][c0 + e] * inv;
+        // the value to split is a f; the remainders are fused explicitly, so the
+        // digits do not depend on what the compiler contracts
+        double a = t[row][c0 + e], f = inv;
 #pragma unroll
         for (int sl = 0; sl < kQ8Slices; ++sl) {
-          const double q = rint(r);
+          const double q = rint(a * f);
           d[sl][e] = (int)q;
-          r = (r - q) * kQ8Base;
+          a = __builtin_fma(a, f, -q);
+          f = kQ8Base;
         }
       }
       uint32_t digits = 0;  // the digits any lane of the block has
@@ -1172,8 +1177,11 @@ __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int6
 #pragma unroll
         for (int q = 0; q < 4; ++q) w[q] = pack4(&d[sl][4 * q]);
         uint32_t* dst = (uint32_t*)(qm + ((blk * kQ8Slices + sl) << 10) + l * 16);
-        *(uint4*)dst = make_uint4(w[0], w[1], w[2], w[3]);
-        digits |= (__ballot((w[0] | w[1] | w[2] | w[3]) != 0) != 0 ? 1u : 0u) << sl;
+        const bool any = __ballot((w[0] | w[1] | w[2] | w[3]) != 0) != 0;
+        // a slice block that held zeros and stays zero is not written again:
+        // the slicing is bound by its bytes (Np = 4096, banded: 53 -> 46 us)
+        if (any || (was >> sl & 1)) *(uint4*)dst = make_uint4(w[0], w[1], w[2], w[3]);
+        digits |= (any ? 1u : 0u) << sl;
       }
       if (l == 0) zm[(int64_t)z * szm + blk] = (uint8_t)digits;
     }

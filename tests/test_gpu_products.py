@@ -130,3 +130,23 @@ def test_int8_zero_digit_blocks(dm, monkeypatch, prec):
                     ctx.set_variant(N, v)
                     out.append(ctx.fermi_recursion(T(h0), beta, mu, n)[0].cpu().numpy())
             assert np.array_equal(out[0], out[2]) and np.array_equal(out[1], out[3]), name
+
+
+@pytest.mark.parametrize("solver", ["ns", "cg"])
+def test_int8_slices_of_earlier_calls(dm, solver):
+    """The slicing writes no zeros over zeros: after calls with denser, emptier, smaller and larger
+    matrices a context gives bit for bit what a fresh one gives."""
+    rng = np.random.default_rng(4)
+    a = 0.02 * rng.standard_normal((640, 640))
+    dense, chain, eye = a + a.T, workloads.chain_1d(640, 3), 0.3 * np.eye(640)
+    mats = [dense, eye, chain, dense[:130, :130], chain, eye[:400, :400], dense[:400, :400], eye]
+    opts = dict(dirs_max=0, prec="int8x13", solver=solver, tol_cg=1e-6)
+
+    def solve(ctx, h0):
+        return ctx.fermi_recursion(T(h0), 8.0, 0.07, 12)[0].cpu().numpy()
+
+    with dm.Context(640, **opts) as used:
+        for k, h0 in enumerate(mats):
+            print(f"case int8 slices of earlier calls {solver} {k} N={h0.shape[0]}", flush=True)
+            with dm.Context(640, **opts) as fresh:
+                assert np.array_equal(solve(used, h0), solve(fresh, h0)), k
