@@ -34,7 +34,9 @@ is timed on the same workload after the timed region (one solve;
 the dominant kernel: 2 N^3 flops per logical matrix product (every split
 product of the same logical product counts once) over the kernel's device
 time; the executed matrix-core rate (every split product counted) is
-reported beside it as mfma_executed and mfma_util.
+reported beside it as mfma_executed and mfma_util, except for the int8
+kernels: they leave out the products of digit blocks that are zero, whose
+number only the device knows (null).
 
 Other modes: --copy-calibration only runs a
 plain device copy of known size, the reference that scales the FETCH_SIZE /
@@ -463,7 +465,9 @@ def main():
     pe = prof["engines"][dom]
     avg_ms = pe["ms"] / max(pe["launches"], 1)
     achieved = pe["useful_flops"] / max(pe["ms"], 1e-12) / 1e9   # algorithmic TFLOP/s
-    executed = pe["mfma_flops"] / max(pe["ms"], 1e-12) / 1e9     # every split product counted
+    # every split product counted; unknown for int8, whose kernels leave out zero digit blocks
+    executed = None if dom.startswith("int8") else pe["mfma_flops"] / max(pe["ms"], 1e-12) / 1e9
+    int8_ran = any(v["launches"] for e, v in prof["engines"].items() if e.startswith("int8"))
     peak = PEAKS_TFLOPS[dom]
     name = args.workload if not args.n else None
     acc = accuracy(name, P0, P1, P2, mu, st) if name else None
@@ -488,8 +492,10 @@ def main():
                      "frac": achieved / peak,
                      "achieved_measure": "algorithmic: 2 N^3 per logical product and member over "
                                          "the kernel's device time; peak is the dense matrix-core "
-                                         f"rate of the kernel's own type ({DTYPE[dom]})",
-                     "mfma_executed": executed, "mfma_util": executed / peak,
+                                         f"rate of the kernel's own type ({DTYPE[dom]})"
+                                         + ("; the products of digit blocks that are zero add nothing and "
+                                            "are left out, but count here" if executed is None else ""),
+                     "mfma_executed": executed, "mfma_util": None if executed is None else executed / peak,
                      "algorithmic_flops_per_launch": pe["useful_flops"] / max(pe["launches"], 1),
                      "traffic": traffic["bytes_per_launch"] if traffic else None,
                      "traffic_unit": "bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-scaled)",
@@ -498,10 +504,11 @@ def main():
                      "avg_launch_ms": avg_ms,
                      "product_time_share": prof["ms"] / ms_step / args.steps,
                      "engines": {e: {"launches": v["launches"], "ms": v["ms"],
-                                     "mfma_tflops": v["mfma_flops"] / max(v["ms"], 1e-12) / 1e9,
+                                     "mfma_tflops": None if e.startswith("int8")
+                                     else v["mfma_flops"] / max(v["ms"], 1e-12) / 1e9,
                                      "algorithmic_tflops": v["useful_flops"] / max(v["ms"], 1e-12) / 1e9}
                                  for e, v in prof["engines"].items() if v["launches"]}},
-        "mfma_tflops_whole_step": st["mfma_flops"] / (ms_step / 1e3) / 1e12,
+        "mfma_tflops_whole_step": None if int8_ran else st["mfma_flops"] / (ms_step / 1e3) / 1e12,
         "useful_tflops_whole_step": st["useful_flops"] / (ms_step / 1e3) / 1e12,
         "newton_iters": st["newton_iters"], "cg_iters_total": st["cg_iters_total"],
         "step_seconds": [b - a for a, b in zip([0.0] + marks[:-1], marks)],

@@ -414,7 +414,8 @@ __device__ __forceinline__ void f64_store_partial(double* s, int ks, int qm, int
 }
 
 // Direct form for products that leave most of the chip idle with 128 x 128
-// tiles (see small_edge): TM x TM output tile per workgroup (TM 32 or 64), KS
+// tiles (see small_edge): TM x TM output tile per workgroup (used with TM = 32;
+// from 64 on the operands are staged through LDS, gemm_f64_lds64_tile), KS
 // waves per 32 x 32 quadrant that take the 16-wide k chunks in turn, so even
 // an Np = 128 product runs on 16 CUs with a serial chain of one or two chunks
 // instead of 16 LDS stages on one CU.  Each lane loads four consecutive k of a
