@@ -49,6 +49,16 @@ __device__ inline int find_block(const BSView& m, int i, int j) {
   return -1;
 }
 
+// The same for a whole wave with one (i, j): the lanes compare side by side.
+__device__ inline int find_block_wave(const BSView& m, int i, int j) {
+  const int lane = threadIdx.x & 63, end = m.rows[i + 1];
+  for (int base = m.rows[i]; base < end; base += 64) {
+    const unsigned long long hit = __ballot(base + lane < end && m.cols[base + lane] == j);
+    if (hit) return base + __ffsll((long long)hit) - 1;
+  }
+  return -1;
+}
+
 // ------------------------------------------------------------------ symbolic
 // Block row i: bit j of bits[i * words + j / 32] is set when block (i, j) of C
 // can be non-zero; counts[i] = number of set bits.  One workgroup per block
@@ -62,10 +72,10 @@ __global__ __launch_bounds__(kT) void k_symbolic(BSExpr e, int nb, int words, ui
     const BSView& A = e.A[t];
     const BSView& B = e.B[t];
     const int a0 = A.rows[i], a1 = A.rows[i + 1];
-    // (k slot, j slot) pairs spread over the threads
-    for (int as = a0; as < a1; ++as) {
+    // a k slot per wave, its j slots over the lanes
+    for (int as = a0 + (int)(threadIdx.x >> 6); as < a1; as += kT / 64) {
       const int k = A.cols[as];
-      for (int bs = B.rows[k] + (int)threadIdx.x; bs < B.rows[k + 1]; bs += kT) {
+      for (int bs = B.rows[k] + (int)(threadIdx.x & 63); bs < B.rows[k + 1]; bs += 64) {
         const int j = B.cols[bs];
         atomicOr(&row[j >> 5], 1u << (j & 31));
       }
@@ -164,21 +174,35 @@ __global__ __launch_bounds__(kT) void k_fill(const uint32_t* bits, int words, co
 }
 
 // ------------------------------------------------------------------ numeric
-// One wave per candidate block s of C: the block products of every term over
-// the common inner blocks (FP64 MFMA, 2 x 2 tiles of 16 x 16, k in steps of
+// Candidate block s of C, by one wave or, with SPLIT, by the four waves of a
+// workgroup (one 16 x 16 tile each, the same sums): the block products of every
+// term over the common inner blocks (FP64 MFMA, 16 x 16 tiles, k in steps of
 // 4), the addends and the diagonal; bmax[s] = max |C_s|, nprods[s] = block
 // products formed.  Block products read their operand blocks straight from
-// global memory (each is 8 KB contiguous).  The searches for the blocks of B
-// run side by side, one inner block per lane (one after the other each is a
-// chain of five dependent loads).
+// global memory (each is 8 KB contiguous).  A block is a chain of dependent
+// loads and MFMAs, so the searches for the blocks of B run side by side, one
+// inner block per lane (one after the other each is a chain of five loads),
+// and the addends are found first and all loaded before the first store (a
+// load behind a store that may alias waits for it, a memory latency per element).
+template <bool SPLIT>
 __device__ inline void numeric_block(const BSExpr& e, const BSView& Cv, int s, double* bmax, double* nprods) {
-  const int lane = threadIdx.x & 63;
+  constexpr int NT = SPLIT ? 1 : 2;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int a0 = SPLIT ? wave >> 1 : 0, b0 = SPLIT ? wave & 1 : 0;
   const int i = Cv.ridx[s], j = Cv.cols[s];
-  d4v acc[2][2];
+  int cslot[2] = {-1, -1};
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int t = 0; t < 2; ++t)
+    if (t < e.nadd) cslot[t] = find_block_wave(e.C[t], i, j);
+  // v_mfma_f64_16x16x4f64 result: register r of lane l holds row 4r + l/16, column l%16
+  auto at = [&](int a, int b, int r) {
+    return ((a0 + a) * 16 + 4 * r + (lane >> 4)) * kB + (b0 + b) * 16 + (lane & 15);
+  };
+  d4v acc[NT][NT];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = (d4v){0.0, 0.0, 0.0, 0.0};
+  for (int a = 0; a < NT; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) acc[a][b] = (d4v){0.0, 0.0, 0.0, 0.0};
   int nprod = 0;
   for (int t = 0; t < e.nterm; ++t) {
     const BSView& A = e.A[t];
@@ -193,49 +217,70 @@ __device__ inline void numeric_block(const BSExpr& e, const BSView& Cv, int s, d
         const int l = __ffsll((long long)found) - 1;
         found &= found - 1;
         const int as = base + l, bs = __builtin_amdgcn_readlane(mine, l);
-        const double* Ab = A.val + (int64_t)as * kBB;
-        const double* Bb = B.val + (int64_t)bs * kBB;
+        // A operand: lane l holds row (l % 16) and inner index kk + l / 16;
+        // B operand: inner index kk + l / 16 and column (l % 16)
+        const double* Ab = A.val + (int64_t)as * kBB + (a0 * 16 + (lane & 15)) * kB + (lane >> 4);
+        const double* Bb = B.val + (int64_t)bs * kBB + (lane >> 4) * kB + b0 * 16 + (lane & 15);
 #pragma unroll
         for (int kk = 0; kk < kB; kk += 4) {
-          double av[2], bv[2];
-          // A operand: lane l holds row (l % 16) and inner index kk + l / 16
+          double av[NT], bv[NT];
 #pragma unroll
-          for (int a = 0; a < 2; ++a) av[a] = alpha * Ab[(a * 16 + (lane & 15)) * kB + kk + (lane >> 4)];
-          // B operand: lane l holds inner index kk + l / 16 and column (l % 16)
+          for (int a = 0; a < NT; ++a) av[a] = alpha * Ab[a * 16 * kB + kk];
 #pragma unroll
-          for (int b = 0; b < 2; ++b) bv[b] = Bb[(kk + (lane >> 4)) * kB + b * 16 + (lane & 15)];
+          for (int b = 0; b < NT; ++b) bv[b] = Bb[kk * kB + b * 16];
 #pragma unroll
-          for (int a = 0; a < 2; ++a)
+          for (int a = 0; a < NT; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < NT; ++b)
               acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
         }
       }
     }
   }
   // addends, diagonal, output and the block's largest element
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (t >= e.nadd || cslot[t] < 0) continue;
+    const double* Cs = e.C[t].val + (int64_t)cslot[t] * kBB;
+    const double beta = e.beta[t];
+    double x[NT][NT][4];
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+      for (int b = 0; b < NT; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[a][b][r] = Cs[at(a, b, r)];
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+      for (int b = 0; b < NT; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[a][b][r] = __builtin_fma(beta, x[a][b][r], acc[a][b][r]);
+  }
   double* Cb = Cv.val + (int64_t)s * kBB;
-  int cslot[2] = {-1, -1};
-  for (int t = 0; t < e.nadd; ++t) cslot[t] = find_block(e.C[t], i, j);
   double mx = 0.0;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NT; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NT; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        // v_mfma_f64_16x16x4f64 result: register r of lane l holds row 4r + l/16, column l%16
-        const int row = a * 16 + 4 * r + (lane >> 4), col = b * 16 + (lane & 15);
+        const int row = (a0 + a) * 16 + 4 * r + (lane >> 4), col = (b0 + b) * 16 + (lane & 15);
         double v = acc[a][b][r];
-        for (int t = 0; t < e.nadd; ++t)
-          if (cslot[t] >= 0) v += e.beta[t] * e.C[t].val[(int64_t)cslot[t] * kBB + row * kB + col];
         if (i == j && row == col && (int64_t)i * kB + row < e.n) v += e.diag;
         Cb[row * kB + col] = v;
         mx = fmax(mx, fabs(v));
       }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-  if (lane == 0) {
+  if constexpr (SPLIT) {
+    __shared__ double red[kT / 64];
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kT / 64; ++q) mx = fmax(mx, red[q]);
+  }
+  if (lane == 0 && (!SPLIT || wave == 0)) {
     bmax[s] = mx;
     nprods[s] = (double)nprod;
   }
@@ -244,15 +289,22 @@ __device__ inline void numeric_block(const BSExpr& e, const BSView& Cv, int s, d
 __global__ __launch_bounds__(kT) void k_numeric(BSExpr e, BSView Cv, int nslots, double* bmax,
                                                 double* nprods) {
   const int s = __builtin_amdgcn_readfirstlane(blockIdx.x * (kT / 64) + (threadIdx.x >> 6));
-  if (s < nslots) numeric_block(e, Cv, s, bmax, nprods);
+  if (s < nslots) numeric_block<false>(e, Cv, s, bmax, nprods);
 }
 
-// The same with the number of candidates on the device (Cv.rows[nb]).
+// The same with the number of candidates on the device (Cv.rows[nb]): a
+// workgroup per candidate while they all fit the launch (up to 1024, the four
+// SIMDs of every CU four times), else a wave per candidate, in turn (N = 2048:
+// 12.5 -> 10.5 us per launch on average).
 __global__ __launch_bounds__(kT) void k_numeric_dev(BSExpr e, BSView Cv, int nb, double* bmax, double* nprods) {
   const int n = Cv.rows[nb];
+  if (n <= (int)gridDim.x) {
+    if ((int)blockIdx.x < n) numeric_block<true>(e, Cv, blockIdx.x, bmax, nprods);
+    return;
+  }
   for (int s = __builtin_amdgcn_readfirstlane(blockIdx.x * (kT / 64) + (threadIdx.x >> 6)); s < n;
        s += gridDim.x * (kT / 64))
-    numeric_block(e, Cv, s, bmax, nprods);
+    numeric_block<false>(e, Cv, s, bmax, nprods);
 }
 
 // Largest of n values into out[0] (one workgroup, n = 0 gives 0).
@@ -311,7 +363,7 @@ __global__ __launch_bounds__(kT) void k_compact(BSView src, const int* keep, int
 // nor copies them, and the scans and reductions move into the kernels that
 // use them (4 launches instead of 10, 3 copies and 2 synchronisations).  The
 // evaluations are bound by that chain, not by their products: N = 2048, 64
-// block rows, one direction to second order 105 -> 33 ms, same bits.  The rows
+// block rows, one direction to second order 105 -> 30 ms, same bits.  The rows
 // end at one candidate per thread (kFusedRows); above, every block would read
 // the maxima of more than 65536 blocks.
 
@@ -630,8 +682,7 @@ hipError_t sparse_eval(const BSExpr& e, int nb, int cap, double tau, uint32_t* b
   hipLaunchKernelGGL(k_symbolic, dim3(nb), dim3(kT), (size_t)words * sizeof(uint32_t), s, e, nb, words, bits, counts);
   hipLaunchKernelGGL(k_scan_fill, dim3(nb), dim3(kT), 0, s, bits, words, counts, nb, cap, tmp.rows, tmp.cols, tmp.ridx,
                      need);
-  // a candidate per wave for up to 4096, the rest in turn
-  const int blocks = (int)std::min<int64_t>(((int64_t)cap + kT / 64 - 1) / (kT / 64), 1024);
+  const int blocks = std::min(cap, 1024);
   hipLaunchKernelGGL(k_numeric_dev, dim3(blocks), dim3(kT), 0, s, e, tmp, nb, bmax, nprods);
   hipLaunchKernelGGL(k_keep_compact, dim3(nb), dim3(kT), 0, s, tmp, bmax, nprods, nb, tau, out, prods);
   return hipGetLastError();
