@@ -420,11 +420,13 @@ dmpt_status dmpt_bench_product(dmpt_ctx ctx, int64_t N, dmpt_prec prec, int vari
 
 /* Product-kernel autotuner: times every variant of the context's engines
  * (its precision's, and the 6-product refinement's when enabled) at the
- * padded size of N and keeps the fastest for all later products of that
+ * padded size of N, on full and symmetric products (int8: of a dense and of
+ * a decaying matrix), and keeps the fastest for all later products of that
  * padded size on this context.  When the environment variable
  * DMPT_TUNE_CACHE names a file, choices are read from it (per GPU
- * architecture, engine and padded size) and new ones appended, so later
- * processes skip the timing.  *variant (may be NULL) receives the choice for
+ * architecture, version of the kernels, engine and padded size; lines of
+ * other versions are ignored) and new ones appended, so later processes skip
+ * the timing.  *variant (may be NULL) receives the choice for
  * the context's precision. */
 dmpt_status dmpt_autotune(dmpt_ctx ctx, int64_t N, int* variant);
 

@@ -3813,6 +3813,68 @@ dmpt_status dmpt_congruence(dmpt_ctx c, int64_t N, const double* Z, const double
   return DMPT_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Mean device time (ms) of `reps` products with one kernel variant on workspace
+// matrices filled with a hashed pattern (times exp(-decay |i - j|)): C = X Y^T,
+// or the square C = X X^T as a product marked symmetric.
+dmpt_status time_product(dmpt_ctx c, int64_t N, Engine eng, int variant, int reps, double decay, bool square,
+                         double* ms) {
+  Call k = make_call(c, N, false);
+  k.eng = eng;
+  k.np = engine_planes(k.eng);
+  hipStream_t s = c->stream;
+  uint16_t* px[3];
+  uint16_t* py[3];
+  planes_of(k, c->ws.D0, 0, px);
+  planes_of(k, c->ws.S0, 0, py);
+  HIPCHK(c, fill_pattern<double>((double*)mptr(k, c->ws.D0, 0), k.nn, 1u, px, k.np, s, k.Np, decay));
+  HIPCHK(c, fill_pattern<double>((double*)mptr(k, c->ws.S0, 0), k.nn, 2u, py, k.np, s, k.Np, decay));
+  GemmArgs a{};
+  a.eng = k.eng;
+  a.Np = k.Np;
+  a.Ne = k.Np;
+  a.batch = 1;
+  a.X = op(k, c->ws.D0, 0, false);
+  a.Y = op(k, square ? c->ws.D0 : c->ws.S0, 0, false);
+  a.C = mptr(k, c->ws.R, 0);
+  a.alpha = 1.0;
+  a.partials = c->d_part;
+  a.acc64 = acc64_of(c, k.eng);
+  a.variant = variant;
+  a.sym = square && !c->full_tiles ? 1 : 0;
+  if (engine_int8(k.eng)) {
+    if (k.Np > kQ8MaxK) return fail(c, DMPT_ERR_UNSUPPORTED, "int8 products need N <= 32768");
+    STCHK(q8_operand(k, a.X, 1));
+    STCHK(q8_operand(k, a.Y, 1));
+    if (a.sym && c->d_dpart) {
+      a.dpart = c->d_dpart;
+      a.dsplit = c->diag_split;
+      a.dpart_members = c->dpart_members;
+    }
+  }
+  hipEvent_t e0, e1;
+  HIPCHK(c, hipEventCreate(&e0));
+  HIPCHK(c, hipEventCreate(&e1));
+  HIPCHK(c, gemm(a, s));  // warm-up
+  HIPCHK(c, hipEventRecord(e0, s));
+  for (int r = 0; r < reps; ++r) HIPCHK(c, gemm(a, s));
+  HIPCHK(c, hipEventRecord(e1, s));
+  HIPCHK(c, hipEventSynchronize(e1));
+  float t = 0.f;
+  HIPCHK(c, hipEventElapsedTime(&t, e0, e1));
+  (void)hipEventDestroy(e0);
+  (void)hipEventDestroy(e1);
+  *ms = t / reps;
+  return DMPT_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 dmpt_status dmpt_bench_product(dmpt_ctx c, int64_t N, dmpt_prec prec, int variant, int reps, double* ms,
                                double* tflops) {
   if (!c || !ms) return DMPT_ERR_ARG;
@@ -3829,48 +3891,9 @@ dmpt_status dmpt_bench_product(dmpt_ctx c, int64_t N, dmpt_prec prec, int varian
     return fail(c, DMPT_ERR_NOMEM, "precision needs a different workspace than the context holds");
   if (hipSetDevice(c->device) != hipSuccess) return fail(c, DMPT_ERR_HIP, "hipSetDevice failed");
   ENTER(c);
-  Call k = make_call(c, N, false);
-  k.eng = eng;
-  k.np = engine_planes(k.eng);
-  hipStream_t s = c->stream;
-  uint16_t* px[3];
-  uint16_t* py[3];
-  planes_of(k, c->ws.D0, 0, px);
-  planes_of(k, c->ws.S0, 0, py);
-  HIPCHK(c, fill_pattern<double>((double*)mptr(k, c->ws.D0, 0), k.nn, 1u, px, k.np, s));
-  HIPCHK(c, fill_pattern<double>((double*)mptr(k, c->ws.S0, 0), k.nn, 2u, py, k.np, s));
-  GemmArgs a{};
-  a.eng = k.eng;
-  a.Np = k.Np;
-  a.Ne = k.Np;
-  a.batch = 1;
-  a.X = op(k, c->ws.D0, 0, false);
-  a.Y = op(k, c->ws.S0, 0, false);
-  a.C = mptr(k, c->ws.R, 0);
-  a.alpha = 1.0;
-  a.partials = c->d_part;
-  a.acc64 = acc64_of(c, k.eng);
-  a.variant = variant;
-  if (engine_int8(k.eng)) {
-    if (k.Np > kQ8MaxK) return fail(c, DMPT_ERR_UNSUPPORTED, "int8 products need N <= 32768");
-    STCHK(q8_operand(k, a.X, 1));
-    STCHK(q8_operand(k, a.Y, 1));
-  }
-  hipEvent_t e0, e1;
-  HIPCHK(c, hipEventCreate(&e0));
-  HIPCHK(c, hipEventCreate(&e1));
-  HIPCHK(c, gemm(a, s));  // warm-up (and LDS attribute)
-  HIPCHK(c, hipEventRecord(e0, s));
-  for (int r = 0; r < reps; ++r) HIPCHK(c, gemm(a, s));
-  HIPCHK(c, hipEventRecord(e1, s));
-  HIPCHK(c, hipEventSynchronize(e1));
-  float t = 0.f;
-  HIPCHK(c, hipEventElapsedTime(&t, e0, e1));
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  *ms = t / reps;
-  if (tflops)
-    *tflops = 2.0 * (double)k.Np * k.Np * k.Np * engine_terms(k.eng) / (*ms * 1e-3) / 1e12;
+  STCHK(time_product(c, N, eng, variant, reps, 0.0, false, ms));
+  const double Np = (double)padded(N);
+  if (tflops) *tflops = 2.0 * Np * Np * Np * engine_terms(eng) / (*ms * 1e-3) / 1e12;
   return DMPT_OK;
 }
 
@@ -3893,20 +3916,13 @@ bool is_tuned(dmpt_ctx c, Engine eng, int64_t Np) {
   return false;
 }
 
-dmpt_prec prec_of(Engine e) {
-  switch (e) {
-    case Engine::F64: return DMPT_FP64;
-    case Engine::F32: return DMPT_FP32;
-    case Engine::BF16S2: return DMPT_BF16X3;
-    case Engine::BF16S3: return DMPT_BF16X6;
-    case Engine::I8S4: return DMPT_INT8X13;
-    case Engine::I8S3: return DMPT_INT8X6;
-  }
-  return DMPT_FP64;
-}
+// Version of the kernels behind the variant numbers and of the products they are
+// timed on, part of a cache line's first field: lines of another version hold
+// choices between other kernels and are not read.
+constexpr int kTuneSet = 2;
 
-// Variant from the tuning cache file (DMPT_TUNE_CACHE: lines "arch engine Np acc64 variant ms"),
-// or -1.
+// Variant from the tuning cache file (DMPT_TUNE_CACHE: lines "arch/version engine Np acc64
+// variant ms"), or -1.
 int cache_lookup(const char* path, const std::string& arch, Engine eng, int64_t Np, int acc64) {
   FILE* f = std::fopen(path, "r");
   if (!f) return -1;
@@ -3929,7 +3945,13 @@ void cache_store(const char* path, const std::string& arch, Engine eng, int64_t 
 }
 
 // Time every variant of one engine at padded size Np (a few products each) and
-// keep the fastest; a cached choice for this architecture is taken as is.
+// keep the one with the smallest sum over the forms a solve runs: full and
+// symmetric products (the tiles of the FP64 and FP32 kernels differ: Np = 2048,
+// FP64, full 310 us with variant 0 and 297 with 1, symmetric 241 and 296), and
+// with int8 both of a dense matrix and of one that decays away from the
+// diagonal, whose zero digits only variants 0 and 1 leave out (Np = 4096, 13
+// products: dense 704 and 662 us, banded iterates 163 and 662).  A cached
+// choice for this architecture is taken as is.
 dmpt_status tune_engine(dmpt_ctx c, Engine eng, int64_t N, int* chosen) {
   const int64_t Np = padded(N);
   const int acc64 = acc64_of(c, eng);
@@ -3942,17 +3964,25 @@ dmpt_status tune_engine(dmpt_ctx c, Engine eng, int64_t N, int* chosen) {
     const size_t colon = arch.find(':');
     if (colon != std::string::npos) arch.resize(colon);
     if (arch.empty()) arch = "unknown";
+    arch += "/" + std::to_string(kTuneSet);
   }
   int best = path ? cache_lookup(path, arch, eng, Np, acc64) : -1;
   if (best < 0 || best >= nv) {
     best = 0;
     double best_ms = INFINITY;
     const int reps = Np >= 4096 ? 2 : (Np >= 1024 ? 5 : 20);
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, DMPT_ERR_HIP, "hipSetDevice failed");
+    ENTER(c);
     for (int v = 0; v < nv; ++v) {
-      double ms = 0.0;
-      STCHK(dmpt_bench_product(c, N, prec_of(eng), v, reps, &ms, nullptr));
-      if (ms < best_ms) {
-        best_ms = ms;
+      double sum = 0.0;
+      for (int form = 0; form < (engine_int8(eng) ? 4 : 2); ++form) {
+        double ms = 0.0;
+        // a decay length of 32: a digit per 177 rows
+        STCHK(time_product(c, N, eng, v, reps, form & 2 ? 1.0 / 32.0 : 0.0, (form & 1) != 0, &ms));
+        sum += ms;
+      }
+      if (sum < best_ms) {
+        best_ms = sum;
         best = v;
       }
     }

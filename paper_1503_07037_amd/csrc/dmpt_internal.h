@@ -355,10 +355,11 @@ hipError_t set_values(int* p, int v, int n, double* q, double qv, int nq, hipStr
 // dst[z] = src[z / div] for z < n (member masks from system masks)
 hipError_t expand_mask(const int* src, int div, int* dst, int n, hipStream_t s);
 
-// Hashed pattern in [-1, 1) (with planes), for timing runs.
+// Hashed pattern in [-1, 1) (with planes), for timing runs; with decay, times
+// exp(-decay |row - column|) of an ld x ld matrix.
 template <class T>
 hipError_t fill_pattern(T* x, int64_t n, uint32_t seed, uint16_t* const* planes, int nplanes,
-                        hipStream_t s);
+                        hipStream_t s, int64_t ld = 0, double decay = 0.0);
 
 // Linear canonical correction of one system's order-k responses, k = order
 // (1 or 2; batched solve): with t its trace record (Tr Pk_z at 1 + (k-1) d + z,

@@ -906,16 +906,18 @@ __global__ void k_expand(const int* src, int div, int* dst, int n) {
   if (i < n) dst[i] = src[i / div];
 }
 
-// Deterministic non-trivial fill (a hashed pattern in [-1, 1)) with planes.
+// Deterministic non-trivial fill (a hashed pattern in [-1, 1)) with planes; with decay,
+// times exp(-decay |row - column|) of an ld x ld matrix.
 template <class T>
 __global__ __launch_bounds__(kT) void k_fill(T* x, int64_t n, uint32_t seed, Planes pl, int np,
-                                             int64_t Np) {
+                                             int64_t Np, int64_t ld, double decay) {
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT) {
     uint32_t h = (uint32_t)i * 2654435761u ^ seed;
     h ^= h >> 15;
     h *= 2246822519u;
     h ^= h >> 13;
-    const T v = (T)((double)(h & 0xffffff) / 8388608.0 - 1.0);
+    T v = (T)((double)(h & 0xffffff) / 8388608.0 - 1.0);
+    if (decay > 0.0) v = (T)((double)v * exp(-decay * fabs((double)(i / ld - i % ld))));
     x[i] = v;
     if (np) split_store((double)v, pl.p, np, plane_off_lin(i, Np));
   }
@@ -1676,16 +1678,19 @@ hipError_t expand_mask(const int* src, int div, int* dst, int n, hipStream_t s) 
 
 template <class T>
 hipError_t fill_pattern(T* x, int64_t n, uint32_t seed, uint16_t* const* planes, int nplanes,
-                        hipStream_t s) {
+                        hipStream_t s, int64_t ld, double decay) {
+  if (decay > 0.0 && ld < 1) return hipErrorInvalidValue;
   Planes pl{{nullptr, nullptr, nullptr}};
   for (int p = 0; p < nplanes; ++p) pl.p[p] = planes[p];
   const int64_t Np = nplanes ? plane_np(n) : 0;
   if (nplanes && !Np) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_fill<T>, dim3(ew_grid(n)), dim3(kT), 0, s, x, n, seed, pl, nplanes, Np);
+  hipLaunchKernelGGL(k_fill<T>, dim3(ew_grid(n)), dim3(kT), 0, s, x, n, seed, pl, nplanes, Np, ld, decay);
   return hipGetLastError();
 }
-template hipError_t fill_pattern<double>(double*, int64_t, uint32_t, uint16_t* const*, int, hipStream_t);
-template hipError_t fill_pattern<float>(float*, int64_t, uint32_t, uint16_t* const*, int, hipStream_t);
+template hipError_t fill_pattern<double>(double*, int64_t, uint32_t, uint16_t* const*, int, hipStream_t, int64_t,
+                                         double);
+template hipError_t fill_pattern<float>(float*, int64_t, uint32_t, uint16_t* const*, int, hipStream_t, int64_t,
+                                        double);
 
 hipError_t lin_correct(double* t, int d, int J, int rs0, double* mu, double* shift, double c,
                        double* delta, double* const* P1, const double* PJ, int64_t N, const int* gate,

@@ -102,3 +102,32 @@ def test_batched_solve_tunes_every_bucket(dm):
     for k, r in enumerate(refs):
         assert np.abs(P0[k].cpu().numpy() - r["P0"]).max() < 1e-6
         assert np.abs(P1[k][0].cpu().numpy() - r["P1"][0]).max() < 1e-6 * np.abs(r["P1"][0]).max()
+
+
+@pytest.mark.parametrize("prec,N,fit", [("int8x13", 4096, (0, 1)), ("int8x6", 2048, (0, 1)), ("fp64", 2048, (0,))])
+def test_autotune_picks_by_the_products_of_a_solve(dm, prec, N, fit):
+    """The choice holds for what solves run, not for one dense full product: int8 variants 2 and 3
+    are up to 6 % faster there but cannot leave out zero digits (a factor of 4 on decaying matrices),
+    FP64 variant 1 is 4 % faster there and 20 % slower on symmetric products."""
+    with dm.Context(N, dirs_max=0, prec=prec) as ctx:
+        v = ctx.autotune(N)
+        print(f"  tuned {prec} N={N}: variant {v}", flush=True)
+        assert v in fit
+
+
+def test_tune_cache_of_other_kernels_is_ignored(dm, tmp_path, monkeypatch):
+    """A cache line without the version of the kernels behind the variant numbers is not a choice
+    between them (here: a variant that is slower by a factor of 3), and is left in the file."""
+    N = 512
+    path = tmp_path / "tune.txt"
+    path.write_text("gfx950 0 512 0 2 0.110400\n")
+    monkeypatch.setenv("DMPT_TUNE_CACHE", str(path))
+    with dm.Context(N, dirs_max=0, prec="fp64") as ctx:
+        v = ctx.autotune(N)
+        print(f"  tuned fp64 N={N}: variant {v}", flush=True)
+        assert v != 2
+    lines = path.read_text().splitlines()
+    assert lines[0] == "gfx950 0 512 0 2 0.110400" and len(lines) == 2
+    with dm.Context(N, dirs_max=0, prec="fp64") as ctx:
+        assert ctx.autotune(N) == v
+    assert path.read_text().splitlines() == lines
