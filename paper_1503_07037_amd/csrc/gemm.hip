@@ -109,6 +109,27 @@ __device__ inline double block_sum(double v, double* red) {
   return s;
 }
 
+// block_sum over H values per thread, as if the block had H times the waves (set h of wave w
+// is wave h * (number of waves) + w).
+template <int H>
+__device__ inline double block_sum_sets(double (&v)[H], double* red) {
+  const int w = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6);
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v[h] += __shfl_xor(v[h], o, 64);
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+    if ((threadIdx.x & 63) == 0) red[h * nw + w] = v[h];
+  __syncthreads();
+  double s = 0.0;
+  if (threadIdx.x == 0) {
+    for (int i = 0; i < H * nw; ++i) s += red[i];
+  }
+  return s;
+}
+
 // Round-to-nearest-even FP32 -> BF16 bits.
 __device__ inline uint16_t bf16_rne(float x) {
   uint32_t u = __float_as_uint(x);
@@ -342,17 +363,53 @@ constexpr int small_ld() { return TM + 1; }
 template <int TM, int KS>
 constexpr size_t small_lds() { return (size_t)KS * TM * small_ld<TM>() * sizeof(double); }
 
-// Epilogue of the small-tile FP64 and FP32 kernels, whose KS k groups left
-// their partial TM x TM tiles in LDS (rows of TM + 1 doubles, small_lds bytes;
-// the caller has synchronised): they are summed in the order of ks.  With sym
-// the block writes its tile and the mirrored one.
+// The k groups of the small-tile FP64 kernels.  The 16-wide k chunks of a tile
+// go to G groups in turn, whose partial tiles are added in order.  G depends on
+// the tile edge alone, so the bits of a product do not depend on the launch: a
+// block of KS waves per 32 x 32 quadrant takes the groups in H = G / KS sets
+// with an accumulator each, and the partials of <W, C> are added as G waves per
+// quadrant would.  (With G = KS, chosen by the number of blocks, a direction
+// alone and one of three differed in the last bits.)  The second set also
+// breaks the chain of MFMAs on one accumulator: 64-wide tiles, one set against
+// two, 2048 310 and 253 us, 2432 485 and 445; with 16 waves and one set 1024
+// takes 44 us, with 8 and two 42.
+constexpr int kGroups32 = 8, kGroups64 = 4;
+
+// Elements of a TM x TM tile per thread of a block with KS waves per quadrant.
 template <int TM, int KS>
+constexpr int small_per() { return 16 / KS; }
+
+// v: the sums of the KS H partial tiles, added in the order of the sets and,
+// within one, of ks (store(h) leaves set h's tiles in LDS, rows of TM + 1
+// doubles, small_lds bytes).
+template <int TM, int KS, int H, class Store>
+__device__ __forceinline__ void partial_sums(double* s, Store store, double (&v)[small_per<TM, KS>()]) {
+  constexpr int THREADS = (TM / 32) * (TM / 32) * KS * 64, LD = small_ld<TM>(), PART = TM * LD;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    if (h) __syncthreads();
+    store(h);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < small_per<TM, KS>(); ++u) {
+      const int e = threadIdx.x + u * THREADS;
+      const double* t = s + (e / TM) * LD + e % TM;
+#pragma unroll
+      for (int p = 0; p < KS; ++p) v[u] = h + p ? v[u] + t[p * PART] : t[0];
+    }
+  }
+}
+
+// Epilogue of the small-tile FP64 and FP32 kernels with the sums v of
+// partial_sums.  With sym the block writes its tile and the mirrored one (from
+// LDS, over the first partial tile: every thread over the elements it read).
+template <int TM, int KS, int H>
 __device__ __forceinline__ void partial_epilogue(const GemmArgs& a, int z, int bx, int nbx, int tm, int tn, double* s,
-                                                 double* red) {
+                                                 double* red, const double (&acc)[small_per<TM, KS>()]) {
   constexpr int THREADS = (TM / 32) * (TM / 32) * KS * 64;
-  constexpr int LD = small_ld<TM>(), PART = TM * LD;
-  constexpr int PER = TM * TM / THREADS;
-  static_assert(PER >= 1, "at least one output element per thread");
+  constexpr int LD = small_ld<TM>();
+  constexpr int PER = small_per<TM, KS>();
+  static_assert(PER >= 1 && PER % H == 0, "whole rounds of the H sets");
   const int64_t Np = a.Np;
   const int tid = threadIdx.x;
   // a diagonal tile's elements above the diagonal are computed too (so the loads need no branch) and
@@ -364,22 +421,19 @@ __device__ __forceinline__ void partial_epilogue(const GemmArgs& a, int z, int b
     return base + (int64_t)(e / TM) * Np + e % TM;
   };
   constexpr int NV = PER < 4 ? PER : 4;
-  double dsum = 0.0;
+  double dsum[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) dsum[h] = 0.0;
 #pragma unroll
   for (int u0 = 0; u0 < PER; u0 += NV) {
     double v[NV], out[NV], w[NV];
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      const int e = tid + (u0 + u) * THREADS, r = e / TM, c = e % TM;
-      v[u] = s[r * LD + c];
-#pragma unroll
-      for (int p = 1; p < KS; ++p) v[u] += s[p * PART + r * LD + c];
-    }
+    for (int u = 0; u < NV; ++u) v[u] = acc[u0 + u];
     epi_values<NV>(a, z, [&](int u) { return off(u0 + u); }, v, out, w);
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
       const int e = tid + (u0 + u) * THREADS, r = e / TM, c = e % TM;
-      dsum += w[u] * out[u];
+      dsum[(u0 + u) % H] = __builtin_fma(w[u], out[u], dsum[(u0 + u) % H]);
       if (a.sym) s[r * LD + c] = out[u];
     }
   }
@@ -393,7 +447,7 @@ __device__ __forceinline__ void partial_epilogue(const GemmArgs& a, int z, int b
     }
   }
   if (a.W) {
-    const double t = block_sum(dsum, red);
+    const double t = block_sum_sets<H>(dsum, red);
     if (tid == 0) a.partials[(int64_t)z * nbx + bx] = t;
   }
 }
@@ -413,40 +467,45 @@ __device__ __forceinline__ void f64_store_partial(double* s, int ks, int qm, int
         s[ks * PART + (qm * 32 + i * 16 + 4 * r + (lane >> 4)) * LD + qn * 32 + j * 16 + (lane & 15)] = acc[i][j][r];
 }
 
+template <int H>
+__device__ __forceinline__ void f64_zero(d4v (&acc)[H][2][2]) {
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[h][i][j] = (d4v){0.0, 0.0, 0.0, 0.0};
+}
+
 // Direct form for products that leave most of the chip idle with 128 x 128
-// tiles (see small_edge): TM x TM output tile per workgroup (used with TM = 32;
-// from 64 on the operands are staged through LDS, gemm_f64_lds64_tile), KS
-// waves per 32 x 32 quadrant that take the 16-wide k chunks in turn, so even
-// an Np = 128 product runs on 16 CUs with a serial chain of one or two chunks
-// instead of 16 LDS stages on one CU.  Each lane loads four consecutive k of a
-// row (two 16-byte loads; the four lane groups together one 128-byte line)
-// straight into registers: both operands then hold k = 4 (lane / 16) + e in
-// element e, the same order on both sides, which is all the MFMA needs.  No
-// LDS in the k loop, the next chunk's loads run under the current chunk's 16
-// MFMAs.  The KS partial tiles are summed through LDS in a fixed order.  With
-// sym the block writes its tile and the mirrored one from LDS, so no
-// mirroring pass follows.
-template <int TM, int KS>
+// tiles (see small_edge): 32 x 32 output tile per workgroup (from 64 on the
+// operands are staged through LDS, gemm_f64_lds64_tile), KS waves that take the
+// 16-wide k chunks in turn, so even an Np = 128 product runs on 16 CUs with a
+// serial chain of one or two chunks instead of 16 LDS stages on one CU.  Each
+// lane loads four consecutive k of a row (two 16-byte loads; the four lane
+// groups together one 128-byte line) straight into registers: both operands
+// then hold k = 4 (lane / 16) + e in element e, the same order on both sides,
+// which is all the MFMA needs.  No LDS in the k loop, the next chunk's loads
+// run under the current chunk's 16 MFMAs.  The partial tiles are summed through
+// LDS in a fixed order.  With sym the block writes its tile and the mirrored
+// one from LDS, so no mirroring pass follows.
+template <int KS>
 __device__ __forceinline__ void gemm_f64_direct_tile(const GemmArgs& a, int z, int bx, int nbx) {
-  constexpr int QS = TM / 32, NQ = QS * QS, NW = NQ * KS;
+  constexpr int TM = 32, H = kGroups32 / KS;
+  static_assert(H == 1 || H == 2, "the loop alternates two chunks");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ double red[NW];
+  __shared__ double red[kGroups32];
   if (a.active && !a.active[z]) return;
   count_member(a, bx);
   const int64_t Np = a.Np;
   int tm, tn;
   tile_coords(bx, (int)(Np / TM), (int)(Np / TM), tm, tn, a.sym);
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int quad = wave % NQ, ks = wave / NQ;
-  const int qm = quad / QS, qn = quad % QS;
+  const int tid = threadIdx.x, lane = tid & 63, ks = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t lrow = (int64_t)(lane & 15) * Np + 2 * (lane >> 4);
-  const double* X = (const double*)a.X.m + (z / a.X.div) * a.X.stride + ((int64_t)tm * TM + qm * 32) * Np + lrow;
-  const double* Y = (const double*)a.Y.m + (z / a.Y.div) * a.Y.stride + ((int64_t)tn * TM + qn * 32) * Np + lrow;
-  d4v acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (d4v){0.0, 0.0, 0.0, 0.0};
+  const double* X = (const double*)a.X.m + (z / a.X.div) * a.X.stride + (int64_t)tm * TM * Np + lrow;
+  const double* Y = (const double*)a.Y.m + (z / a.Y.div) * a.Y.stride + (int64_t)tn * TM * Np + lrow;
+  d4v acc[H][2][2];
+  f64_zero<H>(acc);
   struct Frag {
     d2f v[2][2];  // [16-row group][half of the four k]
   };
@@ -460,15 +519,14 @@ __device__ __forceinline__ void gemm_f64_direct_tile(const GemmArgs& a, int z, i
         y.v[i][h] = *(const d2f*)(Y + (int64_t)i * 16 * Np + k0 + 8 * h);
       }
   };
-  auto mma = [&](const Frag& x, const Frag& y) {
+  auto mma = [&](const Frag& x, const Frag& y, d4v (&c)[2][2]) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.v[i][e >> 1][e & 1], y.v[j][e >> 1][e & 1],
-                                                           acc[i][j], 0, 0, 0);
+          c[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.v[i][e >> 1][e & 1], y.v[j][e >> 1][e & 1], c[i][j], 0, 0, 0);
   };
   // a tile that lies in the padding has a zero product
   const int nch = (tm * TM < a.Ne && tn * TM < a.Ne) ? (int)((a.Ne + 15) >> 4) : 0;
@@ -477,37 +535,37 @@ __device__ __forceinline__ void gemm_f64_direct_tile(const GemmArgs& a, int z, i
   if (ch < nch) load(x0, y0, ch);
   while (ch < nch) {
     if (ch + KS < nch) load(x1, y1, ch + KS);
-    mma(x0, y0);
+    mma(x0, y0, acc[0]);
     ch += KS;
     if (ch >= nch) break;
     if (ch + KS < nch) load(x0, y0, ch + KS);
-    mma(x1, y1);
+    mma(x1, y1, acc[H - 1]);
     ch += KS;
   }
-  f64_store_partial<TM>((double*)smem, ks, qm, qn, acc);
-  __syncthreads();
-  partial_epilogue<TM, KS>(a, z, bx, nbx, tm, tn, (double*)smem, red);
+  double v[small_per<TM, KS>()];
+  partial_sums<TM, KS, H>((double*)smem, [&](int h) { f64_store_partial<TM>((double*)smem, ks, 0, 0, acc[h]); }, v);
+  partial_epilogue<TM, KS, H>(a, z, bx, nbx, tm, tn, (double*)smem, red, v);
 }
 
-template <int TM, int KS>
-__global__ __launch_bounds__((TM / 32) * (TM / 32) * KS * 64) void k_gemm_f64_direct(GemmArgs a) {
-  gemm_f64_direct_tile<TM, KS>(a, blockIdx.z, blockIdx.x, gridDim.x);
+template <int KS>
+__global__ __launch_bounds__(KS * 64) void k_gemm_f64_direct(GemmArgs a) {
+  gemm_f64_direct_tile<KS>(a, blockIdx.z, blockIdx.x, gridDim.x);
 }
 
-template <int TM, int KS>
-__global__ __launch_bounds__((TM / 32) * (TM / 32) * KS * 64) void k_gemm_f64_direct_grouped(
-    const GemmArgs* __restrict__ list, const int* __restrict__ start, int nprob) {
+template <int KS>
+__global__ __launch_bounds__(KS * 64) void k_gemm_f64_direct_grouped(const GemmArgs* __restrict__ list,
+                                                                     const int* __restrict__ start, int nprob) {
   int p = 0;
   const int b = blockIdx.x;
   while (p + 1 < nprob && b >= start[p + 1]) ++p;
   const GemmArgs& a = list[p];
-  const int tiles = grouped_tiles(a, TM);
+  const int tiles = grouped_tiles(a, 32);
   const int local = b - start[p];
-  gemm_f64_direct_tile<TM, KS>(a, local / tiles, local % tiles, tiles);
+  gemm_f64_direct_tile<KS>(a, local / tiles, local % tiles, tiles);
 }
 
-// 64 x 64 output tile, KS groups of four waves (32 x 32 each) that take the
-// 16-wide k chunks in turn, operands staged through LDS (rows of 128 bytes
+// 64 x 64 output tile, KS times four waves (32 x 32 each) that take the
+// 16-wide k chunks in turn (kGroups64), operands staged through LDS (rows of 128 bytes
 // padded to 144: the 16-byte fragment reads of 16 rows fall on different
 // banks), two LDS stages and one register stage.
 constexpr int kF64LdRow = 18;  // doubles per staged row
@@ -519,9 +577,10 @@ constexpr size_t f64_lds64_lds() {
 
 template <int KS>
 __device__ __forceinline__ void gemm_f64_lds64_tile(const GemmArgs& a, int z, int bx, int nbx) {
-  constexpr int NW = 4 * KS;
+  constexpr int H = kGroups64 / KS;
+  static_assert(H == 1 || H == 2, "the sets alternate like the LDS stages");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ double red[NW];
+  __shared__ double red[4 * kGroups64];
   if (a.active && !a.active[z]) return;
   count_member(a, bx);
   const int64_t Np = a.Np;
@@ -554,11 +613,8 @@ __device__ __forceinline__ void gemm_f64_lds64_tile(const GemmArgs& a, int z, in
       *(d2f*)(d + (64 + i * 32) * kF64LdRow) = gy[i];
     }
   };
-  d4v acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (d4v){0.0, 0.0, 0.0, 0.0};
+  d4v acc[H][2][2];
+  f64_zero<H>(acc);
   const int nch = (tm * 64 < a.Ne && tn * 64 < a.Ne) ? (int)((a.Ne + 15) >> 4) : 0;
   const int rounds = (nch + KS - 1) / KS;  // the same for every group (the barriers)
   if (ks < nch) {
@@ -568,7 +624,7 @@ __device__ __forceinline__ void gemm_f64_lds64_tile(const GemmArgs& a, int z, in
   }
   __syncthreads();
   const int foff = (lane & 15) * kF64LdRow + 2 * (lane >> 4);
-  for (int rd = 0; rd < rounds; ++rd) {
+  auto round = [&](int rd, d4v (&c)[2][2]) {
     const int ch = ks + rd * KS;
     if (ch < nch) {
       const double* sx = base + (rd & 1) * 2 * 64 * kF64LdRow + qm * 32 * kF64LdRow + foff;
@@ -583,7 +639,7 @@ __device__ __forceinline__ void gemm_f64_lds64_tile(const GemmArgs& a, int z, in
         }
       // the staging of the next chunk goes between the halves of the MFMAs, so
       // they start as soon as the fragments are there (2432 full 495 -> 490 us,
-      // three members of 1024 124 -> 116)
+      // three members of 1024 124 -> 116; with one accumulator set)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         if (e == 2 && ch + KS < nch) {
@@ -596,15 +652,20 @@ __device__ __forceinline__ void gemm_f64_lds64_tile(const GemmArgs& a, int z, in
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[i][e >> 1][e & 1], yv[j][e >> 1][e & 1], acc[i][j], 0,
-                                                             0, 0);
+            c[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[i][e >> 1][e & 1], yv[j][e >> 1][e & 1], c[i][j], 0, 0,
+                                                           0);
       }
     }
     __syncthreads();
+  };
+  for (int rd = 0; rd < rounds; rd += H) {
+    round(rd, acc[0]);
+    if (H > 1 && rd + 1 < rounds) round(rd + 1, acc[H - 1]);
   }
-  f64_store_partial<64>((double*)smem, ks, qm, qn, acc);  // the last round ended with a barrier
-  __syncthreads();
-  partial_epilogue<64, KS>(a, z, bx, nbx, tm, tn, (double*)smem, red);
+  // the last round ended with a barrier
+  double v[small_per<64, KS>()];
+  partial_sums<64, KS, H>((double*)smem, [&](int h) { f64_store_partial<64>((double*)smem, ks, qm, qn, acc[h]); }, v);
+  partial_epilogue<64, KS, H>(a, z, bx, nbx, tm, tn, (double*)smem, red, v);
 }
 
 template <int KS>
@@ -921,8 +982,9 @@ __device__ __forceinline__ void gemm_f32_lds64_tile(const GemmArgs& a, int z, in
 #pragma unroll
     for (int r = 0; r < 16; ++r)
       s[(qm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * small_ld<64>() + qn * 32 + (lane & 31)] = accd[r];
-    __syncthreads();
-    partial_epilogue<64, 1>(a, z, bx, nbx, tm, tn, s, nullptr);
+    double v[small_per<64, 1>()];
+    partial_sums<64, 1, 1>(s, [](int) {}, v);
+    partial_epilogue<64, 1, 1>(a, z, bx, nbx, tm, tn, s, nullptr, v);
     return;
   }
   const int64_t base_off = ((int64_t)tm * 64 + qm * 32 + 4 * (lane >> 5)) * Np + (int64_t)tn * 64 + qn * 32 + (lane & 31);
@@ -984,10 +1046,10 @@ __global__ __launch_bounds__(256, 4) void k_gemm_f32_lds64_grouped(const GemmArg
 // tiles fill the 256 CUs several times.  Measured per product, full /
 // symmetric (us; 128-wide tiles, 64-wide ones, 32-wide ones):
 //   FP64  Np 128: 23 / 23, 9 / 10, 5.2 / 5.5;  512: 78 / 81, 23 / 24, 12 / 12;  768:
-//   115 / 118, 34 / 34, 38 / 27;  1024: 151 / 156, 45 / 44, 67 / 51;  2048: 321 / 314,
-//   321 / 241;  2432: 648 / 647, 568 / 297;  3072: 1565 / 807, 1076 / 596;  4096: 2187 /
-//   1675, 2396 / 1368 (full products of three members at 4096: 6.1 and 6.7 ms,
-//   the 128-wide tiles' 68 TFLOP/s against 62).
+//   115 / 118, 32 / 34, 38 / 27;  1024: 151 / 156, 42 / 43, 67 / 51;  2048: 321 / 314,
+//   253 / 196;  2432: 648 / 647, 445 / 243;  3072: 1565 / 807, 836 / 480;  4096: 2187 /
+//   1667, - / 1125 (full products of three members at 4096, with one accumulator
+//   set: 6.1 and 6.7 ms, the 128-wide tiles' 68 TFLOP/s against 62).
 //   FP32  (with C1, C2 and W) Np 128: 27 full, 16 symmetric, 8.7 / 8.4;  256: 39 / 28, 12.5 /
 //   12.2;  512: 62 / 51, 20 / 20;  1024: 125 / 100, 40 / 36;  2432: 549 / 492, 387 / 195
 //   (three members 1479 / 1272, 1108 / 578);  4096: 1910 / 1737, 1700 / 900 (three members
@@ -1001,9 +1063,11 @@ int small_edge(Engine eng, int64_t Np) {
 // Symmetric products keep the 64-wide tiles: twice the granularity, and the
 // mirrored tile is written from LDS instead of by a mirroring pass.
 int small_sym_edge(Engine eng, int64_t Np) { return std::min(64, small_edge(eng, Np)); }
-// k groups per FP64 block: with no more blocks than CUs every block has its CU
-// to itself, and more waves hide the latency of its serial k loop (Np = 1024,
-// one full product: 45 us with 4 groups, 49 with 2; three members: 132 and 129).
+// Waves per block of the 32-wide FP64 tiles (the sums are those of 8 k groups
+// either way): with no more blocks than CUs every block has its CU to itself,
+// and more waves hide the latency of its serial k loop (one full product at Np =
+// 128 5.3 us with 8 waves, 6.2 with 4, at 512 11.6 and 12.0; three members at
+// 512 27.0 and 26.0).
 bool few_blocks(int blocks) { return blocks <= 256; }
 
 template <class K>
@@ -1013,10 +1077,9 @@ hipError_t lds_attr(K* kernel, size_t lds) {
 
 hipError_t prepare_small() {
   hipError_t e;
-  if ((e = lds_attr(k_gemm_f64_direct<32, 8>, small_lds<32, 8>()))) return e;
-  if ((e = lds_attr(k_gemm_f64_direct<32, 4>, small_lds<32, 4>()))) return e;
-  if ((e = lds_attr(k_gemm_f64_direct_grouped<32, 4>, small_lds<32, 4>()))) return e;
-  if ((e = lds_attr(k_gemm_f64_lds64<4>, f64_lds64_lds<4>()))) return e;
+  if ((e = lds_attr(k_gemm_f64_direct<8>, small_lds<32, 8>()))) return e;
+  if ((e = lds_attr(k_gemm_f64_direct<4>, small_lds<32, 4>()))) return e;
+  if ((e = lds_attr(k_gemm_f64_direct_grouped<4>, small_lds<32, 4>()))) return e;
   if ((e = lds_attr(k_gemm_f64_lds64<2>, f64_lds64_lds<2>()))) return e;
   if ((e = lds_attr(k_gemm_f64_lds64_grouped<2>, f64_lds64_lds<2>()))) return e;
   if ((e = lds_attr(k_gemm_f32_lds64<kF32SmallBK>, f32_lds64_lds<kF32SmallBK>()))) return e;
@@ -1029,9 +1092,8 @@ hipError_t launch_small(const GemmArgs& a, int edge, int tiles, hipStream_t s) {
   if (a.eng == Engine::F32)
     hipLaunchKernelGGL(k_gemm_f32_lds64<kF32SmallBK>, grid, dim3(256), f32_lds64_lds<kF32SmallBK>(), s, a);
   else if (edge == 32 && few)
-    hipLaunchKernelGGL((k_gemm_f64_direct<32, 8>), grid, dim3(512), (small_lds<32, 8>()), s, a);
-  else if (edge == 32) hipLaunchKernelGGL((k_gemm_f64_direct<32, 4>), grid, dim3(256), (small_lds<32, 4>()), s, a);
-  else if (few) hipLaunchKernelGGL(k_gemm_f64_lds64<4>, grid, dim3(1024), f64_lds64_lds<4>(), s, a);
+    hipLaunchKernelGGL((k_gemm_f64_direct<8>), grid, dim3(512), (small_lds<32, 8>()), s, a);
+  else if (edge == 32) hipLaunchKernelGGL((k_gemm_f64_direct<4>), grid, dim3(256), (small_lds<32, 4>()), s, a);
   else hipLaunchKernelGGL(k_gemm_f64_lds64<2>, grid, dim3(512), f64_lds64_lds<2>(), s, a);
   return hipGetLastError();
 }
@@ -1043,7 +1105,7 @@ hipError_t launch_small_grouped(Engine eng, int edge, const GemmArgs* list, cons
     hipLaunchKernelGGL(k_gemm_f32_lds64_grouped<kF32SmallBK>, grid, dim3(256), f32_lds64_lds<kF32SmallBK>(), s, list,
                        start, nprob);
   else if (edge == 32)
-    hipLaunchKernelGGL((k_gemm_f64_direct_grouped<32, 4>), grid, dim3(256), (small_lds<32, 4>()), s, list, start, nprob);
+    hipLaunchKernelGGL((k_gemm_f64_direct_grouped<4>), grid, dim3(256), (small_lds<32, 4>()), s, list, start, nprob);
   else
     hipLaunchKernelGGL(k_gemm_f64_lds64_grouped<2>, grid, dim3(512), f64_lds64_lds<2>(), s, list, start, nprob);
   return hipGetLastError();

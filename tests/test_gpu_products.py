@@ -150,3 +150,29 @@ def test_int8_slices_of_earlier_calls(dm, solver):
             print(f"case int8 slices of earlier calls {solver} {k} N={h0.shape[0]}", flush=True)
             with dm.Context(640, **opts) as fresh:
                 assert np.array_equal(solve(used, h0), solve(fresh, h0)), k
+
+
+@pytest.mark.parametrize("N", [96, 200, 384, 500, 700, 1000, 1400])
+def test_fp64_bits_do_not_depend_on_the_company(dm, N):
+    """A direction gives the same bits alone and beside others, and a system of a batch the same
+    whether products are launched per bucket or for all buckets together: the k groups a product's
+    sums are split into follow from its size, not from the number of blocks of the launch."""
+    print(f"case fp64 bits N={N}", flush=True)
+    rng = np.random.default_rng(N)
+    H0 = T(workloads.banded(N, 5))
+    H1 = [T(np.diag(rng.standard_normal(N))) for _ in range(3)]
+    with dm.Context(N, dirs_max=3, prec="fp64") as ctx:
+        got = [ctx.response(H0, H1[:d], beta=10.0, n=20, order=1, mu=[0.05] + [0.0] * d) for d in (1, 2, 3)]
+        for r in got[1:]:
+            assert torch.equal(r[0], got[0][0]) and torch.equal(r[1][0], got[0][1][0])
+    small = [64, N // 2, N]
+    H0s = [H0] + [T(workloads.banded(e, 9 + i)) for i, e in enumerate(small)]
+    H1s = [[H1[0]]] + [[T(np.diag(np.linspace(-1.0, 1.0, e)))] for e in small]
+    out = []
+    for count, grouped in ((1, 1), (4, 1), (4, 0)):
+        with dm.Context(N, dirs_max=1, prec="fp64", grouped=grouped) as ctx:
+            P0, P1, _, _, _ = ctx.mu_newton_batched(H0s[:count], H1s[:count], [10.0] * count,
+                                                    [h.shape[0] / 2.0 for h in H0s[:count]], n=20, order=1)
+            out.append((P0[0], P1[0][0]))
+    for p0, p1 in out[1:]:
+        assert torch.equal(p0, out[0][0]) and torch.equal(p1, out[0][1])
