@@ -2926,32 +2926,20 @@ dmpt_status build_plan(dmpt_ctx c, BatchedPlan& plan, std::vector<void*>& owned)
     plan.in_ews.clear();
     plan.out_ews.clear();
   }
-  if (list.empty()) {
-    // nothing to multiply: every launch is issued by itself
-    plan.in_ews.clear();
-    plan.ew_group.assign(nops, -1);
+  // each list is there if it has entries: what refers to it was added with them
+  auto upload = [&](auto*& d, const auto& host) -> dmpt_status {
+    if (host.empty()) return DMPT_OK;
+    const size_t bytes = host.size() * sizeof(host[0]);
+    d = (std::remove_reference_t<decltype(d)>)dev_alloc(c, bytes);
+    if (!d) return fail(c, DMPT_ERR_NOMEM, "batched plan allocation failed");
+    owned.push_back(d);
+    HIPCHK(c, hipMemcpy(d, host.data(), bytes, hipMemcpyHostToDevice));
     return DMPT_OK;
-  }
-  if (!ewlist.empty()) {
-    plan.d_ewlist = (EwArgs*)dev_alloc(c, ewlist.size() * sizeof(EwArgs));
-    if (!plan.d_ewlist) return fail(c, DMPT_ERR_NOMEM, "batched plan allocation failed");
-    owned.push_back(plan.d_ewlist);
-    HIPCHK(c, hipMemcpy(plan.d_ewlist, ewlist.data(), ewlist.size() * sizeof(EwArgs), hipMemcpyHostToDevice));
-  }
-  plan.d_list = (GemmArgs*)dev_alloc(c, list.size() * sizeof(GemmArgs));
-  plan.d_start = (int*)dev_alloc(c, starts.size() * sizeof(int));
-  if (!cglist.empty()) {
-    plan.d_cglist = (CgArgs*)dev_alloc(c, cglist.size() * sizeof(CgArgs));
-    if (plan.d_cglist) owned.push_back(plan.d_cglist);
-  }
-  if (!plan.d_list || !plan.d_start || (!cglist.empty() && !plan.d_cglist))
-    return fail(c, DMPT_ERR_NOMEM, "batched plan allocation failed");
-  if (!cglist.empty())
-    HIPCHK(c, hipMemcpy(plan.d_cglist, cglist.data(), cglist.size() * sizeof(CgArgs), hipMemcpyHostToDevice));
-  owned.push_back(plan.d_list);
-  owned.push_back(plan.d_start);
-  HIPCHK(c, hipMemcpy(plan.d_list, list.data(), list.size() * sizeof(GemmArgs), hipMemcpyHostToDevice));
-  HIPCHK(c, hipMemcpy(plan.d_start, starts.data(), starts.size() * sizeof(int), hipMemcpyHostToDevice));
+  };
+  STCHK(upload(plan.d_list, list));
+  STCHK(upload(plan.d_cglist, cglist));
+  STCHK(upload(plan.d_ewlist, ewlist));
+  STCHK(upload(plan.d_start, starts));
   return DMPT_OK;
 }
 
