@@ -1108,6 +1108,18 @@ __global__ __launch_bounds__(kT) void k_qscale(const double* __restrict__ part, 
   if (threadIdx.x == 0) qs[z] = m / 127.0;
 }
 
+// Digits of a f into column e of d.  The remainders are fused explicitly, so the
+// digits do not depend on what the compiler contracts.
+__device__ __forceinline__ void q8_digits(double a, double f, int (&d)[kQ8Slices][16], int e) {
+#pragma unroll
+  for (int sl = 0; sl < kQ8Slices; ++sl) {
+    const double q = rint(a * f);
+    d[sl][e] = (int)q;
+    a = __builtin_fma(a, f, -q);
+    f = kQ8Base;
+  }
+}
+
 __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int64_t sx, int64_t Np,
                                               int8_t* __restrict__ q8, int64_t sq, double* __restrict__ qs,
                                               uint8_t* __restrict__ zm, int64_t szm, const int* active,
@@ -1160,18 +1172,7 @@ __global__ __launch_bounds__(kT) void k_quant(const double* __restrict__ x, int6
       const int row = l & 31, c0 = (l >> 5) * 16;
       int d[kQ8Slices][16];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        // the value to split is a f; the remainders are fused explicitly, so the
-        // digits do not depend on what the compiler contracts
-        double a = t[row][c0 + e], f = inv;
-#pragma unroll
-        for (int sl = 0; sl < kQ8Slices; ++sl) {
-          const double q = rint(a * f);
-          d[sl][e] = (int)q;
-          a = __builtin_fma(a, f, -q);
-          f = kQ8Base;
-        }
-      }
+      for (int e = 0; e < 16; ++e) q8_digits(t[row][c0 + e], inv, d, e);
       uint32_t digits = 0;  // the digits any lane of the block has
 #pragma unroll
       for (int sl = 0; sl < kQ8Slices; ++sl) {
@@ -1239,16 +1240,8 @@ __global__ __launch_bounds__(kT) void k_cg_p_q8(double* __restrict__ P, const do
       pv.x = rv.x + beta * pv.x;
       pv.y = rv.y + beta * pv.y;
       *(d2v*)(pm + off + e) = pv;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        double r = (h ? pv.y : pv.x) * inv;
-#pragma unroll
-        for (int sl = 0; sl < kQ8Slices; ++sl) {
-          const double t = rint(r);
-          d[sl][e + h] = (int)t;
-          r = (r - t) * kQ8Base;
-        }
-      }
+      q8_digits(pv.x, inv, d, e);
+      q8_digits(pv.y, inv, d, e + 1);
     }
     uint32_t digits = 0;  // a block is one wave's 64 pieces
 #pragma unroll
