@@ -143,3 +143,38 @@ def test_sparse_sizes_on_both_sides_of_the_host_free_form(dm, N):
             with pytest.raises(dm.DMPTError) as e:
                 ctx.sparse_response(H0, beta=beta, Ne=N / 2.0, n=n, order=0, tau=1e-9, blocks_per_row=2)
             assert "blocks_per_row" in str(e.value)
+
+
+def test_sparse_more_candidates_than_workgroups(dm):
+    """tau = 0 at N = 1300: the patterns fill (41 x 41 blocks), so a wave takes several candidate blocks in
+    turn (more than 1024); every element of orders 0 and 1 against the oracle, at the untruncated bound above."""
+    print("case sparse N=1300 tau=0", flush=True)
+    N, n, beta, Ne = 1300, 20, 10.0, 650.0
+    h0 = workloads.chain_1d(N, 6)
+    h1 = [np.diag((np.arange(N) - N / 2.0) / N)]
+    ref = oracle.canonical_response(h0, h1, None, beta, Ne, n, order=1)
+    with dm.Context(128, dirs_max=1, prec="fp64") as ctx:
+        P0, P1, _, mu, st = ctx.sparse_response(T(h0), [T(h) for h in h1], beta=beta, Ne=Ne, n=n, order=1, tau=0.0)
+    assert st["blocks_max"] > 1024
+    assert float(np.abs(P0.cpu().numpy() - ref["P0"]).max()) < 1e-10
+    assert _rel(P1[0], ref["P1"][0]) < 1e-10
+    assert abs(mu[0] - ref["mu0"]) < 1e-10
+
+
+def test_sparse_largest_host_free_size_by_windows(dm):
+    """N = 8192 (256 block rows): windows of P0 at both ends and in the middle against the oracle on the
+    stretch of chain around them, 500 sites wider on either side (P0 of the gapped chain decays by more
+    than 1e-10 over that), at the truncated bound above."""
+    print("case sparse windows N=8192", flush=True)
+    N, beta, n = 8192, 10.0, 22
+    h0 = workloads.dimer_chain(N, 5)
+    with dm.Context(128, dirs_max=1, prec="fp64") as ctx:
+        P0, _, _, mu, _ = ctx.sparse_response(T(h0), beta=beta, Ne=N / 2.0, n=n, order=0, tau=1e-9, count_thr=1e-5,
+                                              blocks_per_row=48)
+    P0 = P0.cpu().numpy()
+    for lo, hi in ((0, 200), (1000, 1200), (4000, 4200), (7992, 8192)):
+        a, b = max(0, lo - 500), min(N, hi + 500)
+        ref = oracle.density(h0[a:b, a:b], beta, n, mu[0])[lo - a:hi - a, lo - a:hi - a]
+        assert np.abs(P0[lo:hi, lo:hi] - ref).max() < 1e-6, (lo, hi)
+    far = np.abs(np.subtract.outer(np.arange(0, N, 7), np.arange(0, N, 7))) > 600
+    assert np.abs(P0[::7, ::7][far]).max() < 1e-6
