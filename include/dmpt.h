@@ -398,9 +398,11 @@ dmpt_status dmpt_congruence(dmpt_ctx ctx, int64_t N, const double* Z, const doub
                             int mode, dmpt_stats* st);
 
 /* Product-kernel variants (per engine; 0 is the default):
- *   DMPT_FP64    0: output tile edge by size (32 up to N = 512, 64 below 4096, else 128)
+ *   DMPT_FP64    0: output tile edge by padded size (32 up to 512, 64 below 4096, else 128;
+ *                symmetric products 64 from there on too)
  *                1: 128 x 128 tiles, 16-deep k stages, 8 waves   2: 128 x 128, 8-deep, 4 waves
- *   DMPT_FP32    0: output tile edge by size (32 up to N = 384, 64 below 4096, else 128)
+ *   DMPT_FP32    0: output tile edge by padded size (64 below 4096, else 128; symmetric
+ *                products 64 from there on too)
  *                1: 128 x 128 tiles, 16-deep k stages, 8 waves   2: 128 x 128, 32-deep, 4 waves
  *   DMPT_BF16X3, DMPT_BF16X6 (options.acc64 = 0)
  *                0: 256 x 256 output tiles where the padded size allows   1: 128 x 128 tiles
