@@ -30,13 +30,16 @@ current product-kernel source, else null.
 
 The accuracy-matched FP64 form (the same library in DMPT_FP64, same solvers)
 is timed on the same workload after the timed region (one solve;
---no-fp64-compare skips it).  roofline.achieved is the algorithmic rate of
-the dominant kernel: 2 N^3 flops per logical matrix product (every split
-product of the same logical product counts once) over the kernel's device
-time; the executed matrix-core rate (every split product counted) is
-reported beside it as mfma_executed and mfma_util, except for the int8
-kernels: they leave out the products of digit blocks that are zero, whose
-number only the device knows (null).
+--no-fp64-compare skips it).  For FP64, FP32 and BF16 kernels the roofline is
+the matrix cores': roofline.achieved is the algorithmic rate of the dominant
+kernel, 2 N^3 flops per logical matrix product (every split product of the
+same logical product counts once) over the kernel's device time, and the
+executed rate (every split product counted) is reported beside it as
+mfma_executed and mfma_util.  The int8 kernels leave out the products of digit
+blocks that are zero, whose number only the device knows, and are bound by
+their bytes: their roofline is the memory's, the measured traffic of a launch
+over its device time (null without a counter summary of the current kernel);
+the algorithmic rate stands beside it as algorithmic_tflops.
 
 Other modes: --copy-calibration only runs a
 plain device copy of known size, the reference that scales the FETCH_SIZE /
@@ -59,6 +62,7 @@ sys.path.insert(0, ROOT)
 # dense matrix-core peaks of an MI355X per engine (int8: TOP/s)
 PEAKS_TFLOPS = {"bf16x3": 2500.0, "bf16x6": 2500.0, "int8x13": 5000.0, "int8x6": 5000.0, "fp32": 157.3,
                 "fp64": 78.6}
+PEAK_HBM_TBS = 8.0  # HBM3E of an MI355X
 DTYPE = {"bf16x3": "bf16", "bf16x6": "bf16", "int8x13": "i8", "int8x6": "i8", "fp32": "f32", "fp64": "f64"}
 REFINE_NAME = {1: "bf16x6", 2: "int8x13"}
 
@@ -115,6 +119,23 @@ def measured_traffic(engine, alg_bytes_per_launch):
     if not ref or abs(ref - alg_bytes_per_launch) > 0.01 * ref:
         return None
     return t
+
+
+def roofline(engine, algorithmic_tflops, avg_ms, traffic):
+    """What bounds the dominant product kernel and how near it runs: the matrix cores' dense peak, or for
+    the int8 kernels, which leave out products of zero digit blocks, the memory (measured traffic)."""
+    if engine.startswith("int8"):
+        rate = traffic["bytes_per_launch"] / avg_ms / 1e9 if traffic else None  # TB/s
+        return {"bound": "hbm", "achieved": rate, "peak": PEAK_HBM_TBS, "unit": "TB/s",
+                "frac": rate / PEAK_HBM_TBS if traffic else None,
+                "achieved_measure": "measured HBM bytes per launch (traffic) over the kernel's mean device time; "
+                                    "the products of digit blocks that are zero are left out, so the matrix "
+                                    "cores' rate is no roofline (algorithmic_tflops counts them)"}
+    peak = PEAKS_TFLOPS[engine]
+    return {"bound": "mfma", "achieved": algorithmic_tflops, "peak": peak, "unit": "TFLOP/s",
+            "frac": algorithmic_tflops / peak,
+            "achieved_measure": "algorithmic: 2 N^3 per logical product and member over the kernel's device "
+                                f"time; peak is the dense matrix-core rate of the kernel's own type ({DTYPE[engine]})"}
 
 
 def copy_calibration():
@@ -472,6 +493,7 @@ def main():
     name = args.workload if not args.n else None
     acc = accuracy(name, P0, P1, P2, mu, st) if name else None
     traffic = measured_traffic(dom, pe["bytes"] / max(pe["launches"], 1))
+    roof = roofline(dom, achieved, avg_ms, traffic)
     res = {
         "metric": "response solves/sec (P0+P1+P2) and MFMA TFLOP/s at N=8192, err <=1e-6 vs FP64",
         "value": value, "unit": "responses/s", "n_gpus": 1, "steps": args.steps,
@@ -488,13 +510,7 @@ def main():
                    + (", int8 digit products summed exactly in int32" if
                       (refine == 2 or args.prec.startswith("int8")) else ""),
                    "parallelism": "single GPU"},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                     "frac": achieved / peak,
-                     "achieved_measure": "algorithmic: 2 N^3 per logical product and member over "
-                                         "the kernel's device time; peak is the dense matrix-core "
-                                         f"rate of the kernel's own type ({DTYPE[dom]})"
-                                         + ("; the products of digit blocks that are zero add nothing and "
-                                            "are left out, but count here" if executed is None else ""),
+        "roofline": {**roof, "algorithmic_tflops": achieved,
                      "mfma_executed": executed, "mfma_util": None if executed is None else executed / peak,
                      "algorithmic_flops_per_launch": pe["useful_flops"] / max(pe["launches"], 1),
                      "traffic": traffic["bytes_per_launch"] if traffic else None,

@@ -48,3 +48,15 @@ def test_workloads_are_seeded_and_shaped():
     assert len(sy) == 64 and all(256 <= s["N"] <= 3072 * 1.1 for s in sy)
     assert all(5.0 <= s["beta"] <= 40.0 and s["Ne"] == s["N"] / 2.0 for s in sy)
     assert sy == workloads.batched_systems(4, count=64)
+
+
+def test_bench_roofline_of_int8_is_the_memory(monkeypatch):
+    """The int8 kernels leave out zero digits, so their algorithmic rate is no share of a matrix-core peak;
+    without a counter summary of the current kernel their roofline is unknown."""
+    monkeypatch.syspath_prepend(ROOT)
+    import bench
+    r = bench.roofline("int8x13", 3000.0, 0.5, {"bytes_per_launch": 2.0e9})
+    assert r["bound"] == "hbm" and abs(r["achieved"] - 4.0) < 1e-12 and abs(r["frac"] - 0.5) < 1e-12
+    assert bench.roofline("int8x6", 3000.0, 0.5, None)["frac"] is None
+    r = bench.roofline("fp64", 60.0, 0.5, None)
+    assert r["bound"] == "mfma" and r["achieved"] == 60.0 and abs(r["frac"] - 60.0 / 78.6) < 1e-12
