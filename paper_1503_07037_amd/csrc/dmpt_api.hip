@@ -3934,12 +3934,13 @@ void cache_store(const char* path, const std::string& arch, Engine eng, int64_t 
 
 // Time every variant of one engine at padded size Np (a few products each) and
 // keep the one with the smallest sum over the forms a solve runs: full and
-// symmetric products (the tiles of the FP64 and FP32 kernels differ: Np = 2048,
-// FP64, full 310 us with variant 0 and 297 with 1, symmetric 241 and 296), and
+// symmetric products (the tiles of the FP64 and FP32 kernels differ: Np = 6144,
+// FP64, full 7.6 ms with variant 0 and 7.2 with 1, symmetric 3.9 and 4.2), and
 // with int8 both of a dense matrix and of one that decays away from the
 // diagonal, whose zero digits only variants 0 and 1 leave out (Np = 4096, 13
-// products: dense 704 and 662 us, banded iterates 163 and 662).  A cached
-// choice for this architecture is taken as is.
+// products: dense 704 us with variant 0 and 662 with 3, on the iterates of a
+// band matrix 163 and 662; whole call 122 and 298 ms).  A cached choice for
+// this architecture is taken as is.
 dmpt_status tune_engine(dmpt_ctx c, Engine eng, int64_t N, int* chosen) {
   const int64_t Np = padded(N);
   const int acc64 = acc64_of(c, eng);

@@ -108,7 +108,7 @@ def test_batched_solve_tunes_every_bucket(dm):
 def test_autotune_picks_by_the_products_of_a_solve(dm, prec, N, fit):
     """The choice holds for what solves run, not for one dense full product: int8 variants 2 and 3
     are up to 6 % faster there but cannot leave out zero digits (a factor of 4 on decaying matrices),
-    FP64 variant 1 is 4 % faster there and 20 % slower on symmetric products."""
+    FP64 variant 1 is about as fast there and 30 % slower on symmetric products."""
     with dm.Context(N, dirs_max=0, prec=prec) as ctx:
         v = ctx.autotune(N)
         print(f"  tuned {prec} N={N}: variant {v}", flush=True)
